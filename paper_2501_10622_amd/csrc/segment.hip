@@ -20,8 +20,8 @@
 //    pointer doubling in LDS, so every cell ends at a root or at the first cell
 //    its chain reaches outside the tile.  Such exit targets are always on a
 //    tile boundary, so only the 2312 boundary cells of each tile (kept in a
-//    compact array) take part in the global pointer-jumping rounds.  A root at or
-//    below tau is written as -1 by its own tile, so the rounds carry the
+//    compact array) have their chains followed across tiles.  A root at or
+//    below tau is written as -1 by its own tile, so the chains carry the
 //    threshold along and no later pass reads the field again.  A last pass,
 //    one workgroup per tile, loads the resolved entries of the one-cell shell
 //    around the tile (every exit target lies in it) into LDS and maps each
@@ -250,13 +250,16 @@ __global__ void __launch_bounds__(SEG_THREADS) max_tile_kernel(const float *__re
 constexpr int PR_THREADS = RX * RY;          // one z column each
 constexpr int PR_PER = RCELLS / PR_THREADS;  // RZ cells per thread
 static_assert(RHCELLS >= RCELLS, "the pointer array fits where the field was");
+constexpr int CHASE_FLAGS = 8;  // one per launch of the boundary chase, at most 4 at n = 1024
 
 template <bool FULL>
 __global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float *__restrict__ c, TileGrid rg,
                                                                     uint32_t tau_ord, int32_t *__restrict__ ptr,
                                                                     int32_t *__restrict__ bnd,
-                                                                    uint32_t *__restrict__ mask, uint32_t *status) {
+                                                                    uint32_t *__restrict__ mask,
+                                                                    uint32_t *__restrict__ flags, uint32_t *status) {
     __shared__ uint32_t V[RHCELLS];
+    if (blockIdx.x == 0 && threadIdx.x < CHASE_FLAGS) flags[threadIdx.x] = 0u;  // of the chase that follows
     int32_t *loc = reinterpret_cast<int32_t *>(V);  // after the parents are formed
     int x0, y0, z0;
     const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -425,7 +428,7 @@ __global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float 
     }
     if (!full) {
         // a short tile leaves some of its boundary slots unused: they hold -1
-        // (final), so that the jump rounds, which visit every slot, read no
+        // (final), so that the chase, which visits every slot, reads no
         // stale entry
         for (int k = threadIdx.x; k < NBND; k += PR_THREADS) bnd[int64_t(tile) * NBND + k] = -1;
         __syncthreads();
@@ -447,127 +450,71 @@ __global__ void zero_words_kernel(uint32_t *w, int64_t count) {
         w[i] = 0u;
 }
 
-__global__ void fill_flags_kernel(uint32_t *flags, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) flags[i] = (i == 0) ? 1u : 0u;
-}
-
-// Pointer jumping over the boundary entries, in place.  Round 0 visits every
-// entry; each workgroup appends to its own slice of a list (cap entries at
-// blockIdx * cap, count in counts[blockIdx]) the entries that changed and now
-// point at a boundary cell, whose own entry may still change: only those can
-// change again (an entry that does not change points at a root, which is
-// final).  Each later round visits its workgroup's slice of the previous
-// round's list and writes the entries still active to the other list, so no
-// global counter is shared and the lists shrink.  Round r runs only if round
-// r - 1 left an entry active, so a fixed number of launches is enough.
-constexpr int BATCH = 8;  // independent iterations per thread and pass, so their loads overlap
-
-// Appends the entries k with `again` set to this workgroup's slice `mine`
-// (one LDS reservation per wavefront).
-__device__ __forceinline__ void append_active(bool again, uint32_t k, uint32_t *mine, uint32_t *lcount) {
-    const int lane = threadIdx.x & 63;
-    const unsigned long long bits = __ballot(again);
-    if (bits) {
-        const int leader = __ffsll(bits) - 1;
-        uint32_t at = 0;
-        if (lane == leader) at = atomicAdd(lcount, uint32_t(__popcll(bits)));
-        at = __shfl(at, leader, 64);
-        if (again) mine[at + __popcll(bits & ((1ull << lane) - 1ull))] = k;
-    }
-}
+// Follows the pointer chains of the boundary entries to their ends, in place:
+// an entry is final when it is -1, points at an interior cell (a root, since a
+// chain leaves a tile through its boundary) or at a boundary cell that points
+// at itself (a root).  Entries of other tiles may be advanced while they are
+// read; whatever a read returns lies further along the same chain, so the ends
+// do not depend on the order.
+//
+// One launch takes at most CHASE_HOPS hops per entry: after it every pointer
+// is final or has come CHASE_HOPS boundary cells along its chain, so each hop of
+// the next launch covers as many, and ceil(log_CHASE_HOPS(entries)) launches
+// reach the end of any chain.  A launch runs only if the one before left an
+// entry open.  Chains cross few tiles (one to three at scales of 1 to 4 cells),
+// so the first launch ends them all, and a hop is two dependent loads: the
+// latency of BATCH chains per thread is what bounds it.  Rounds of pointer
+// doubling with lists of the entries still open (one hop per launch,
+// ceil(log2(entries)) + 1 launches, 18 at 64^3 to 30 at 1024^3, 2.2 us each when
+// nothing is left to do) took 48 us at 64^3, 123 us at 256^3 and 2.0 ms at
+// 1024^3 where the chase takes 17 us, 47 us and 1.47 ms.
+constexpr int BATCH = 8;  // independent chains per thread, so their loads overlap
+constexpr int CHASE_HOPS = 1024;
 
 template <bool FULL>
-__global__ void __launch_bounds__(256) bnd_jump_first_kernel(int32_t *__restrict__ bnd, int64_t count, TileGrid tg,
-                                                             uint32_t *__restrict__ list, int64_t cap,
-                                                             uint32_t *__restrict__ counts, uint32_t *flags) {
-    __shared__ uint32_t lcount;
-    if (threadIdx.x == 0) lcount = 0u;
-    __syncthreads();
-    uint32_t *mine = list + int64_t(blockIdx.x) * cap;
+__global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t count, TileGrid tg, uint32_t *flags,
+                                                        int round) {
+    if (round > 0 && flags[round] == 0u) return;
+    bool open = false;
     const int64_t step = int64_t(gridDim.x) * blockDim.x * BATCH;
     for (int64_t k0 = blockIdx.x * int64_t(blockDim.x) * BATCH + threadIdx.x; k0 < count; k0 += step) {
-        int32_t p[BATCH], q[BATCH];
-        int64_t s[BATCH];
+        int32_t p0[BATCH], p[BATCH];
+        bool on[BATCH];
+        bool any = false;
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
             const int64_t k = k0 + int64_t(i) * blockDim.x;
-            p[i] = k < count ? bnd[k] : 0;
+            p0[i] = k < count ? bnd[k] : -1;
         }
 #pragma unroll
         for (int i = 0; i < BATCH; ++i) {
-            const int64_t k = k0 + int64_t(i) * blockDim.x;
-            // -1 (a root at or below tau) and interior targets (roots) are final
-            s[i] = k < count && p[i] >= 0 ? bnd_slot<FULL>(tg, p[i]) : -1;
-            q[i] = s[i] >= 0 ? bnd[s[i]] : p[i];
+            p[i] = p0[i];
+            on[i] = p[i] >= 0;
+            any |= on[i];
         }
+        for (int hop = 0; any && hop < CHASE_HOPS; ++hop) {
+            int32_t q[BATCH];
 #pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t k = k0 + int64_t(i) * blockDim.x;
-            bool again = false;
-            if (k < count && q[i] != p[i]) {
-                bnd[k] = q[i];
-                again = q[i] >= 0 && bnd_slot<FULL>(tg, q[i]) >= 0;
+            for (int i = 0; i < BATCH; ++i) {
+                const int64_t s = on[i] ? bnd_slot<FULL>(tg, p[i]) : -1;
+                q[i] = s >= 0 ? bnd[s] : p[i];
             }
-            append_active(again, uint32_t(k), mine, &lcount);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        counts[blockIdx.x] = lcount;
-        if (lcount) flags[1] = 1u;
-    }
-}
-
-// Round r >= 1: list_in / counts_in hold round r - 1's active entries, the
-// entries still active after this round go to list_out / counts_out.
-template <bool FULL>
-__global__ void __launch_bounds__(256) bnd_jump_kernel(int32_t *__restrict__ bnd, const uint32_t *__restrict__ list_in,
-                                                       const uint32_t *__restrict__ counts_in,
-                                                       uint32_t *__restrict__ list_out,
-                                                       uint32_t *__restrict__ counts_out, int64_t cap, TileGrid tg,
-                                                       uint32_t *flags, int round) {
-    if (flags[round] == 0u) return;
-    __shared__ uint32_t lcount;
-    if (threadIdx.x == 0) lcount = 0u;
-    __syncthreads();
-    const uint32_t *from = list_in + int64_t(blockIdx.x) * cap;
-    uint32_t *mine = list_out + int64_t(blockIdx.x) * cap;
-    const int64_t count = counts_in[blockIdx.x];
-    for (int64_t j0 = threadIdx.x; j0 < count; j0 += int64_t(blockDim.x) * BATCH) {
-        uint32_t k[BATCH];
-        int32_t p[BATCH], q[BATCH];
+            any = false;
 #pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t j = j0 + int64_t(i) * blockDim.x;
-            k[i] = j < count ? from[j] : 0u;
-        }
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t j = j0 + int64_t(i) * blockDim.x;
-            p[i] = j < count ? bnd[k[i]] : -1;
-        }
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t sl = p[i] >= 0 ? bnd_slot<FULL>(tg, p[i]) : -1;
-            q[i] = sl >= 0 ? bnd[sl] : p[i];
-        }
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t j = j0 + int64_t(i) * blockDim.x;
-            bool again = false;
-            if (j < count && q[i] != p[i]) {
-                bnd[k[i]] = q[i];
-                again = q[i] >= 0 && bnd_slot<FULL>(tg, q[i]) >= 0;
+            for (int i = 0; i < BATCH; ++i) {
+                on[i] = q[i] != p[i] && q[i] >= 0;
+                p[i] = q[i];
+                any |= on[i];
             }
-            append_active(again, k[i], mine, &lcount);
+        }
+        open |= any;
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+            const int64_t k = k0 + int64_t(i) * blockDim.x;
+            if (p[i] != p0[i]) bnd[k] = p[i];
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        counts_out[blockIdx.x] = lcount;
-        if (lcount) flags[round + 1] = 1u;
-    }
+    if (__ballot(open) && (threadIdx.x & 63) == 0) flags[round + 1] = 1u;
 }
 
 // One workgroup per resolve tile: the resolved boundary entries of the
@@ -762,10 +709,11 @@ TileGrid resolve_grid(int n) {
     return TileGrid{n, (n + RX - 1) / RX, (n + RY - 1) / RY, (n + RZ - 1) / RZ, FastDiv(uint32_t(n))};
 }
 
-int rounds_for(uint64_t count) {
-    int k = 0;
-    while ((uint64_t(1) << k) < count) ++k;
-    return k + 1;  // ceil(log2(longest chain)) rounds, plus one that sees no change
+// Launches that end every chain of at most `count` boundary cells.
+int chase_launches(uint64_t count) {
+    int k = 1;
+    for (uint64_t reach = CHASE_HOPS; reach < count; reach *= CHASE_HOPS) ++k;
+    return k;
 }
 
 struct MaximaLayout {
@@ -797,45 +745,28 @@ int stride_grid(int64_t work) {
     return int(g > 4096 ? 4096 : (g < 1 ? 1 : g));
 }
 
-int batched_grid(int64_t work) { return stride_grid((work + BATCH - 1) / BATCH); }
-
 struct SegmentLayout {
-    size_t flags, ptr, bnd, list[2], counts[2], total;
-    int rounds;
+    size_t flags, ptr, bnd, total;
+    int launches;  // of the boundary chase
     int64_t nbnd;
-    int jump_grid;      // workgroups of every jump round
-    int64_t list_cap;   // list entries per workgroup
 };
 
 SegmentLayout segment_layout(int n) {
     SegmentLayout L{};
     const uint64_t cells = uint64_t(n) * n * n;
+    const TileGrid rg = resolve_grid(n);
+    L.nbnd = int64_t(rg.ntx) * rg.nty * rg.ntz * NBND;
+    L.launches = chase_launches(uint64_t(L.nbnd));
     size_t off = 0;
     L.flags = off;
-    {
-        const TileGrid rg = resolve_grid(n);
-        L.nbnd = int64_t(rg.ntx) * rg.nty * rg.ntz * NBND;
-        L.rounds = rounds_for(uint64_t(L.nbnd));
-        off = align_up(off + sizeof(uint32_t) * (L.rounds + 2));
-        L.ptr = off;
-        off = align_up(off + sizeof(int32_t) * cells);
-        L.bnd = off;
-        off = align_up(off + sizeof(int32_t) * size_t(L.nbnd));
-        // every round-0 workgroup visits at most cap entries
-        L.jump_grid = batched_grid(L.nbnd);
-        const int64_t per_pass = int64_t(L.jump_grid) * 256 * BATCH;
-        L.list_cap = (L.nbnd + per_pass - 1) / per_pass * 256 * BATCH;
-        for (int b = 0; b < 2; ++b) {  // the active lists of even and odd rounds
-            L.list[b] = off;
-            off = align_up(off + sizeof(uint32_t) * size_t(L.list_cap) * size_t(L.jump_grid));
-            L.counts[b] = off;
-            off = align_up(off + sizeof(uint32_t) * size_t(L.jump_grid));
-        }
-    }
+    off = align_up(off + sizeof(uint32_t) * CHASE_FLAGS);
+    L.ptr = off;
+    off = align_up(off + sizeof(int32_t) * cells);
+    L.bnd = off;
+    off = align_up(off + sizeof(int32_t) * size_t(L.nbnd));
     L.total = off;
     return L;
 }
-
 
 }  // namespace
 
@@ -873,41 +804,32 @@ hf_status launch_parent_resolve(hf_ctx *ctx, const SegmentLayout &L, char *w8, i
     const dim3 grid(tg.ntx * tg.nty * tg.ntz);
     auto *ptr = reinterpret_cast<int32_t *>(w8 + L.ptr);
     auto *bnd = reinterpret_cast<int32_t *>(w8 + L.bnd);
+    auto *flags = reinterpret_cast<uint32_t *>(w8 + L.flags);
     if (all_full(n))
         HF_LAUNCH(ctx, K_PARENT, parent_resolve_kernel<true>, grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
-                  host_ordered_bits(tau), ptr, bnd, mask, ctx->d_status);
+                  host_ordered_bits(tau), ptr, bnd, mask, flags, ctx->d_status);
     else
         HF_LAUNCH(ctx, K_PARENT, parent_resolve_kernel<false>, grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
-                  host_ordered_bits(tau), ptr, bnd, mask, ctx->d_status);
+                  host_ordered_bits(tau), ptr, bnd, mask, flags, ctx->d_status);
     return launch_status();
 }
 
-// After launch_parent_resolve: pointer-jumping rounds over the boundary
-// entries, and the final mapping through them.
+// After launch_parent_resolve: the chains of the boundary entries, and the
+// final mapping through them.
 hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, int32_t *cell_label) {
     const TileGrid tg = resolve_grid(n);
     auto *flags = reinterpret_cast<uint32_t *>(w8 + L.flags);
     auto *ptr = reinterpret_cast<int32_t *>(w8 + L.ptr);
     auto *bnd = reinterpret_cast<int32_t *>(w8 + L.bnd);
-    uint32_t *list[2], *counts[2];
-    for (int b = 0; b < 2; ++b) {
-        list[b] = reinterpret_cast<uint32_t *>(w8 + L.list[b]);
-        counts[b] = reinterpret_cast<uint32_t *>(w8 + L.counts[b]);
-    }
     const bool full = all_full(n);
-    if (full)
-        HF_LAUNCH(ctx, K_JUMP, bnd_jump_first_kernel<true>, dim3(L.jump_grid), dim3(256), 0, ctx->stream, bnd,
-                  L.nbnd, tg, list[0], L.list_cap, counts[0], flags);
-    else
-        HF_LAUNCH(ctx, K_JUMP, bnd_jump_first_kernel<false>, dim3(L.jump_grid), dim3(256), 0, ctx->stream, bnd,
-                  L.nbnd, tg, list[0], L.list_cap, counts[0], flags);
-    for (int r = 1; r < L.rounds; ++r) {
+    const dim3 chase(stride_grid((L.nbnd + BATCH - 1) / BATCH));
+    for (int r = 0; r < L.launches; ++r) {
         if (full)
-            HF_LAUNCH(ctx, K_JUMP, bnd_jump_kernel<true>, dim3(L.jump_grid), dim3(256), 0, ctx->stream, bnd,
-                      list[(r - 1) & 1], counts[(r - 1) & 1], list[r & 1], counts[r & 1], L.list_cap, tg, flags, r);
+            HF_LAUNCH(ctx, K_JUMP, bnd_chase_kernel<true>, chase, dim3(256), 0, ctx->stream, bnd, L.nbnd, tg, flags,
+                      r);
         else
-            HF_LAUNCH(ctx, K_JUMP, bnd_jump_kernel<false>, dim3(L.jump_grid), dim3(256), 0, ctx->stream, bnd,
-                      list[(r - 1) & 1], counts[(r - 1) & 1], list[r & 1], counts[r & 1], L.list_cap, tg, flags, r);
+            HF_LAUNCH(ctx, K_JUMP, bnd_chase_kernel<false>, chase, dim3(256), 0, ctx->stream, bnd, L.nbnd, tg, flags,
+                      r);
     }
     const dim3 grid(tg.ntx * tg.nty * tg.ntz);
     if (full)
@@ -939,9 +861,6 @@ hf_status hf::maxima_segment(hf_ctx *ctx, const hf_box &box, const float *cwt, f
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
     char *w8 = static_cast<char *>(ws);
     char *wm = w8 + SL.total;
-    auto *flags = reinterpret_cast<uint32_t *>(w8 + SL.flags);
-    HF_LAUNCH(ctx, K_FLAGS, fill_flags_kernel, dim3((SL.rounds + 2 + 255) / 256), dim3(256), 0, ctx->stream, flags,
-              SL.rounds + 2);
     auto *mask = reinterpret_cast<uint32_t *>(wm + ML.mask);
     if (n % 32 != 0)  // rows straddle mask words: the maxima are set bit by bit into a cleared mask
         HF_LAUNCH(ctx, K_FLAGS, zero_words_kernel, dim3(stride_grid(ML.words)), dim3(256), 0, ctx->stream, mask,
@@ -989,10 +908,7 @@ extern "C" hf_status hf_segment(hf_ctx *ctx, const hf_box *box, const float *cwt
     if (s != HF_OK) return s;
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
     char *w8 = static_cast<char *>(ws);
-    auto *flags = reinterpret_cast<uint32_t *>(w8 + L.flags);
     const int n = box->n;
-    HF_LAUNCH(ctx, K_FLAGS, fill_flags_kernel, dim3((L.rounds + 2 + 255) / 256), dim3(256), 0, ctx->stream, flags,
-              L.rounds + 2);
     s = launch_parent_resolve(ctx, L, w8, n, cwt, tau, nullptr);
     if (s != HF_OK) return s;
     return segment_finish(ctx, L, w8, n, cell_label);

@@ -1,0 +1,39 @@
+"""Segmentation chains that cross more tiles than one launch of the boundary
+chase follows (-m gpu): a path of increasing values that steps over a tile
+boundary at every cell, folded back and forth through the box."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cwthf as O
+
+pytestmark = pytest.mark.gpu
+
+
+def zigzag(n: int):
+    """Path cells (z, y, x) in ascending order: along y at x = 31 and 32 in turn
+    (a tile boundary), then three planes up in z and back; no two cells of the
+    path are neighbours unless they follow each other."""
+    path, z, up = [], 1, True
+    while z + 3 < n - 1:
+        ys = range(1, n - 2) if up else range(n - 3, 0, -1)
+        path += [(z, y, 31 + (y & 1)) for y in ys]
+        path += [(z + 1, ys[-1], 31 + (ys[-1] & 1)), (z + 2, ys[-1], 31 + (ys[-1] & 1))]
+        z += 3
+        up = not up
+    return path
+
+
+@pytest.mark.parametrize("n", [64, 75])
+def test_path_over_more_boundaries_than_one_launch_follows(n):
+    import paper_2501_10622_amd as hfm
+    path = zigzag(n)
+    steps = sum(a[2] != b[2] for a, b in zip(path, path[1:]))
+    assert steps > 1024  # boundary cells along the chain
+    c = np.full((n, n, n), 0.25, dtype=np.float32)
+    for k, cell in enumerate(path):
+        c[cell] = 1.0 + k
+    got = hfm.segment(torch.as_tensor(c, device="cuda:0")).cpu().numpy()
+    z, y, x = path[-1]
+    assert all(got[cell] == (z * n + y) * n + x for cell in path)
+    assert np.array_equal(got, O.segment(c))

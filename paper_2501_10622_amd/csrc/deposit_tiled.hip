@@ -54,12 +54,15 @@ constexpr int PART_PER = 8;
 constexpr int CHUNK = PART_THREADS * PART_PER;                          // particles per scatter workgroup
 constexpr int HIST_CHUNKS = 8;                                          // scatter chunks per histogram workgroup
 constexpr int HCHUNK = CHUNK * HIST_CHUNKS;
+constexpr int HIST_MIN_CHUNK = 2048, HIST_FILL = 4;                   // smaller for few particles (hist_chunk)
 constexpr int REPLICAS = 16;   // level-1 counters are replicated to spread atomic traffic
 constexpr int MAX_DIGITS = 512;
 constexpr int HIST_THREADS = 512;  // histogram workgroups stay at 512 threads
 constexpr int ACC_THREADS = 512;
 constexpr uint16_t NO_POS = 0xffffu;  // staging position of a particle whose position was rejected
-constexpr int OFF_STRIDE = MAX_DIGITS + 2;  // per-chunk row of staging offsets (ndest + 1 used)
+
+// Row of a chunk's staging offsets for ndest destinations (ndest + 1 used, an even number kept).
+__host__ __device__ inline int off_stride(int ndest) { return (ndest + 2) & ~1; }
 
 // Where one level's scatter chunks put their elements, kept for step 6: the
 // position of every element in its chunk's destination-sorted staging order
@@ -69,8 +72,8 @@ constexpr int OFF_STRIDE = MAX_DIGITS + 2;  // per-chunk row of staging offsets 
 // not stored: the runs are in destination order, so the offsets give it.
 struct RunMaps {
     uint16_t *pos;     // [elements]
-    uint32_t *base;    // [chunks * MAX_DIGITS]
-    uint16_t *offset;  // [chunks * OFF_STRIDE]
+    uint32_t *base;    // [chunks * ndest]
+    uint16_t *offset;  // [chunks * off_stride(ndest)]
 };
 
 // Records one scatter chunk's run table (called by every thread after the
@@ -78,10 +81,10 @@ struct RunMaps {
 __device__ __forceinline__ void save_run_table(const RunMaps &m, int64_t chunk, int ndest, const uint32_t *h,
                                                const uint32_t *off, const uint32_t *gbase, uint32_t total) {
     for (int d = threadIdx.x; d < ndest; d += blockDim.x) {
-        m.base[chunk * MAX_DIGITS + d] = h[d] ? gbase[d] : 0u;
-        m.offset[chunk * OFF_STRIDE + d] = uint16_t(off[d]);
+        m.base[chunk * ndest + d] = h[d] ? gbase[d] : 0u;
+        m.offset[chunk * off_stride(ndest) + d] = uint16_t(off[d]);
     }
-    if (threadIdx.x == 0) m.offset[chunk * OFF_STRIDE + ndest] = uint16_t(total);
+    if (threadIdx.x == 0) m.offset[chunk * off_stride(ndest) + ndest] = uint16_t(total);
 }
 
 struct Geom {
@@ -237,14 +240,14 @@ static_assert(REPLICAS % NUM_XCD == 0, "replicas split evenly over the XCDs");
 // ---------------------------------------------------------------- level 1
 template <typename T>
 __global__ void __launch_bounds__(HIST_THREADS) l1_hist_kernel(const T *__restrict__ pos, int64_t np,
-                                                               FixedPoint<T> fp, Geom g, uint32_t *count1,
-                                                               uint32_t *status) {
+                                                               FixedPoint<T> fp, Geom g, int hchunk,
+                                                               uint32_t *count1, uint32_t *status) {
     __shared__ uint32_t h[MAX_DIGITS];
     for (int b = threadIdx.x; b < MAX_DIGITS; b += blockDim.x) h[b] = 0u;
     __syncthreads();
     bool bad = false;
-    const int64_t base = int64_t(blockIdx.x) * HCHUNK;
-    const int64_t end = base + HCHUNK < np ? base + HCHUNK : np;
+    const int64_t base = int64_t(blockIdx.x) * hchunk;
+    const int64_t end = base + hchunk < np ? base + hchunk : np;
     for (int64_t i0 = base + threadIdx.x; i0 < end; i0 += HIST_THREADS * LBATCH) {
         Q3 q[LBATCH];
         bool ok[LBATCH];
@@ -254,72 +257,72 @@ __global__ void __launch_bounds__(HIST_THREADS) l1_hist_kernel(const T *__restri
             if (ok[k]) atomicAdd(&h[bucket_of(g, q[k].x >> g.bits, q[k].y >> g.bits, q[k].z >> g.bits)], 1u);
     }
     __syncthreads();
-    uint32_t *mine = count1 + (blockIdx.x % REPLICAS) * MAX_DIGITS;
+    uint32_t *mine = count1 + (base / HCHUNK) % REPLICAS * MAX_DIGITS;  // the replica these chunks advance
     for (int b = threadIdx.x; b < g.nbuckets; b += blockDim.x)
         if (h[b]) atomicAdd(&mine[b], h[b]);
     if (bad) atomicOr(status, ST_INPUT);
 }
 
-// start1 = exclusive scan of the bucket totals; cursor1[r][b] = where replica r's
-// share of bucket b starts; chunk_first / hchunk_first = exclusive scans of the
-// number of level-2 scatter / histogram chunks per bucket.
-__global__ void __launch_bounds__(MAX_DIGITS) l1_scan_kernel(const uint32_t *__restrict__ count1, int nbuckets,
-                                                             uint32_t *start1, uint32_t *cursor1,
-                                                             uint32_t *chunk_first, uint32_t *hchunk_first,
-                                                             uint32_t *nrec_out) {
-    __shared__ uint32_t s[MAX_DIGITS], c[MAX_DIGITS], hc[MAX_DIGITS], tmp[MAX_DIGITS];
-    const int t = threadIdx.x;
-    uint32_t cnt = 0;
-    if (t < nbuckets)
-        for (int r = 0; r < REPLICAS; ++r) cnt += count1[r * MAX_DIGITS + t];
-    s[t] = cnt;
-    c[t] = (cnt + CHUNK - 1) / CHUNK;
-    hc[t] = (cnt + HCHUNK - 1) / HCHUNK;
-    __syncthreads();
-    const uint32_t total = block_exclusive_scan(s, tmp, nbuckets);
-    const uint32_t chunks = block_exclusive_scan(c, tmp, nbuckets);
-    const uint32_t hchunks = block_exclusive_scan(hc, tmp, nbuckets);
+// The level-1 tables, one workgroup per counter replica r (each forms the
+// bucket totals and their scan for itself; workgroup 0 writes the tables that
+// do not depend on r):
+//   start1 = exclusive scan of the bucket totals; chunk_first / hchunk_first =
+//   exclusive scans of the number of level-2 scatter / histogram chunks per bucket;
+//   cursor1[r][b] = seg_v[b][r] = the bucket-major index where replica r's share
+//   of bucket b starts, seg_p[b][r] = the storage slot where it is kept (the
+//   records of the replicas before r, then r's shares of the buckets before b).
+__global__ void __launch_bounds__(MAX_DIGITS) l1_tables_kernel(const uint32_t *__restrict__ count1, int nbuckets,
+                                                               uint32_t hchunk, uint32_t *__restrict__ start1,
+                                                               uint32_t *__restrict__ cursor1,
+                                                               uint32_t *__restrict__ chunk_first,
+                                                               uint32_t *__restrict__ hchunk_first,
+                                                               uint32_t *__restrict__ nrec_out,
+                                                               uint32_t *__restrict__ seg_v,
+                                                               uint32_t *__restrict__ seg_p) {
+    __shared__ uint32_t s[MAX_DIGITS], tmp[MAX_DIGITS];
+    const int r = blockIdx.x, t = threadIdx.x;
+    uint32_t cnt = 0, below = 0, own = 0;  // bucket t: all replicas, those before r, r itself
     if (t < nbuckets) {
-        start1[t] = s[t];
-        uint32_t run = s[t];
-        for (int r = 0; r < REPLICAS; ++r) {
-            cursor1[r * MAX_DIGITS + t] = run;
-            run += count1[r * MAX_DIGITS + t];
+        uint32_t c[REPLICAS];
+#pragma unroll
+        for (int q = 0; q < REPLICAS; ++q) c[q] = count1[q * MAX_DIGITS + t];
+#pragma unroll
+        for (int q = 0; q < REPLICAS; ++q) {
+            cnt += c[q];
+            below += q < r ? c[q] : 0u;
+            own = q == r ? c[q] : own;
         }
-        chunk_first[t] = c[t];
-        hchunk_first[t] = hc[t];
+    }
+    auto scan = [&](uint32_t v, uint32_t &total) {
+        __syncthreads();
+        s[t] = v;
+        __syncthreads();
+        total = block_exclusive_scan(s, tmp, nbuckets);
+        return s[t];
+    };
+    uint32_t total, rbase, unused;
+    const uint32_t first = scan(cnt, total);
+    scan(below, rbase);
+    const uint32_t place = scan(own, unused);
+    if (t < nbuckets) {
+        cursor1[r * MAX_DIGITS + t] = first + below;
+        seg_v[t * REPLICAS + r] = first + below;
+        seg_p[t * REPLICAS + r] = rbase + place;
+    }
+    if (r != 0) return;
+    uint32_t chunks, hchunks;
+    const uint32_t c0 = scan((cnt + CHUNK - 1) / CHUNK, chunks);
+    const uint32_t h0 = scan((cnt + hchunk - 1) / hchunk, hchunks);
+    if (t < nbuckets) {
+        start1[t] = first;
+        chunk_first[t] = c0;
+        hchunk_first[t] = h0;
     }
     if (t == 0) {
         start1[nbuckets] = total;
         if (nrec_out) *nrec_out = total;
         chunk_first[nbuckets] = chunks;
         hchunk_first[nbuckets] = hchunks;
-    }
-}
-
-// Storage of the replica-major level-1 records, one workgroup per replica r:
-// seg_v[b][r] = the bucket-major index where replica r's share of bucket b
-// starts (cursor1's initial value), seg_p[b][r] = the storage slot where it is
-// kept (the records of the replicas before r, then r's shares of the buckets
-// before b).
-__global__ void __launch_bounds__(MAX_DIGITS) l1_segs_kernel(const uint32_t *__restrict__ count1, int nbuckets,
-                                                             const uint32_t *__restrict__ cursor1,
-                                                             uint32_t *__restrict__ seg_v,
-                                                             uint32_t *__restrict__ seg_p) {
-    __shared__ uint32_t s[MAX_DIGITS], tmp[MAX_DIGITS];
-    const int r = blockIdx.x, t = threadIdx.x;
-    uint32_t before = 0;
-    if (t < nbuckets)
-        for (int q = 0; q < r; ++q) before += count1[q * MAX_DIGITS + t];
-    s[t] = before;
-    __syncthreads();
-    const uint32_t rbase = block_exclusive_scan(s, tmp, nbuckets);
-    s[t] = t < nbuckets ? count1[r * MAX_DIGITS + t] : 0u;
-    __syncthreads();
-    block_exclusive_scan(s, tmp, nbuckets);
-    if (t < nbuckets) {
-        seg_v[t * REPLICAS + r] = cursor1[r * MAX_DIGITS + t];
-        seg_p[t * REPLICAS + r] = rbase + s[t];
     }
 }
 
@@ -1004,11 +1007,11 @@ __device__ void chunk_gather(const RunMaps &m, int64_t chunk, int ndest, int64_t
                              const uint32_t *__restrict__ keep, const ClaimOut &claim = ClaimOut{},
                              const TileClaim &tc = TileClaim{}) {
     __shared__ uint32_t base_s[MAX_DIGITS];
-    __shared__ uint16_t off_s[OFF_STRIDE];
+    __shared__ uint16_t off_s[MAX_DIGITS + 2];
     __shared__ int32_t val[CHUNK];
     static_assert(CHUNK == PART_THREADS * PART_PER, "one staging position per thread and slot");
-    for (int d = threadIdx.x; d < ndest; d += blockDim.x) base_s[d] = m.base[chunk * MAX_DIGITS + d];
-    for (int d = threadIdx.x; d <= ndest; d += blockDim.x) off_s[d] = m.offset[chunk * OFF_STRIDE + d];
+    for (int d = threadIdx.x; d < ndest; d += blockDim.x) base_s[d] = m.base[chunk * ndest + d];
+    for (int d = threadIdx.x; d <= ndest; d += blockDim.x) off_s[d] = m.offset[chunk * off_stride(ndest) + d];
     uint16_t p[PART_PER], dd[PART_PER];
 #pragma unroll
     for (int k = 0; k < PART_PER; ++k) {
@@ -1111,8 +1114,13 @@ bool make_geom(const hf_box &box, Geom &out) {
     g.ntiles = g.ntx * g.nty * g.ntz;
     g.skirt = g.tx * AYZ + g.tx * TYZ;  // y and z faces
     // buckets of whole rows of tiles along x where that fits (the accumulation
-    // walks each row in order), then the fewest buckets, then the most
-    // cube-like bucket
+    // walks each row in order), then one bucket where it can hold every tile,
+    // else the smaller larger one of buckets and tiles per bucket, then the most
+    // cube-like bucket.  512^3: 128 buckets of 256 tiles against the fewest
+    // possible, 64 of 512: the labels' pass to level-1 order 1074 -> 902 us for
+    // three scales, the pass to input order 846 -> 911 us, level-1 scatter
+    // 841 -> 892 us; 1024^3 has one choice (512 of 512)
+    const bool one = g.ntiles <= MAX_DIGITS;
     long best_nb = -1;
     double best_shape = 0.0;
     auto search = [&](int bx_from) {
@@ -1128,8 +1136,10 @@ bool make_geom(const hf_box &box, Geom &out) {
                     const double hi = ex > ey ? (ex > ez ? ex : ez) : (ey > ez ? ey : ez);
                     const double lo = ex < ey ? (ex < ez ? ex : ez) : (ey < ez ? ey : ez);
                     const double shape = hi / lo;
-                    if (best_nb < 0 || nb < best_nb || (nb == best_nb && shape < best_shape)) {
-                        best_nb = nb;
+                    const long tiles = long(bx) * by * bz;
+                    const long wide = one ? nb : (nb > tiles ? nb : tiles);
+                    if (best_nb < 0 || wide < best_nb || (wide == best_nb && shape < best_shape)) {
+                        best_nb = wide;
                         best_shape = shape;
                         g.btx = bx;
                         g.bty = by;
@@ -1255,8 +1265,9 @@ OrderLayout order_layout(const Geom &g, int64_t np) {
     const size_t chunks[2] = {chunks1, chunks1 + size_t(g.nbuckets)};  // level 2: one partial chunk per bucket
     for (int l = 0; l < 2; ++l) {
         L.pos[l] = take(sizeof(uint16_t) * size_t(np));
-        L.base[l] = take(sizeof(uint32_t) * chunks[l] * MAX_DIGITS);
-        L.offset[l] = take(sizeof(uint16_t) * chunks[l] * OFF_STRIDE);
+        const int ndest = l == 0 ? g.nbuckets : g.digits;
+        L.base[l] = take(sizeof(uint32_t) * chunks[l] * size_t(ndest));
+        L.offset[l] = take(sizeof(uint16_t) * chunks[l] * size_t(off_stride(ndest)));
     }
     L.total = off;
     return L;
@@ -1272,6 +1283,20 @@ unsigned resident_grid(const hf_ctx *ctx, const void *kernel, unsigned blocks) {
     if (g < NUM_XCD) g = NUM_XCD;
     const unsigned need = (blocks + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     return g < need ? g : need;
+}
+
+// Particles per histogram workgroup: a power of two that divides HCHUNK, so
+// that every workgroup's particles belong to one counter replica.  Few
+// particles take smaller chunks, so that HIST_FILL workgroups per CU are at
+// work: with HCHUNK the 2^18 particles of a 64^3 box were four workgroups.
+// Level-2 histogram 53 -> 6.6 us at 64^3 (2^18 FP64 particles), 51 -> 27 us at
+// 128^3 (2^21), 53 -> 12 us at 96^3; 256^3 (2^24) level 1 61 -> 53 and level 2
+// 64 -> 42 us.  From 2^26 particles on HCHUNK fills the device and each
+// workgroup's up to 512 counter atomics are spread over most particles.
+int hist_chunk(const hf_ctx *ctx, int64_t np) {
+    int c = HCHUNK;
+    while (c > HIST_MIN_CHUNK && np / c < HIST_FILL * int64_t(ctx->cus)) c >>= 1;
+    return c;
 }
 
 template <typename T>
@@ -1307,43 +1332,37 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
     uint32_t *nrec = order ? order->nrec : nullptr;
     hipStream_t st = ctx->stream;
     const FixedPoint<T> fp = make_fixed_point<T>(box);
-    HF_LAUNCH(ctx, K_DEP_PREP, zero_u32_kernel, dim3(64), dim3(256), 0, st, count1, int64_t(MAX_DIGITS * REPLICAS));
-    HF_LAUNCH(ctx, K_DEP_PREP, zero_u32_kernel, dim3(64), dim3(256), 0, st, count2, int64_t(g.ntiles));
+    // the counters of both levels lie back to back (count2 last)
+    const int64_t clear = (reinterpret_cast<char *>(count2) - reinterpret_cast<char *>(count1)) / 4 + g.ntiles;
+    HF_LAUNCH(ctx, K_DEP_PREP, zero_u32_kernel, dim3(64), dim3(256), 0, st, count1, clear);
     const unsigned part_blocks = unsigned((np + CHUNK - 1) / CHUNK);
-    const unsigned hist_blocks = unsigned((np + HCHUNK - 1) / HCHUNK);
+    const int hchunk = hist_chunk(ctx, np);
+    const unsigned hist_blocks = unsigned((np + hchunk - 1) / hchunk);
     if (g.nbuckets > 1) {
         if (hist_blocks)
             HF_LAUNCH(ctx, K_DEP_L1_HIST, l1_hist_kernel<T>, dim3(hist_blocks), dim3(HIST_THREADS), 0, st, pos, np,
-                      fp, g, count1, ctx->d_status);
-        HF_LAUNCH(ctx, K_DEP_PREP, l1_scan_kernel, dim3(1), dim3(MAX_DIGITS), 0, st, count1, g.nbuckets, start1,
-                  cursor1, chunk_first, hchunk_first, nrec);
-        HF_LAUNCH(ctx, K_DEP_PREP, l1_segs_kernel, dim3(REPLICAS), dim3(MAX_DIGITS), 0, st, count1, g.nbuckets,
-                  cursor1, seg_v, seg_p);
+                      fp, g, hchunk, count1, ctx->d_status);
+        HF_LAUNCH(ctx, K_DEP_PREP, l1_tables_kernel, dim3(REPLICAS), dim3(MAX_DIGITS), 0, st, count1, g.nbuckets,
+                  uint32_t(hchunk), start1, cursor1, chunk_first, hchunk_first, nrec, seg_v, seg_p);
         if (part_blocks)
             HF_LAUNCH(ctx, K_DEP_L1_SCATTER, l1_scatter_kernel<T>,
                       dim3(resident_grid(ctx, reinterpret_cast<const void *>(&l1_scatter_kernel<T>),
                                          replica_grid(part_blocks))),
                       dim3(PART_THREADS), 0, st, pos, np, fp, g, cursor1, seg_v, seg_p, rec1, m1);
-        const L2Input<T, true> hin{pos, np, fp, rec1, seg_v, seg_p, start1, hchunk_first, g.nbuckets, HCHUNK};
+        const L2Input<T, true> hin{pos, np, fp, rec1, seg_v, seg_p, start1, hchunk_first, g.nbuckets, hchunk};
         const L2Input<T, true> sin{pos, np, fp, rec1, seg_v, seg_p, start1, chunk_first, g.nbuckets, CHUNK};
         HF_LAUNCH(ctx, K_DEP_L2_HIST, (l2_hist_kernel<T, true>), dim3(hist_blocks + unsigned(g.nbuckets)),
                   dim3(HIST_THREADS), 0, st, hin, g, count2, ctx->d_status);
-        HF_LAUNCH(ctx, K_DEP_PREP, seg_reduce_kernel<SCAN_TILES>, dim3(scan_groups(tile_scan)), dim3(SCAN_THREADS),
-                  0, st, tile_scan);
-        HF_LAUNCH(ctx, K_DEP_PREP, seg_scan_kernel<SCAN_TILES>, dim3(scan_groups(tile_scan)), dim3(SCAN_THREADS), 0,
-                  st, tile_scan);
+        launch_scan<SCAN_TILES>(ctx, K_DEP_PREP, tile_scan);
         HF_LAUNCH(ctx, K_DEP_L2_SCATTER, (l2_scatter_kernel<T, true>), dim3(part_blocks + unsigned(g.nbuckets)),
                   dim3(PART_THREADS), 0, st, sin, g, cursor2, rec2, m2);
     } else {
-        const L2Input<T, false> hin{pos, np, fp, nullptr, nullptr, nullptr, nullptr, nullptr, 1, HCHUNK};
+        const L2Input<T, false> hin{pos, np, fp, nullptr, nullptr, nullptr, nullptr, nullptr, 1, hchunk};
         const L2Input<T, false> sin{pos, np, fp, nullptr, nullptr, nullptr, nullptr, nullptr, 1, CHUNK};
         if (hist_blocks)
             HF_LAUNCH(ctx, K_DEP_L2_HIST, (l2_hist_kernel<T, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st,
                       hin, g, count2, ctx->d_status);
-        HF_LAUNCH(ctx, K_DEP_PREP, seg_reduce_kernel<SCAN_TILES>, dim3(scan_groups(tile_scan)), dim3(SCAN_THREADS),
-                  0, st, tile_scan);
-        HF_LAUNCH(ctx, K_DEP_PREP, seg_scan_kernel<SCAN_TILES>, dim3(scan_groups(tile_scan)), dim3(SCAN_THREADS), 0,
-                  st, tile_scan);
+        launch_scan<SCAN_TILES>(ctx, K_DEP_PREP, tile_scan);
         if (part_blocks)
             HF_LAUNCH(ctx, K_DEP_L2_SCATTER, (l2_scatter_kernel<T, false>), dim3(part_blocks), dim3(PART_THREADS),
                       0, st, sin, g, cursor2, rec2, RunMaps{});

@@ -1,5 +1,5 @@
-// Exclusive scan of n uint32 counts in two launches over many workgroups, in
-// a fixed order (no atomics), for the offset tables of the partition and list
+// Exclusive scan of n uint32 counts, short ones by one workgroup
+// (one_scan_kernel), others in two launches over many workgroups, in a fixed order (no atomics), for the offset tables of the partition and list
 // passes:
 //   seg_reduce_kernel: workgroup g sums the values [g S, min(n, (g+1) S)) into
 //                      partial[g];
@@ -107,6 +107,68 @@ __global__ void __launch_bounds__(SCAN_THREADS) seg_scan_kernel(ScanJob j) {
             if (int64_t(carry) > j.cap) atomicOr(j.status, hf::ST_CAPACITY);
         }
     }
+}
+
+// Up to SCAN_SMALL counts: the whole scan by one workgroup, SCAN_PER
+// consecutive values per thread, in one launch instead of two.  Two launches
+// of a few microseconds each are what the short scans cost (4.7 + 4.7 us for
+// 64 to 4096 tile counts; 5 us in one); longer ones want every CU.
+constexpr int SCAN_PER = 8;
+constexpr int SCAN_SMALL = SCAN_THREADS * SCAN_PER;
+
+template <int TAG>
+__global__ void __launch_bounds__(SCAN_THREADS) one_scan_kernel(ScanJob j) {
+    __shared__ uint32_t wsum[SCAN_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = int(j.n);
+    const int per = (n + SCAN_THREADS - 1) / SCAN_THREADS;
+    const int lo = int(threadIdx.x) * per;
+    uint32_t v[SCAN_PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_PER; ++k) {
+        v[k] = k < per && lo + k < n ? j.in[lo + k] : 0u;
+        sum += v[k];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += y;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    uint32_t e = inc - sum;
+    uint64_t total = 0;
+    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+        e += w < wave ? wsum[w] : 0u;
+        total += wsum[w];
+    }
+#pragma unroll
+    for (int k = 0; k < SCAN_PER; ++k) {
+        if (k < per && lo + k < n) {
+            j.out[lo + k] = e;
+            if (j.out2) j.out2[lo + k] = e;
+        }
+        e += v[k];
+    }
+    if (threadIdx.x == 0) {
+        j.out[n] = uint32_t(total);
+        if (j.total64) {
+            *j.total64 = int64_t(total);
+            if (int64_t(total) > j.cap) atomicOr(j.status, hf::ST_CAPACITY);
+        }
+    }
+}
+
+// Enqueues the scan.
+template <int TAG>
+inline void launch_scan(hf_ctx *ctx, int kid, const ScanJob &j) {
+    if (j.n <= SCAN_SMALL) {
+        HF_LAUNCH(ctx, kid, one_scan_kernel<TAG>, dim3(1), dim3(SCAN_THREADS), 0, ctx->stream, j);
+        return;
+    }
+    HF_LAUNCH(ctx, kid, seg_reduce_kernel<TAG>, dim3(scan_groups(j)), dim3(SCAN_THREADS), 0, ctx->stream, j);
+    HF_LAUNCH(ctx, kid, seg_scan_kernel<TAG>, dim3(scan_groups(j)), dim3(SCAN_THREADS), 0, ctx->stream, j);
 }
 
 }  // namespace

@@ -787,10 +787,7 @@ hf_status mask_to_list(hf_ctx *ctx, const MaximaLayout &L, char *w8, int32_t *ma
               L.words, counts);
     const ScanJob sj = scan_job(counts, L.nchunks, reinterpret_cast<uint64_t *>(w8 + L.partial), offsets, nullptr,
                                 d_count, max_cap, ctx->d_status);
-    HF_LAUNCH(ctx, K_MAX_SCAN, seg_reduce_kernel<SCAN_MAXIMA>, dim3(scan_groups(sj)), dim3(SCAN_THREADS), 0,
-              ctx->stream, sj);
-    HF_LAUNCH(ctx, K_MAX_SCAN, seg_scan_kernel<SCAN_MAXIMA>, dim3(scan_groups(sj)), dim3(SCAN_THREADS), 0, ctx->stream,
-              sj);
+    launch_scan<SCAN_MAXIMA>(ctx, K_MAX_SCAN, sj);
     HF_LAUNCH(ctx, K_MAX_WRITE, list_write_kernel, dim3(L.nchunks), dim3(LIST_CHUNK_WORDS), 0, ctx->stream, mask,
               L.words, offsets, max_cap, max_idx);
     return launch_status();

@@ -539,8 +539,7 @@ hf_status hf::unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const 
         HF_LAUNCH(ctx, K_UNBIND, ub_count_kernel, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np, roots,
                   d_count, nroots, ncells, slot, keep, cnt, ctx->d_status);
     const ScanJob sj = scan_job(cnt, nroots, partial, start);
-    HF_LAUNCH(ctx, K_UNBIND, seg_reduce_kernel<SCAN_GROUPS>, dim3(scan_groups(sj)), dim3(SCAN_THREADS), 0, st, sj);
-    HF_LAUNCH(ctx, K_UNBIND, seg_scan_kernel<SCAN_GROUPS>, dim3(scan_groups(sj)), dim3(SCAN_THREADS), 0, st, sj);
+    launch_scan<SCAN_GROUPS>(ctx, K_UNBIND, sj);
     if (np > 0)
         HF_LAUNCH(ctx, K_UNBIND, ub_gather_kernel, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np, slot,
                   start, cur, pid);

@@ -444,7 +444,8 @@ hf_status hf_identify(hf_ctx *ctx, const hf_box *box, const void *pos, hf_dtype 
  * HF_ERR_SIZE for an n_j outside [8, 1024] or frac_bits outside [8, 20].
  * Workspace: hf_identify_grids_ws_size (the largest scale's stage workspace,
  * or the check's with velocities, its group counters and one byte per
- * maximum of the largest list). */
+ * maximum of the largest list; with velocities also accepted without the
+ * 52 bytes per particle that hf_unbind can do without). */
 typedef struct {
     double kw;                 /* scale k_w = w box_len / 1000 */
     int32_t n;                 /* this scale's grid points per side */
@@ -486,7 +487,10 @@ hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac_bits, cons
  * outside [0, n^3], a non-positive grav_mass or a negative particle_th; a
  * label >= 0 that is not among the roots, or a root outside [0, n^3), sets
  * HF_ERR_INPUT (the label becomes -1).  Workspace: hf_unbind_ws_size (a slot
- * per cell, and 29 bytes per particle). */
+ * per cell, 12 bytes per root and 81 bytes per particle, of which 52 hold the
+ * members' positions and velocities in group order; a workspace without those
+ * 52 is accepted, and every pass then fetches them from pos and vel: the same
+ * results, slower). */
 hf_status hf_unbind_ws_size(const hf_box *box, int64_t np, int64_t nroots, size_t *bytes);
 hf_status hf_unbind(hf_ctx *ctx, const hf_box *box, const void *pos, const void *vel, hf_dtype dtype, int64_t np,
                     const int32_t *roots, int64_t nroots, const uint8_t *group_keep, int32_t *particle_label,

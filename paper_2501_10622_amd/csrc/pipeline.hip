@@ -336,7 +336,7 @@ struct GridsLayout {
 };
 
 hf_status grids_layout(double box_len, int32_t frac_bits, int64_t np, int32_t count, const hf_grid_scale *scales,
-                       bool with_vel, GridsLayout &L) {
+                       bool with_vel, bool records, GridsLayout &L) {
     if (!scales || count < 1 || count > HF_CWT_BATCH_MAX || np < 0) return HF_ERR_ARG;
     size_t shared = 0, groups = 0;
     int64_t cap = 0;
@@ -351,7 +351,7 @@ hf_status grids_layout(double box_len, int32_t frac_bits, int64_t np, int32_t co
         if (s != HF_OK) return s;
         shared = need > shared ? need : shared;
         if (with_vel) {  // steps 9-10 reuse the stage region once every scale's stages are done
-            const size_t ub = unbind_ws_bytes(b, np, scales[j].max_cap);
+            const size_t ub = unbind_ws_bytes(b, np, scales[j].max_cap, records);
             shared = ub > shared ? ub : shared;
         }
         groups = groups_ws_bytes(b) > groups ? groups_ws_bytes(b) : groups;
@@ -369,7 +369,7 @@ extern "C" hf_status hf_identify_grids_ws_size(double box_len, int32_t frac_bits
                                               const hf_grid_scale *scales, int32_t with_velocities, size_t *bytes) {
     if (!bytes) return HF_ERR_ARG;
     GridsLayout L{};
-    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, L);
+    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, true, L);
     if (s == HF_OK) *bytes = L.total;
     return s;
 }
@@ -386,7 +386,9 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
     const bool with_vel = vel != nullptr;
     if (with_vel && (!(grav_mass > 0.0) || !(grav_mass < 1e300))) return HF_ERR_ARG;
     GridsLayout L{};
-    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, L);
+    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, L);
+    if (s != HF_OK) return s;
+    if (ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, false, L);
     if (s != HF_OK) return s;
     int32_t hw[HF_CWT_BATCH_MAX];
     for (int j = 0; j < count; ++j) {
@@ -436,7 +438,7 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
         // removes (all of a discarded group's) are free again for later scales
         if (s == HF_OK && with_vel && sj.max_cap > 0) {
             s = unbind_dev(ctx, b, pos, vel, dtype, np, sj.max_idx, sj.max_cap, sj.group_keep, sj.particle_label,
-                           grav_mass, particle_th, sj.bound_keep, w0, sj.d_count);
+                           grav_mass, particle_th, sj.bound_keep, w0, sb, sj.d_count, sj.group_particles);
             if (s == HF_OK) s = unclaim(ctx, sj.particle_label, np, j, halo_scale, halo_root);
         }
     }

@@ -26,7 +26,16 @@ struct ScanJob {
     int64_t *total64;     // or null
     int64_t cap;          // capacity checked against the total (when total64 is set)
     uint32_t *status;
+    const int64_t *d_n = nullptr;  // on the device: values from min(*d_n, n) on count as 0 and are not read, and out
+                                   // is written up to that place only (and at n)
 };
+
+// Values of the job that are read.
+__device__ __forceinline__ int64_t scan_len(const ScanJob &j) {
+    if (!j.d_n) return j.n;
+    const int64_t d = *j.d_n;
+    return d < j.n ? d : j.n;
+}
 
 inline ScanJob scan_job(const uint32_t *in, int64_t n, uint64_t *partial, uint32_t *out, uint32_t *out2 = nullptr,
                         int64_t *total64 = nullptr, int64_t cap = 0, uint32_t *status = nullptr) {
@@ -59,8 +68,8 @@ __device__ __forceinline__ uint64_t scan_block_sum(uint64_t v, uint64_t *red) {
 template <int TAG>
 __global__ void __launch_bounds__(SCAN_THREADS) seg_reduce_kernel(ScanJob j) {
     __shared__ uint64_t red[SCAN_THREADS / 64];
-    const int64_t lo = int64_t(blockIdx.x) * j.seg;
-    const int64_t hi = lo + j.seg < j.n ? lo + j.seg : j.n;
+    const int64_t lo = int64_t(blockIdx.x) * j.seg, len = scan_len(j);
+    const int64_t hi = lo + j.seg < len ? lo + j.seg : len;
     uint64_t s = 0;
     for (int64_t i = lo + threadIdx.x; i < hi; i += SCAN_THREADS) s += j.in[i];
     const uint64_t t = scan_block_sum(s, red);
@@ -74,11 +83,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) seg_scan_kernel(ScanJob j) {
     const int g = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint64_t carry = scan_block_sum(threadIdx.x < unsigned(g) ? j.partial[threadIdx.x] : 0ull, red);
-    const int64_t lo = int64_t(g) * j.seg;
-    const int64_t hi = lo + j.seg < j.n ? lo + j.seg : j.n;
+    const int64_t lo = int64_t(g) * j.seg, len = scan_len(j);
+    const int64_t end = len < j.n ? len + 1 : j.n;  // the place after a shorter list holds its total
+    const int64_t hi = lo + j.seg < end ? lo + j.seg : end;
     for (int64_t base = lo; base < hi; base += SCAN_THREADS) {
         const int64_t i = base + threadIdx.x;
-        const uint32_t v = i < hi ? j.in[i] : 0u;
+        const uint32_t v = i < hi && i < len ? j.in[i] : 0u;
         uint32_t inc = v;
         for (int off = 1; off < 64; off <<= 1) {
             const uint32_t y = __shfl_up(inc, off, 64);
@@ -120,13 +130,13 @@ template <int TAG>
 __global__ void __launch_bounds__(SCAN_THREADS) one_scan_kernel(ScanJob j) {
     __shared__ uint32_t wsum[SCAN_THREADS / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = int(j.n);
+    const int n = int(j.n), len = int(scan_len(j));
     const int per = (n + SCAN_THREADS - 1) / SCAN_THREADS;
     const int lo = int(threadIdx.x) * per;
     uint32_t v[SCAN_PER], sum = 0;
 #pragma unroll
     for (int k = 0; k < SCAN_PER; ++k) {
-        v[k] = k < per && lo + k < n ? j.in[lo + k] : 0u;
+        v[k] = k < per && lo + k < len ? j.in[lo + k] : 0u;
         sum += v[k];
     }
     uint32_t inc = sum;

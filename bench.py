@@ -35,17 +35,18 @@ CSRC = os.path.join(ROOT, "paper_2501_10622_amd", "csrc")
 TIMER_SYMBOLS = {
     "zero_grid": ("fill_u64_kernel",), "deposit": ("tile_accum_kernel",), "label": ("label_kernel",),
     "deposit_atomic": ("deposit_atomic_kernel",),
-    "deposit_prep": ("zero_u32_kernel", "l1_scan_kernel", "l1_segs_kernel", "seg_reduce_kernel<0>", "seg_scan_kernel<0>"),
+    "deposit_prep": ("zero_u32_kernel", "l1_tables_kernel", "one_scan_kernel<0>", "seg_reduce_kernel<0>",
+                     "seg_scan_kernel<0>"),
     "deposit_l1_hist": ("l1_hist_kernel",), "deposit_l1_scatter": ("l1_scatter_kernel",),
     "deposit_l2_hist": ("l2_hist_kernel",), "deposit_l2_scatter": ("l2_scatter_kernel",),
     "deposit_fold": ("skirt_fold_kernel",),
-    "tables_1": ("tables_stage1",), "tables_2": ("tables_stage2",), "fft_x_fwd": ("fft_x_fwd_kernel",),
-    "mass": ("mass_kernel",), "fft_y_fwd": ("fft_y_kernel<false>",), "fft_z_mul": ("fft_z_mul_kernel",),
-    "fft_y_inv": ("fft_y_kernel<true>",), "fft_x_inv": ("fft_x_inv_kernel",),
+    "tables_1": ("tables_kernel",), "fft_x_fwd": ("fft_x_fwd_kernel",),
+    "fft_y_fwd": ("fft_y_fwd_kernel",), "fft_z_mul": ("fft_z_mul_kernel",),
+    "fft_y_inv": ("fft_y_inv_kernel",), "fft_x_inv": ("fft_x_inv_kernel",),
     "maxima_mark": ("max_tile_kernel", "max_direct_kernel"), "maxima_count": ("mask_count_kernel",),
-    "maxima_scan": ("seg_reduce_kernel<1>", "seg_scan_kernel<1>"), "maxima_write": ("list_write_kernel",),
-    "parent": ("parent_resolve_kernel", "parent_direct_kernel"), "jump_flags": ("fill_flags_kernel",),
-    "jump": ("bnd_jump_first_kernel", "bnd_jump_kernel", "jump_direct_kernel"), "finalize": ("seg_finalize_kernel", "finalize_direct_kernel"),
+    "maxima_scan": ("one_scan_kernel<1>", "seg_reduce_kernel<1>", "seg_scan_kernel<1>"), "maxima_write": ("list_write_kernel",),
+    "parent": ("parent_resolve_kernel",), "jump_flags": ("zero_words_kernel",),
+    "jump": ("bnd_chase_kernel",), "finalize": ("seg_finalize_kernel",),
     "label_tiles": ("tile_label_kernel",), "label_level1": ("to_level1_kernel",), "label_input": ("to_input_kernel",),
     "groups_clear": ("groups_clear_kernel",), "groups_cells": ("groups_runs_kernel<false>", "groups_tally_kernel<false>"),
     "groups_particles": ("groups_particles_kernel", "groups_runs_kernel<true>", "groups_tally_kernel<true>"), "groups_decide": ("groups_decide_kernel",),
@@ -64,7 +65,7 @@ def log(msg: str):
 STAGES = {
     "deposit": ("zero_grid", "deposit_atomic", "deposit_prep", "deposit_l1_hist", "deposit_l1_scatter",
                 "deposit_l2_hist", "deposit_l2_scatter", "deposit", "deposit_fold"),
-    "cwt_x_fwd": ("tables_1", "tables_2", "fft_x_fwd", "mass"),
+    "cwt_x_fwd": ("tables_1", "fft_x_fwd"),
     "cwt_y_fwd": ("fft_y_fwd",),
     "cwt_z_mul": ("fft_z_mul",),
     "cwt_y_inv": ("fft_y_inv",),
@@ -116,14 +117,14 @@ def source_digest() -> str:
 
 
 def short_symbol(name: str) -> str:
-    """'void (anonymous namespace)::fft_y_kernel<true>(args...)' -> 'fft_y_kernel<true>'."""
+    """'void (anonymous namespace)::seg_scan_kernel<1>(args...)' -> 'seg_scan_kernel<1>'."""
     import re
     m = re.search(r"(?:::|^|\s)([A-Za-z_]\w*)(<[^()]*>)?\(", name)
     if not m:
         return name
     tmpl = m.group(2) or ""
-    # keep a template argument only where it names a different pass (fft_y_kernel<INV>, the scans' use)
-    return m.group(1) + (tmpl if m.group(1) in ("fft_y_kernel", "seg_reduce_kernel", "seg_scan_kernel",
+    # keep a template argument only where it names a different pass (the scans' use)
+    return m.group(1) + (tmpl if m.group(1) in ("one_scan_kernel", "seg_reduce_kernel", "seg_scan_kernel",
                                                                "stencil_axis_kernel", "groups_tally_kernel",
                                                                "groups_runs_kernel") else "")
 

@@ -8,29 +8,25 @@
 // neighbourhood (itself included); a cell is a maximum iff it is its own
 // parent and its value exceeds tau.
 //
-// Tiled path: one workgroup per 32x16x16 tile holds the tile and
-// a one-cell halo of the field in LDS, forms every cell's parent (the largest
-// key of its 3x3x3 neighbourhood) and the maxima mask, and follows the parent
-// chains inside the tile, so the parents never go to memory.
+// One workgroup per 32x16x16 tile holds the tile and a one-cell halo of the
+// field in LDS, forms every cell's parent (the largest key of its 3x3x3
+// neighbourhood) and the maxima mask, and follows the parent chains inside the
+// tile, so the parents never go to memory.
 //  - maxima: a wavefront covers two 32-cell rows, so its ballot is two aligned
 //    32-bit words of a linear-order bit mask; count / scan / write passes turn
-//    the mask into the sorted index list (hf_maxima alone forms the maxima of
-//    32x8x8 tiles separably, x then y then z).
-//  - segmentation: parent chains are followed inside each 32x16x16 tile by
-//    pointer doubling in LDS, so every cell ends at a root or at the first cell
-//    its chain reaches outside the tile.  Such exit targets are always on a
-//    tile boundary, so only the 2312 boundary cells of each tile (kept in a
-//    compact array) have their chains followed across tiles.  A root at or
-//    below tau is written as -1 by its own tile, so the chains carry the
-//    threshold along and no later pass reads the field again.  A last pass,
-//    one workgroup per tile, loads the resolved entries of the one-cell shell
-//    around the tile (every exit target lies in it) into LDS and maps each
-//    cell of the tile through them.
+//    the mask into the sorted index list.
+//  - segmentation: every cell ends at a root or at the first cell its chain
+//    reaches outside the tile.  Such exit targets are always on a tile boundary,
+//    so only the 2312 boundary cells of each tile (kept in a compact array) have
+//    their chains followed across tiles.  A root at or below tau is no root to
+//    its own tile, so the chains carry the threshold along and no later pass
+//    reads the field again.  A last pass, one workgroup per tile, loads the
+//    resolved entries of the one-cell shell around the tile (every exit target
+//    lies in it) into LDS and maps each cell of the tile through them.
 // Any n: where n is not a multiple of a tile's extent, the last tile along
 // that axis is short (its cells past n are absent); a short tile's far-edge
-// cells take the boundary ranks of a full tile's far edge.  The separable
-// maxima pass of hf_maxima alone needs n % 32 == 0; other sizes use a direct
-// per-cell pass with the same results.
+// cells take the boundary ranks of a full tile's far edge, and the maxima are set
+// bit by bit (rows straddle mask words).
 #include "hf_internal.h"
 #include "scan.h"
 
@@ -46,13 +42,7 @@ __device__ __forceinline__ uint32_t ordered_bits(float c, bool &nan) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ uint64_t cell_key(float c, uint32_t idx, bool &nan) {
-    return (uint64_t(ordered_bits(c, nan)) << 32) | idx;
-}
-
 __device__ __forceinline__ uint32_t wrap(int v, int n) { return uint32_t(v < 0 ? v + n : (v >= n ? v - n : v)); }
-
-__device__ __forceinline__ uint64_t kmax(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
 uint32_t host_ordered_bits(float c) {
     uint32_t u;
@@ -63,22 +53,14 @@ uint32_t host_ordered_bits(float c) {
 }
 
 // ------------------------------------------------------------------ tile geometry
-constexpr int TX = 32, TY = 8, TZ = 8;
-constexpr int TCELLS = TX * TY * TZ;                          // 2048
-constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2;
-constexpr int HCELLS = HX * HY * HZ;                          // 3400
-constexpr int SEG_THREADS = 512;
-constexpr int PER_THREAD = TCELLS / SEG_THREADS;              // 4
-
 // Resolve tiles: chains are followed inside RX x RY x RZ tiles.
 constexpr int RX = 32, RY = 16, RZ = 16;
 constexpr int RCELLS = RX * RY * RZ;                          // 8192
 constexpr int RHX = RX + 2, RHY = RY + 2, RHZ = RZ + 2;
 constexpr int RHCELLS = RHX * RHY * RHZ;                      // 11016 (tile plus one-cell shell)
 static_assert(2 * RHX * RHY + (RHZ - 2) * (2 * RHX + 2 * (RHY - 2)) == RHCELLS - RCELLS, "shell enumeration");
-constexpr int NBND = 2 * RX * RY + (RZ - 2) * (2 * RX + 2 * (RY - 2));  // 2312 boundary cells per tile
-constexpr int RES_THREADS = 1024;
-constexpr int RES_PER = RCELLS / RES_THREADS;                 // 8
+constexpr int RING = 2 * RX + 2 * (RY - 2);                   // boundary cells of an inner z plane
+constexpr int NBND = 2 * RX * RY + (RZ - 2) * RING;           // 2312 boundary cells per tile
 
 struct TileGrid {
     int n;
@@ -98,9 +80,8 @@ __device__ __forceinline__ void cell_coords(const TileGrid &tg, uint32_t g, uint
 // 1..RY-2, then row y = RY-1), plane z = RZ-1.
 __device__ __forceinline__ int bnd_rank(int x, int y, int z) {
     if (z == 0) return y * RX + x;
-    constexpr int MID = 2 * RX + 2 * (RY - 2);
-    if (z == RZ - 1) return RX * RY + (RZ - 2) * MID + y * RX + x;
-    const int base = RX * RY + (z - 1) * MID;
+    if (z == RZ - 1) return RX * RY + (RZ - 2) * RING + y * RX + x;
+    const int base = RX * RY + (z - 1) * RING;
     if (y == 0) return base + x;
     if (y == RY - 1) return base + RX + 2 * (RY - 2) + x;
     if (x == 0) return base + RX + 2 * (y - 1);
@@ -141,126 +122,64 @@ __device__ __forceinline__ int64_t bnd_slot(const TileGrid &rg, int32_t g) {
     return bnd_slot_at<FULL>(rg, x, y, z);
 }
 
-// Loads the keys of the tile at (x0, y0, z0) plus a one-cell periodic halo and
-// leaves the parent key of local cell e = x + TX (y + TY z) in M[e].
-__device__ void tile_parent_keys(const float *__restrict__ c, int n, int x0, int y0, int z0, uint64_t *K,
-                                 uint64_t *M, bool &nan) {
-    // all loads of the tile are issued before any is used (one batch per thread)
-    constexpr int LOADS = (HCELLS + SEG_THREADS - 1) / SEG_THREADS;
-    float v[LOADS];
-    uint32_t jj[LOADS];
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int e = threadIdx.x + i * SEG_THREADS;
-        const int hx = e % HX, hy = (e / HX) % HY, hz = e / (HX * HY);
-        const uint32_t gx = wrap(x0 + hx - 1, n), gy = wrap(y0 + hy - 1, n), gz = wrap(z0 + hz - 1, n);
-        jj[i] = (gz * uint32_t(n) + gy) * uint32_t(n) + gx;
-        if (e < HCELLS) v[i] = c[jj[i]];
-    }
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int e = threadIdx.x + i * SEG_THREADS;
-        if (e < HCELLS) K[e] = cell_key(v[i], jj[i], nan);
-    }
-    __syncthreads();
-    // x: M[hz][hy][x] over HZ x HY x TX
-    for (int e = threadIdx.x; e < TX * HY * HZ; e += SEG_THREADS) {
-        const int x = e % TX, r = e / TX;  // r = hz * HY + hy
-        const uint64_t *k = K + r * HX + x;
-        M[e] = kmax(kmax(k[0], k[1]), k[2]);
-    }
-    __syncthreads();
-    // y: K[hz][y][x] over HZ x TY x TX
-    for (int e = threadIdx.x; e < TX * TY * HZ; e += SEG_THREADS) {
-        const int x = e % TX, y = (e / TX) % TY, hz = e / (TX * TY);
-        const uint64_t *m = M + (hz * HY + y) * TX + x;
-        K[e] = kmax(kmax(m[0], m[TX]), m[2 * TX]);
-    }
-    __syncthreads();
-    // z: M[z][y][x] over TZ x TY x TX
-    for (int e = threadIdx.x; e < TCELLS; e += SEG_THREADS) {
-        const uint64_t *k = K + e;
-        M[e] = kmax(kmax(k[0], k[TX * TY]), k[2 * TX * TY]);
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void tile_origin(const TileGrid &tg, int t, int &x0, int &y0, int &z0) {
-    x0 = (t % tg.ntx) * TX;
-    y0 = ((t / tg.ntx) % tg.nty) * TY;
-    z0 = (t / (tg.ntx * tg.nty)) * TZ;
-}
-
 __device__ __forceinline__ void rtile_origin(const TileGrid &rg, int t, int &x0, int &y0, int &z0) {
     x0 = (t % rg.ntx) * RX;
     y0 = ((t / rg.ntx) % rg.nty) * RY;
     z0 = (t / (rg.ntx * rg.nty)) * RZ;
 }
 
-// Maxima bit mask of the tile from its parent keys M: bit (j % 32) of word
-// j / 32 is set iff cell j is its own parent with a value above tau.
-__device__ __forceinline__ void write_mask(const uint64_t *M, uint32_t n, int x0, int y0, int z0, uint32_t tau_ord,
-                                           uint32_t *__restrict__ mask) {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-        const int e = i * SEG_THREADS + threadIdx.x;  // a wavefront covers rows (y, z) and (y + 1, z)
-        const int x = e % TX, y = (e / TX) % TY, z = e / (TX * TY);
-        const uint32_t g = ((uint32_t(z0 + z) * n) + uint32_t(y0 + y)) * n + uint32_t(x0 + x);
-        const uint64_t p = M[e];
-        const bool is_max = uint32_t(p) == g && uint32_t(p >> 32) > tau_ord;
-        const unsigned long long bits = __ballot(is_max);
-        if ((threadIdx.x & 63) == 0) {
-            mask[g >> 5] = uint32_t(bits);
-            mask[(g + n) >> 5] = uint32_t(bits >> 32);  // next row of the tile
-        }
-    }
-}
-
-__global__ void __launch_bounds__(SEG_THREADS) max_tile_kernel(const float *__restrict__ c, TileGrid tg,
-                                                               uint32_t tau_ord, uint32_t *__restrict__ mask,
-                                                               uint32_t *status) {
-    __shared__ uint64_t K[HCELLS];
-    __shared__ uint64_t M[TX * HY * HZ];
-    int x0, y0, z0;
-    const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
-    tile_origin(tg, int(tile), x0, y0, z0);
-    bool nan = false;
-    tile_parent_keys(c, tg.n, x0, y0, z0, K, M, nan);
-    write_mask(M, uint32_t(tg.n), x0, y0, z0, tau_ord, mask);
-    if (nan) atomicOr(status, ST_INPUT);
-}
-
 // Parents and the chains inside a resolve tile in one pass, one workgroup per
-// RX x RY x RZ tile.  A cell's parent is the index of the largest key of its
-// 3x3x3 neighbourhood, or -1 for a root (its own parent) at or below tau; with
-// a mask the tile's maxima bits are written as well (the maxima are exactly
-// the cells that are their own parent, above tau).
+// RX x RY x RZ tile.  A cell's parent is the largest key of its 3x3x3
+// neighbourhood, and a root (its own parent) at or below tau is no root; with a
+// mask the tile's maxima bits are written as well (the maxima are exactly the
+// cells that are their own parent, above tau); without CHAINS they are all that is
+// wanted.
 //
-// The tile and a one-cell halo of the field sit in LDS as 32-bit
-// order-preserving bits (the index half of a key is formed in registers).
-// Each thread walks one z column: the largest key of each 3x3 halo plane
-// around the column is formed once, and a cell's parent is the largest of the
-// three plane maxima around it (about 10 LDS reads per cell).  The parents
-// then replace the field in LDS as the tile's pointer array, where chains are
-// followed by pointer doubling, so that on exit every cell holds its root (-1
-// for a root at or below tau) or the first cell its chain reaches outside the
-// tile; that goes to ptr and, for the tile's boundary cells, to bnd.  In LDS,
-// loc[e] >= 0 points to local cell loc[e]; loc[e] < 0 is resolved to the
-// value -2 - loc[e].
-constexpr int PR_THREADS = RX * RY;          // one z column each
-constexpr int PR_PER = RCELLS / PR_THREADS;  // RZ cells per thread
-static_assert(RHCELLS >= RCELLS, "the pointer array fits where the field was");
+// The tile and a one-cell shell of the field sit in LDS as 32-bit
+// order-preserving bits, a row of RHX of them per (hy, hz).  A thread walks one
+// z column.  Its nine columns' addresses are kept in the order of their cells'
+// linear indices (rotated where the column or row lies at the end of the
+// periodic box), so the largest key of a halo plane is the last largest value
+// met in that order: a 32-bit compare and two selects per neighbour, the
+// neighbour's address itself being what is selected.  A cell's parent is the
+// largest of the three plane maxima around it, planes in index order too.
+//
+// The field's array then becomes the pointer array, with byte addresses as
+// pointers: a cell points at its parent, a root and every cell of the shell at
+// itself, a root at or below tau at the extra place NONE, which points at
+// itself.  Following a pointer is one LDS read, done when it leads to itself.
+// Wavefronts go on for themselves: what one reads while another writes lies
+// further along the same chain.  The addresses reached go to ptr (16 bits per
+// cell, a column of RZ per thread), and for the tile's boundary cells the index
+// of the cell reached to bnd.
+//
+// Bound by the vector ALUs, busy 78% of the time with 108 instructions per cell
+// (half of them the parents, a quarter the pointers).  With an index decoded per
+// parent, a bounds check per axis, and workgroup-wide rounds over 32-bit indices it
+// was 181 per cell and all of the time: 88 -> 67 us at 256^3, 4.76 -> 3.71 ms at
+// 1024^3, 22 -> 15 us at 96^3.  For the maxima alone it took the place of
+// a pass over 32x8x8 tiles
+// with 64-bit keys and, where n is no multiple of 32, of one that read 27 values per
+// cell from memory (235^3: 157 -> 37 us).
+constexpr int PR_THREADS = RX * RY;           // one z column each
+constexpr int PLANE_BYTES = 4 * RHX * RHY;
+constexpr uint32_t NONE = 4 * RHCELLS;        // address of the place past the halo tile
+static_assert(NONE <= 0xffffu, "addresses fit 16 bits");
+static_assert(RZ % 8 == 0, "a column of addresses is whole 16-byte words");
 constexpr int CHASE_FLAGS = 8;  // one per launch of the boundary chase, at most 4 at n = 1024
 
-template <bool FULL>
+// The words of a column's 16-bit addresses, RZ / 8 of 16 bytes.
+constexpr int COLUMN_WORDS = RZ / 8;
+
+template <bool FULL, bool CHAINS>
 __global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float *__restrict__ c, TileGrid rg,
-                                                                    uint32_t tau_ord, int32_t *__restrict__ ptr,
+                                                                    uint32_t tau_ord, uint4 *__restrict__ ptr,
                                                                     int32_t *__restrict__ bnd,
                                                                     uint32_t *__restrict__ mask,
                                                                     uint32_t *__restrict__ flags, uint32_t *status) {
-    __shared__ uint32_t V[RHCELLS];
-    if (blockIdx.x == 0 && threadIdx.x < CHASE_FLAGS) flags[threadIdx.x] = 0u;  // of the chase that follows
-    int32_t *loc = reinterpret_cast<int32_t *>(V);  // after the parents are formed
+    __shared__ uint32_t V[RHCELLS + 1];
+    __shared__ uint32_t rowbase[RHY * RHZ];  // index of the first cell of each halo row's grid row
+    if (CHAINS && blockIdx.x == 0 && threadIdx.x < CHASE_FLAGS) flags[threadIdx.x] = 0u;  // of the chase that follows
     int x0, y0, z0;
     const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
     rtile_origin(rg, int(tile), x0, y0, z0);
@@ -270,178 +189,193 @@ __global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float 
     // the tile: its cells past n are absent (never pointed to, never written)
     const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
               wz = FULL ? RZ : tile_extent(z0, RZ, n);
-    const bool full = FULL || (wx == RX && wy == RY && wz == RZ);
+    const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
+    if (tid < RHY * RHZ) {
+        const int hy = tid % RHY, hz = tid / RHY;
+        const bool there = FULL || (hy <= wy + 1 && hz <= wz + 1);
+        rowbase[tid] = there ? (wrap(z0 + hz - 1, n) * un + wrap(y0 + hy - 1, n)) * un : 0u;
+    }
+    __syncthreads();
     bool nan = false;
     {
-        // all loads of the halo tile are issued before any is used
-        constexpr int LOADS = (RHCELLS + PR_THREADS - 1) / PR_THREADS;
-        float v[LOADS];
+        // all loads of the halo tile are issued before any is used: the rows'
+        // inner columns, 32 lanes to a row, then their two ends
+        constexpr int ROWS = RHY * RHZ, STEP = PR_THREADS / RX, LOADS = (ROWS + STEP - 1) / STEP;
+        constexpr int ENDS = (2 * ROWS + PR_THREADS - 1) / PR_THREADS;
+        float v[LOADS], w[ENDS];
+        // (past a short tile's shell any cell will do: nothing looks there)
+        const uint32_t gx = FULL ? uint32_t(x0 + x) : (x <= wx ? wrap(x0 + x, n) : 0u);
+        const uint32_t ends[2] = {wrap(x0 - 1, n), FULL || wx == RX ? wrap(x0 + RX, n) : 0u};
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int e = threadIdx.x + i * PR_THREADS;
-            const int hx = e % RHX, hy = (e / RHX) % RHY, hz = e / (RHX * RHY);
-            if (e < RHCELLS)
-                v[i] = c[(wrap(z0 + hz - 1, n) * un + wrap(y0 + hy - 1, n)) * un + wrap(x0 + hx - 1, n)];
+            const int r = y + i * STEP;
+            if (r < ROWS) v[i] = c[rowbase[r] + gx];
+        }
+#pragma unroll
+        for (int i = 0; i < ENDS; ++i) {
+            const int e = tid + i * PR_THREADS;
+            if (e < 2 * ROWS) w[i] = c[rowbase[e >> 1] + ends[e & 1]];
         }
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int e = threadIdx.x + i * PR_THREADS;
-            if (e < RHCELLS) V[e] = ordered_bits(v[i], nan);
+            const int r = y + i * STEP;
+            if (r < ROWS) V[r * RHX + x + 1] = ordered_bits(v[i], nan);
+        }
+#pragma unroll
+        for (int i = 0; i < ENDS; ++i) {
+            const int e = tid + i * PR_THREADS;
+            if (e < 2 * ROWS) V[(e >> 1) * RHX + (e & 1) * (RHX - 1)] = ordered_bits(w[i], nan);
         }
     }
     __syncthreads();
-    // the thread's column (x, y); a wavefront covers rows y and y + 1 of one z,
-    // so its ballot is two aligned 32-bit words of the mask
-    const int x = threadIdx.x % RX, y = threadIdx.x / RX;
-    const int lane = threadIdx.x & 63;
-    uint32_t gx[3], gyn[3];  // global x of the halo columns x - 1 .. x + 1, and (global y) * n of the rows
+    char *const lds = reinterpret_cast<char *>(V);
+    auto at = [lds](uint32_t a) { return reinterpret_cast<uint32_t *>(lds + a); };
+    // addresses in halo plane 0 of the columns around (x, y), in the order of
+    // their linear indices: of rows y - 1, y, y + 1 and columns x - 1, x, x + 1 the
+    // one beyond the end of the box comes last or first
+    const uint32_t own = 4u * uint32_t((y + 1) * RHX + x + 1);
+    uint32_t a[9];
+    {
+        const int xr = x0 + x == 0 ? 1 : (x0 + x == n - 1 ? 2 : 0), yr = y0 + y == 0 ? 1 : (y0 + y == n - 1 ? 2 : 0);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        gx[d] = wrap(x0 + x + d - 1, n);
-        gyn[d] = wrap(y0 + y + d - 1, n) * un;
-    }
-    // largest key of halo plane hz around the column
-    auto plane_max = [&](int hz) {
-        const uint32_t plane = wrap(z0 + hz - 1, n) * un * un;
-        uint64_t best = 0;
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-            const uint32_t row = plane + gyn[dy];
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx)
-                best = kmax(best, (uint64_t(V[(hz * RHY + y + dy) * RHX + x + dx]) << 32) | (row + gx[dx]));
+        for (int k = 0; k < 9; ++k) {
+            const int dy = (k / 3 + yr) % 3 - 1, dx = (k % 3 + xr) % 3 - 1;
+            a[k] = own + uint32_t(4 * (dy * RHX + dx));
         }
-        return best;
-    };
-    int32_t l[PR_PER];
-    // a tile whose halo does not wrap around the periodic box: there a cell's
-    // neighbours, taken in (dz, dy, dx) order, come in increasing global index,
-    // so the largest key is the last largest value met in that order (32-bit
-    // compares and a neighbour code 0..26, no index per neighbour)
-    const bool interior = FULL && x0 > 0 && x0 + RX < n && y0 > 0 && y0 + RY < n && z0 > 0 && z0 + RZ < n;
-    if (interior) {
-        auto plane_arg = [&](int hz, uint32_t &bv, uint32_t &bc) {
-            bv = V[(hz * RHY + y) * RHX + x];
-            bc = 0u;
+    }
+    // value and address of the largest key of halo plane hz around the column
+    auto plane_arg = [&](int hz, uint32_t &bv, uint32_t &ba) {
+        bv = *at(a[0] + uint32_t(hz * PLANE_BYTES));
+        ba = a[0];
 #pragma unroll
-            for (int k = 1; k < 9; ++k) {
-                const uint32_t v = V[(hz * RHY + y + k / 3) * RHX + x + k % 3];
-                const bool up = v >= bv;
-                bv = up ? v : bv;
-                bc = up ? uint32_t(k) : bc;
-            }
-        };
-        uint32_t v0, c0, v1, c1;
-        plane_arg(0, v0, c0);
-        plane_arg(1, v1, c1);
-        const uint32_t gb = (uint32_t(z0) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+        for (int k = 1; k < 9; ++k) {
+            const uint32_t v = *at(a[k] + uint32_t(hz * PLANE_BYTES));
+            const bool up = v >= bv;
+            bv = up ? v : bv;
+            ba = up ? a[k] : ba;
+        }
+        ba += uint32_t(hz * PLANE_BYTES);
+    };
+    auto larger = [](uint32_t &bv, uint32_t &ba, uint32_t v, uint32_t va) {
+        const bool up = v >= bv;
+        bv = up ? v : bv;
+        ba = up ? va : ba;
+    };
+    const bool column = FULL || (x < wx && y < wy);
+    uint32_t l[RZ];
+    uint32_t maxima = 0;  // of the column
+    {
+        uint32_t v0, p0, v1, p1;
+        plane_arg(0, v0, p0);
+        plane_arg(1, v1, p1);
 #pragma unroll
         for (int z = 0; z < RZ; ++z) {
-            uint32_t v2, c2;
-            plane_arg(z + 2, v2, c2);
-            uint32_t bv = v0, bc = c0;
-            if (v1 >= bv) {
+            uint32_t v2, p2, bv, ba;
+            plane_arg(z + 2, v2, p2);
+            if (z0 + z == 0) {  // plane z - 1 is the last of the box
                 bv = v1;
-                bc = c1 + 9u;
-            }
-            if (v2 >= bv) {
+                ba = p1;
+                larger(bv, ba, v2, p2);
+                larger(bv, ba, v0, p0);
+            } else if (z0 + z == n - 1) {  // plane z + 1 is the first
                 bv = v2;
-                bc = c2 + 18u;
+                ba = p2;
+                larger(bv, ba, v0, p0);
+                larger(bv, ba, v1, p1);
+            } else {
+                bv = v0;
+                ba = p0;
+                larger(bv, ba, v1, p1);
+                larger(bv, ba, v2, p2);
             }
-            const uint32_t g = gb + uint32_t(z) * un * un;
-            const bool self = bc == 13u;  // (dz, dy, dx) = (1, 1, 1)
+            const bool self = ba == own + uint32_t((z + 1) * PLANE_BYTES);
             const bool high = bv > tau_ord;
-            if (mask) {  // the wavefront's two rows are two aligned mask words
+            if (FULL && mask) {  // a wavefront covers rows y and y + 1: two aligned mask words
                 const unsigned long long bits = __ballot(self && high);
-                if (lane == 0) {
+                if ((tid & 63) == 0) {
+                    const uint32_t g = (uint32_t(z0 + z) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
                     mask[g >> 5] = uint32_t(bits);
                     mask[(g + un) >> 5] = uint32_t(bits >> 32);
                 }
             }
-            const int lx = x + int(bc % 3u) - 1, ly = y + int((bc / 3u) % 3u) - 1, lz = z + int(bc / 9u) - 1;
-            if (self)
-                l[z] = high ? -2 - int32_t(g) : -1;
-            else if (lx >= 0 && lx < RX && ly >= 0 && ly < RY && lz >= 0 && lz < RZ)
-                l[z] = lx + RX * (ly + RY * lz);
-            else
-                l[z] = -2 - int32_t((uint32_t(z0 + lz) * un + uint32_t(y0 + ly)) * un + uint32_t(x0 + lx));
+            maxima |= self && high ? 1u << z : 0u;
+            l[z] = self && !high ? NONE : ba;
             v0 = v1;
-            c0 = c1;
+            p0 = p1;
             v1 = v2;
-            c1 = c2;
-        }
-    } else {
-        uint64_t b0 = plane_max(0), b1 = plane_max(1);
-#pragma unroll
-        for (int z = 0; z < RZ; ++z) {
-            const uint64_t b2 = plane_max(z + 2);
-            const uint64_t best = kmax(kmax(b0, b1), b2);
-            const bool real = x < wx && y < wy && z < wz;
-            const uint32_t g = (uint32_t(z0 + z) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-            const uint32_t p = uint32_t(best);
-            const bool high = uint32_t(best >> 32) > tau_ord;
-            if (mask) {
-                if (FULL) {  // the wavefront's two rows are two aligned mask words
-                    const unsigned long long bits = __ballot(p == g && high);
-                    if (lane == 0) {
-                        mask[g >> 5] = uint32_t(bits);
-                        mask[(g + un) >> 5] = uint32_t(bits >> 32);
-                    }
-                } else if (real && p == g && high) {  // rows straddle words: the mask was cleared first
-                    atomicOr(&mask[g >> 5], 1u << (g & 31u));
-                }
-            }
-            // local form: a root (above tau: itself; else -1) is resolved, so is
-            // a parent outside the tile; a parent inside is followed
-            l[z] = (p == g) ? (high ? -2 - int32_t(g) : -1) : -2 - int32_t(p);
-            if (!real) l[z] = -1;  // absent
-            if (real && p != g) {
-                uint32_t px, py, pz;
-                cell_coords(rg, p, px, py, pz);
-                const int lx = int(px) - x0, ly = int(py) - y0, lz = int(pz) - z0;
-                if (lx >= 0 && lx < RX && ly >= 0 && ly < RY && lz >= 0 && lz < RZ) l[z] = lx + RX * (ly + RY * lz);
-            }
-            b0 = b1;
-            b1 = b2;
+            p1 = p2;
         }
     }
     if (nan) atomicOr(status, ST_INPUT);
+    if (!FULL && mask && column) {  // rows straddle words: the mask was cleared first
+        const uint32_t g = (uint32_t(z0) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+        for (int z = 0; z < wz; ++z) {
+            const uint32_t gz = g + uint32_t(z) * un * un;
+            if (maxima >> z & 1u) atomicOr(&mask[gz >> 5], 1u << (gz & 31u));
+        }
+    }
+    if (!CHAINS) return;
     __syncthreads();  // every read of the field is done
-#pragma unroll
-    for (int z = 0; z < RZ; ++z) loc[threadIdx.x + z * PR_THREADS] = l[z];  // local cell x + RX (y + RY z)
+    for (uint32_t e = tid; e <= uint32_t(RHCELLS); e += PR_THREADS) V[e] = 4u * e;
     __syncthreads();
-    // pointer doubling inside the tile (chains are at most RCELLS - 1 long)
+    // where the column's pointers are; an absent cell's goes to NONE, which it holds
+    auto slot = [=](int z) {
+        return FULL || (column && z < wz) ? own + uint32_t((z + 1) * PLANE_BYTES) : NONE;
+    };
+#pragma unroll
+    for (int z = 0; z < RZ; ++z) {
+        if (!FULL && slot(z) == NONE) l[z] = NONE;
+        *at(slot(z)) = l[z];
+    }
+    __syncthreads();
+    // (relaxed atomic accesses: other wavefronts write while this one reads)
     bool open = true;
     while (open) {
-        int32_t nv[PR_PER];
-        bool any = false;
+        uint32_t w[RZ];
+        uint32_t moved = 0;
 #pragma unroll
-        for (int i = 0; i < PR_PER; ++i) {
-            const int32_t w = loc[i * PR_THREADS + threadIdx.x];
-            nv[i] = w >= 0 ? loc[w] : w;
-            any |= nv[i] >= 0;
+        for (int z = 0; z < RZ; ++z) w[z] = __hip_atomic_load(at(l[z]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+        for (int z = 0; z < RZ; ++z) {
+            moved |= w[z] ^ l[z];
+            l[z] = w[z];
         }
-        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PR_PER; ++i) loc[i * PR_THREADS + threadIdx.x] = nv[i];
-        open = __syncthreads_or(any);
+        for (int z = 0; z < RZ; ++z)
+            __hip_atomic_store(at(slot(z)), w[z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        open = __any(moved != 0u);
     }
-    if (!full) {
+    uint4 *out = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
+#pragma unroll
+    for (int q = 0; q < COLUMN_WORDS; ++q)
+        out[q] = make_uint4(l[8 * q] | (l[8 * q + 1] << 16), l[8 * q + 2] | (l[8 * q + 3] << 16),
+                            l[8 * q + 4] | (l[8 * q + 5] << 16), l[8 * q + 6] | (l[8 * q + 7] << 16));
+    if (!FULL && !(wx == RX && wy == RY && wz == RZ)) {
         // a short tile leaves some of its boundary slots unused: they hold -1
         // (final), so that the chase, which visits every slot, reads no
         // stale entry
-        for (int k = threadIdx.x; k < NBND; k += PR_THREADS) bnd[int64_t(tile) * NBND + k] = -1;
+        for (int k = tid; k < NBND; k += PR_THREADS) bnd[int64_t(tile) * NBND + k] = -1;
         __syncthreads();
     }
+    if (!column) return;
+    // index of the cell at address p
+    auto cell_at = [&](uint32_t p) {
+        if (p == NONE) return -1;
+        const uint32_t r = p / (4u * RHX), hx = p / 4u - r * RHX;
+        return int32_t(rowbase[r] + wrap(x0 + int(hx) - 1, n));
+    };
+    const int bx = x == wx - 1 ? RX - 1 : x, by = y == wy - 1 ? RY - 1 : y;  // a short tile's far edge: bnd_rank_in
+    int32_t *mine = bnd + int64_t(tile) * NBND;
+    const int ring = bnd_rank(bx, by, 1);  // of plane 1; later inner planes' ranks follow at equal distances
 #pragma unroll
-    for (int i = 0; i < PR_PER; ++i) {
-        const int e = i * PR_THREADS + threadIdx.x;  // (x, y) of this thread, z = i
-        if (x >= wx || y >= wy || i >= wz) continue;
-        const uint32_t g = ((uint32_t(z0 + i) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-        const int32_t t = -2 - loc[e];
-        ptr[g] = t;
-        const int r = bnd_rank_in(x, y, i, wx, wy, wz);
-        if (r >= 0) bnd[int64_t(tile) * NBND + r] = t;
+    for (int z = 0; z < RZ; ++z) {
+        if (!FULL && z >= wz) continue;
+        if (z == wz - 1)
+            mine[bnd_rank(bx, by, RZ - 1)] = cell_at(l[z]);
+        else if (z == 0)
+            mine[bnd_rank(bx, by, 0)] = cell_at(l[z]);
+        else if (ring >= 0)
+            mine[ring + (z - 1) * RING] = cell_at(l[z]);
     }
 }
 
@@ -517,16 +451,19 @@ __global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t co
     if (__ballot(open) && (threadIdx.x & 63) == 0) flags[round + 1] = 1u;
 }
 
-// One workgroup per resolve tile: the resolved boundary entries of the
-// one-cell shell around the tile go to LDS (they belong to the neighbouring
-// tiles; every exit target of the tile lies in the shell), then every cell of
-// the tile maps its pointer: -1 stays -1, a target inside the tile is a root
-// above tau, a target in the shell takes the shell's entry.
+// One workgroup per resolve tile.  A table in LDS holds, at each place of the
+// halo tile, the root that a pointer to it stands for: the resolved boundary
+// entries of the one-cell shell around the tile (they belong to the neighbouring
+// tiles; every exit target of the tile lies in the shell), each cell of the tile
+// its own index (only roots above tau are pointed at), and -1 at NONE.  A cell's
+// label is then the table's entry at its address.  Bound by HBM: 2 bytes read and
+// 4 written per cell (1024^3: 1.57 ms, 4.1 TB/s).  With 32-bit indices in ptr, taken
+// apart into coordinates for every cell, 2.38 ms; 256^3 40 -> 22 us.
 template <bool FULL>
-__global__ void __launch_bounds__(RES_THREADS) seg_finalize_kernel(const int32_t *__restrict__ ptr,
-                                                                   const int32_t *__restrict__ bnd, TileGrid rg,
-                                                                   int32_t *__restrict__ label) {
-    __shared__ int32_t shell[RHCELLS];
+__global__ void __launch_bounds__(PR_THREADS) seg_finalize_kernel(const uint4 *__restrict__ ptr,
+                                                                  const int32_t *__restrict__ bnd, TileGrid rg,
+                                                                  int32_t *__restrict__ label) {
+    __shared__ int32_t table[RHCELLS + 1];
     int x0, y0, z0;
     const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
     rtile_origin(rg, int(tile), x0, y0, z0);
@@ -534,15 +471,12 @@ __global__ void __launch_bounds__(RES_THREADS) seg_finalize_kernel(const int32_t
     const uint32_t un = uint32_t(n);
     const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
               wz = FULL ? RZ : tile_extent(z0, RZ, n);
-    // this tile's pointers and the shell's entries, all loads issued before any is used
-    int32_t t[RES_PER];
+    // this column's addresses and the shell's entries, all loads issued before any is used
+    const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
+    uint4 t[COLUMN_WORDS];
+    const uint4 *in = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
 #pragma unroll
-    for (int i = 0; i < RES_PER; ++i) {
-        const int e = i * RES_THREADS + threadIdx.x;
-        const int x = e % RX, y = (e / RX) % RY, z = e / (RX * RY);
-        t[i] = 0;
-        if (x < wx && y < wy && z < wz) t[i] = ptr[((uint32_t(z0 + z) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x)];
-    }
+    for (int q = 0; q < COLUMN_WORDS; ++q) t[q] = in[q];
     // the one-cell shell around the tile's (wx, wy, wz) cells, enumerated: the
     // two z planes, then per inner plane the two y rows and the two x ends of
     // the rows between them; shell cell (hx, hy, hz) sits at LDS place
@@ -550,12 +484,12 @@ __global__ void __launch_bounds__(RES_THREADS) seg_finalize_kernel(const int32_t
     const int ex = wx + 2, ey = wy + 2, ez = wz + 2;
     const int zplane = ex * ey, ring = 2 * ex + 2 * (ey - 2);
     const int nshell = 2 * zplane + (ez - 2) * ring;
-    constexpr int LOADS = (RHCELLS - RCELLS + RES_THREADS - 1) / RES_THREADS;
+    constexpr int LOADS = (RHCELLS - RCELLS + PR_THREADS - 1) / PR_THREADS;
     int32_t v[LOADS];
     int at[LOADS];
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-        const int k = threadIdx.x + i * RES_THREADS;
+        const int k = tid + i * PR_THREADS;
         at[i] = -1;
         if (k >= nshell) continue;
         int hx, hy, hz;
@@ -583,73 +517,23 @@ __global__ void __launch_bounds__(RES_THREADS) seg_finalize_kernel(const int32_t
     }
 #pragma unroll
     for (int i = 0; i < LOADS; ++i)
-        if (at[i] >= 0) shell[at[i]] = v[i];
+        if (at[i] >= 0) table[at[i]] = v[i];
+    if (tid == 0) table[RHCELLS] = -1;
+    const bool column = x < wx && y < wy;
+    const uint32_t g0 = ((uint32_t(z0) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+    const int own = (RHY + y + 1) * RHX + x + 1;
+#pragma unroll
+    for (int z = 0; z < RZ; ++z)
+        if (FULL || (column && z < wz)) table[own + z * RHX * RHY] = int32_t(g0 + uint32_t(z) * un * un);
     __syncthreads();
+    if (!column) return;
+    const char *lds = reinterpret_cast<const char *>(table);
 #pragma unroll
-    for (int i = 0; i < RES_PER; ++i) {
-        const int e = i * RES_THREADS + threadIdx.x;
-        const int x = e % RX, y = (e / RX) % RY, z = e / (RX * RY);
-        if (x >= wx || y >= wy || z >= wz) continue;
-        const uint32_t g = ((uint32_t(z0 + z) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-        int32_t r = t[i];
-        if (r >= 0) {
-            uint32_t px, py, pz;
-            cell_coords(rg, uint32_t(r), px, py, pz);
-            // shell coordinates of the target, periodic
-            const int hx = int(wrap(int(px) - x0 + 1, n)), hy = int(wrap(int(py) - y0 + 1, n)),
-                      hz = int(wrap(int(pz) - z0 + 1, n));
-            const bool inside = hx >= 1 && hx <= wx && hy >= 1 && hy <= wy && hz >= 1 && hz <= wz;
-            if (!inside) r = shell[(hz * RHY + hy) * RHX + hx];
-        }
-        label[g] = r;
+    for (int z = 0; z < RZ; ++z) {
+        if (!FULL && z >= wz) continue;
+        const uint32_t word = (&t[z / 8].x)[(z % 8) / 2], a = z & 1 ? word >> 16 : word & 0xffffu;
+        label[g0 + uint32_t(z) * un * un] = *reinterpret_cast<const int32_t *>(lds + a);
     }
-}
-
-// ------------------------------------------------------------------ direct path (n % 32 != 0)
-__device__ __forceinline__ uint64_t neighbour_max(const float *__restrict__ c, int n, int x, int y, int z,
-                                                  bool &nan) {
-    uint64_t best = 0;
-#pragma unroll
-    for (int dz = -1; dz <= 1; ++dz) {
-        const uint32_t zz = wrap(z + dz, n);
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-            const uint32_t yy = wrap(y + dy, n);
-            const uint32_t row = (zz * uint32_t(n) + yy) * uint32_t(n);
-#pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (dz == 0 && dy == 0 && dx == 0) continue;
-                const uint32_t j = row + wrap(x + dx, n);
-                best = kmax(best, cell_key(c[j], j, nan));
-            }
-        }
-    }
-    return best;
-}
-
-__global__ void __launch_bounds__(256) max_direct_kernel(const float *__restrict__ c, int n, float tau,
-                                                         uint32_t *__restrict__ mask, uint32_t *status) {
-    const uint32_t cells = uint32_t(n) * n * n;
-    const uint32_t words = (cells + 31) / 32;
-    bool nan = false;
-    // one wavefront per 64 consecutive cells: two mask words
-    for (uint32_t base = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); base < cells;
-         base += gridDim.x * blockDim.x) {
-        const uint32_t j = base + (threadIdx.x & 63u);
-        bool is_max = false;
-        if (j < cells) {
-            const int x = int(j % uint32_t(n)), y = int((j / uint32_t(n)) % uint32_t(n)),
-                      z = int(j / (uint32_t(n) * n));
-            const float v = c[j];
-            is_max = (v > tau) && cell_key(v, j, nan) > neighbour_max(c, n, x, y, z, nan);
-        }
-        const unsigned long long bits = __ballot(is_max);
-        if ((threadIdx.x & 63) == 0) {
-            mask[base >> 5] = uint32_t(bits);
-            if ((base >> 5) + 1 < words) mask[(base >> 5) + 1] = uint32_t(bits >> 32);
-        }
-    }
-    if (nan) atomicOr(status, ST_INPUT);
 }
 
 // ------------------------------------------------------------------ mask -> sorted list
@@ -671,22 +555,19 @@ __global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint
                                                                       int64_t words,
                                                                       const uint32_t *__restrict__ offsets,
                                                                       int64_t cap, int32_t *__restrict__ out) {
-    __shared__ uint32_t pre[LIST_CHUNK_WORDS];
+    static_assert(LIST_CHUNK_WORDS == 128, "two wavefronts");
+    __shared__ uint32_t first;  // maxima of the first wavefront's words
     const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
-    const uint32_t bits0 = w < words ? mask[w] : 0u;
-    pre[threadIdx.x] = uint32_t(__popc(bits0));
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t r = 0;
-        for (int i = 0; i < LIST_CHUNK_WORDS; ++i) {
-            const uint32_t v = pre[i];
-            pre[i] = r;
-            r += v;
-        }
+    uint32_t bits = w < words ? mask[w] : 0u;
+    const uint32_t count = uint32_t(__popc(bits));
+    uint32_t upto = count;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = __shfl_up(upto, off, 64);
+        if (int(threadIdx.x & 63u) >= off) upto += v;
     }
+    if (threadIdx.x == 63) first = upto;
     __syncthreads();
-    uint32_t bits = bits0;
-    uint32_t r = offsets[blockIdx.x] + pre[threadIdx.x];
+    uint32_t r = offsets[blockIdx.x] + upto - count + (threadIdx.x >= 64 ? first : 0u);
     while (bits) {
         const int b = __ffs(bits) - 1;
         bits &= bits - 1;
@@ -696,10 +577,6 @@ __global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint
 }
 
 // ------------------------------------------------------------------ host side
-bool tiled(int n) { return n % TX == 0; }  // TY, TZ, RY and RZ (8 or 16) divide every multiple of 32
-
-TileGrid tile_grid(int n) { return TileGrid{n, n / TX, n / TY, n / TZ, FastDiv(uint32_t(n))}; }
-
 // True where every resolve tile is whole (n a multiple of 32, hence of 16).
 bool all_full(int n) { return n % RX == 0 && n % RY == 0 && n % RZ == 0; }
 
@@ -753,15 +630,15 @@ struct SegmentLayout {
 
 SegmentLayout segment_layout(int n) {
     SegmentLayout L{};
-    const uint64_t cells = uint64_t(n) * n * n;
     const TileGrid rg = resolve_grid(n);
-    L.nbnd = int64_t(rg.ntx) * rg.nty * rg.ntz * NBND;
+    const uint64_t tiles = uint64_t(rg.ntx) * rg.nty * rg.ntz;
+    L.nbnd = int64_t(tiles) * NBND;
     L.launches = chase_launches(uint64_t(L.nbnd));
     size_t off = 0;
     L.flags = off;
     off = align_up(off + sizeof(uint32_t) * CHASE_FLAGS);
     L.ptr = off;
-    off = align_up(off + sizeof(int32_t) * cells);
+    off = align_up(off + sizeof(uint16_t) * RCELLS * tiles);
     L.bnd = off;
     off = align_up(off + sizeof(int32_t) * size_t(L.nbnd));
     L.total = off;
@@ -793,22 +670,28 @@ hf_status mask_to_list(hf_ctx *ctx, const MaximaLayout &L, char *w8, int32_t *ma
     return launch_status();
 }
 
-// Parents (and the maxima mask when given) of a tiled grid, with the chains
-// inside each resolve tile followed: ptr and bnd of the segmentation workspace.
+// Parents (and the maxima mask when given), with the chains inside each resolve
+// tile followed: ptr and bnd of the segmentation workspace.
 hf_status launch_parent_resolve(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, const float *cwt, float tau,
                                 uint32_t *mask) {
     const TileGrid tg = resolve_grid(n);
     const dim3 grid(tg.ntx * tg.nty * tg.ntz);
-    auto *ptr = reinterpret_cast<int32_t *>(w8 + L.ptr);
+    auto *ptr = reinterpret_cast<uint4 *>(w8 + L.ptr);
     auto *bnd = reinterpret_cast<int32_t *>(w8 + L.bnd);
     auto *flags = reinterpret_cast<uint32_t *>(w8 + L.flags);
     if (all_full(n))
-        HF_LAUNCH(ctx, K_PARENT, parent_resolve_kernel<true>, grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
+        HF_LAUNCH(ctx, K_PARENT, (parent_resolve_kernel<true, true>), grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
                   host_ordered_bits(tau), ptr, bnd, mask, flags, ctx->d_status);
     else
-        HF_LAUNCH(ctx, K_PARENT, parent_resolve_kernel<false>, grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
+        HF_LAUNCH(ctx, K_PARENT, (parent_resolve_kernel<false, true>), grid, dim3(PR_THREADS), 0, ctx->stream, cwt, tg,
                   host_ordered_bits(tau), ptr, bnd, mask, flags, ctx->d_status);
     return launch_status();
+}
+
+// Where rows straddle mask words the maxima are set bit by bit into a cleared mask.
+void clear_mask(hf_ctx *ctx, const MaximaLayout &L, int n, uint32_t *mask) {
+    if (!all_full(n))
+        HF_LAUNCH(ctx, K_FLAGS, zero_words_kernel, dim3(stride_grid(L.words)), dim3(256), 0, ctx->stream, mask, L.words);
 }
 
 // After launch_parent_resolve: the chains of the boundary entries, and the
@@ -816,7 +699,7 @@ hf_status launch_parent_resolve(hf_ctx *ctx, const SegmentLayout &L, char *w8, i
 hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, int32_t *cell_label) {
     const TileGrid tg = resolve_grid(n);
     auto *flags = reinterpret_cast<uint32_t *>(w8 + L.flags);
-    auto *ptr = reinterpret_cast<int32_t *>(w8 + L.ptr);
+    auto *ptr = reinterpret_cast<uint4 *>(w8 + L.ptr);
     auto *bnd = reinterpret_cast<int32_t *>(w8 + L.bnd);
     const bool full = all_full(n);
     const dim3 chase(stride_grid((L.nbnd + BATCH - 1) / BATCH));
@@ -830,10 +713,10 @@ hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, i
     }
     const dim3 grid(tg.ntx * tg.nty * tg.ntz);
     if (full)
-        HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<true>, grid, dim3(RES_THREADS), 0, ctx->stream, ptr, bnd, tg,
+        HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<true>, grid, dim3(PR_THREADS), 0, ctx->stream, ptr, bnd, tg,
                   cell_label);
     else
-        HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<false>, grid, dim3(RES_THREADS), 0, ctx->stream, ptr, bnd, tg,
+        HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<false>, grid, dim3(PR_THREADS), 0, ctx->stream, ptr, bnd, tg,
                   cell_label);
     return launch_status();
 }
@@ -859,9 +742,7 @@ hf_status hf::maxima_segment(hf_ctx *ctx, const hf_box &box, const float *cwt, f
     char *w8 = static_cast<char *>(ws);
     char *wm = w8 + SL.total;
     auto *mask = reinterpret_cast<uint32_t *>(wm + ML.mask);
-    if (n % 32 != 0)  // rows straddle mask words: the maxima are set bit by bit into a cleared mask
-        HF_LAUNCH(ctx, K_FLAGS, zero_words_kernel, dim3(stride_grid(ML.words)), dim3(256), 0, ctx->stream, mask,
-                  ML.words);
+    clear_mask(ctx, ML, n, mask);
     s = launch_parent_resolve(ctx, SL, w8, n, cwt, tau, mask);
     if (s != HF_OK) return s;
     s = mask_to_list(ctx, ML, wm, max_idx, max_cap, d_count);
@@ -882,15 +763,15 @@ extern "C" hf_status hf_maxima(hf_ctx *ctx, const hf_box *box, const float *cwt,
     char *w8 = static_cast<char *>(ws);
     auto *mask = reinterpret_cast<uint32_t *>(w8 + L.mask);
     const int n = box->n;
-    if (tiled(n)) {
-        const TileGrid tg = tile_grid(n);
-        HF_LAUNCH(ctx, K_MAX_MARK, max_tile_kernel, dim3(tg.ntx * tg.nty * tg.ntz), dim3(SEG_THREADS), 0,
-                  ctx->stream, cwt, tg, host_ordered_bits(tau), mask, ctx->d_status);
-    } else {
-        const int64_t cells = int64_t(n) * n * n;
-        HF_LAUNCH(ctx, K_MAX_MARK, max_direct_kernel, dim3(stride_grid(cells)), dim3(256), 0, ctx->stream, cwt, n,
-                  tau, mask, ctx->d_status);
-    }
+    const TileGrid tg = resolve_grid(n);
+    const dim3 grid(tg.ntx * tg.nty * tg.ntz);
+    clear_mask(ctx, L, n, mask);
+    if (all_full(n))
+        HF_LAUNCH(ctx, K_MAX_MARK, (parent_resolve_kernel<true, false>), grid, dim3(PR_THREADS), 0, ctx->stream, cwt,
+                  tg, host_ordered_bits(tau), nullptr, nullptr, mask, nullptr, ctx->d_status);
+    else
+        HF_LAUNCH(ctx, K_MAX_MARK, (parent_resolve_kernel<false, false>), grid, dim3(PR_THREADS), 0, ctx->stream, cwt,
+                  tg, host_ordered_bits(tau), nullptr, nullptr, mask, nullptr, ctx->d_status);
     return mask_to_list(ctx, L, w8, max_idx, max_cap, d_count);
 }
 

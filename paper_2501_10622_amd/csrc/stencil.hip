@@ -96,6 +96,7 @@ __device__ __forceinline__ int wrap(int t, int n) {
 // wrap with a fast path for the common in-range index
 __device__ __forceinline__ int wrapq(int t, int n) { return unsigned(t) < unsigned(n) ? t : wrap(t, n); }
 
+constexpr int X_BATCH = 8;     // loads of an x-pass row in flight per lane
 constexpr int LOAD_BATCH = 4;  // rows whose loads are issued together before any is used
 
 // Workgroup sum of the threads' 128-bit masses, in a fixed order, to *out.
@@ -123,12 +124,33 @@ __device__ __forceinline__ void block_mass(unsigned long long lo, unsigned long 
     }
 }
 
+// v[0 .. count) to out, which lies at a multiple of `align` floats: the widest
+// stores that allows, as neighbouring lanes' blocks are 32 bytes apart.
+__device__ __forceinline__ void store_block(float *out, const float (&v)[ST_K], int count, int align) {
+    if (align == 4 && count == ST_K) {
+#pragma unroll
+        for (int k = 0; k < ST_K; k += 4)
+            *reinterpret_cast<float4 *>(out + k) = make_float4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    } else if (align >= 2 && count == ST_K) {
+#pragma unroll
+        for (int k = 0; k < ST_K; k += 2) *reinterpret_cast<float2 *>(out + k) = make_float2(v[k], v[k + 1]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < ST_K; ++k)
+            if (k < count) out[k] = v[k];
+    }
+}
+
 // x pass: xrows whole rows per workgroup; row r of the grid (r = z n + y) is
 // read once with hp cells of periodic halo on either side into a row buffer
 // (xrow_blocks).  Each thread then makes the ST_K outputs of one block of a
 // row from two register windows that move one slot per tap, as the y and z
 // passes do (taps past h weigh 0), and every output adds its taps in the
 // order of a plain loop over d.
+//
+// Bound by HBM (8 bytes read, 8 written per cell).  With a division by the row's
+// slots per slot and single-float stores, 138 vector instructions per cell: 274 us
+// at n = 350, h = 8, where this takes 157 (4.4 TB/s).
 __global__ void __launch_bounds__(ST_THREADS)
     stencil_x_kernel(const int64_t *__restrict__ rho, float *__restrict__ fa, float *__restrict__ fb,
                      Mass128 *__restrict__ mass, int n, int h, int xrows, double wdx, uint32_t *status) {
@@ -146,29 +168,28 @@ __global__ void __launch_bounds__(ST_THREADS)
     for (int d = h + 1 + tid; d <= hp; d += ST_THREADS) wa[d] = wb[d] = 0.0f;
     unsigned long long lo = 0, hi = 0;
     bool neg = false;
-    // the rows' slots as one run of rows * W, LOAD_BATCH loads in flight per thread
-    const int slots = rows * W;
-    for (int s0 = tid; s0 < slots; s0 += ST_THREADS * LOAD_BATCH) {
-        int64_t v[LOAD_BATCH];
+    // a wavefront stages whole rows, X_BATCH loads in flight per lane: slot q = lane
+    // + 64 i keeps its place in its block, and lies 8 i blocks on
+    static_assert(ST_K == 8, "64 slots are 8 blocks");
+    const int lane = tid & 63;
+    for (int r = tid >> 6; r < rows; r += ST_THREADS / 64) {
+        const int64_t *__restrict__ src = rho + (row0 + r) * n;
+        float *dst = buf + r * RF + (lane % ST_K) * LB + lane / ST_K + 1;
+        for (int i0 = 0; i0 * 64 < W; i0 += X_BATCH) {
+            int64_t v[X_BATCH];
+            bool own[X_BATCH];  // each cell counted once, from its own slot
 #pragma unroll
-        for (int u = 0; u < LOAD_BATCH; ++u) {
-            const int sl = s0 + u * ST_THREADS;
-            v[u] = 0;
-            if (sl < slots) {
-                const int r = sl / W, q = sl - r * W;
-                v[u] = rho[(row0 + r) * n + wrapq(q - hp, n)];
+            for (int u = 0; u < X_BATCH; ++u) {
+                const int q = lane + 64 * (i0 + u), x = q - hp;
+                own[u] = unsigned(x) < unsigned(n);
+                v[u] = 0;
+                if (q < W) v[u] = src[wrapq(x, n)];
             }
-        }
 #pragma unroll
-        for (int u = 0; u < LOAD_BATCH; ++u) {
-            const int sl = s0 + u * ST_THREADS;
-            if (sl < slots) {
-                const int r = sl / W, q = sl - r * W;
-                if (q >= hp && q < hp + n) {  // each cell counted once, from its own slot
-                    neg |= v[u] < 0;
-                    add128(lo, hi, static_cast<unsigned long long>(v[u]));
-                }
-                buf[r * RF + (q % ST_K) * LB + q / ST_K + 1] = float(v[u]);
+            for (int u = 0; u < X_BATCH; ++u) {
+                neg |= v[u] < 0;
+                add128(lo, hi, own[u] ? static_cast<unsigned long long>(v[u]) : 0ull);
+                if (lane + 64 * (i0 + u) < W) dst[8 * (i0 + u)] = float(v[u]);
             }
         }
     }
@@ -176,6 +197,10 @@ __global__ void __launch_bounds__(ST_THREADS)
     block_mass(lo, hi, mass + blockIdx.x);  // its barrier also publishes the row buffers
     const float a0 = wa[0];
     const int lanes = (n + ST_K - 1) / ST_K;
+    // floats that every block's start is aligned to: blocks start at multiples of
+    // ST_K in rows of n, and the caller's field may lie at any float
+    const uint64_t bits = reinterpret_cast<uint64_t>(fa) | reinterpret_cast<uint64_t>(fb) | uint64_t(n) * sizeof(float);
+    const int align = bits % 16 == 0 ? 4 : (bits % 8 == 0 ? 2 : 1);
     for (int w = tid; w < rows * lanes; w += ST_THREADS) {
         const int r = w / lanes, l = w - r * lanes;
         // slot qb + j (qb = ST_K l + hp, j >= -ST_K) at ((j + ST_K) mod ST_K) LB + qk + (j + ST_K) / ST_K
@@ -214,15 +239,10 @@ __global__ void __launch_bounds__(ST_THREADS)
                 }
             }
         }
-        float *oa = fa + (row0 + r) * n, *ob = fb + (row0 + r) * n;
-#pragma unroll
-        for (int k = 0; k < ST_K; ++k) {
-            const int x = ST_K * l + k;
-            if (x < n) {
-                oa[x] = sa[k];
-                ob[x] = sb[k];
-            }
-        }
+        const int64_t at = (row0 + r) * n + ST_K * l;
+        const int count = n - ST_K * l < ST_K ? n - ST_K * l : ST_K;
+        store_block(fa + at, sa, count, align);
+        store_block(fb + at, sb, count, align);
     }
 }
 

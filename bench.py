@@ -48,8 +48,9 @@ TIMER_SYMBOLS = {
     "parent": ("parent_resolve_kernel",), "jump_flags": ("zero_words_kernel",),
     "jump": ("bnd_chase_kernel",), "finalize": ("seg_finalize_kernel",),
     "label_tiles": ("tile_label_kernel",), "label_level1": ("to_level1_kernel",), "label_input": ("to_input_kernel",),
-    "groups_clear": ("groups_clear_kernel",), "groups_cells": ("groups_runs_kernel<false>", "groups_tally_kernel<false>"),
-    "groups_particles": ("groups_particles_kernel", "groups_runs_kernel<true>", "groups_tally_kernel<true>"), "groups_decide": ("groups_decide_kernel",),
+    "groups_clear": ("groups_clear_kernel",), "groups_cells": ("groups_cells_kernel",),
+    "groups_particles": ("groups_particles_kernel", "groups_runs_kernel<false>", "groups_tally_kernel<false>",
+                         "groups_runs_kernel<true>", "groups_tally_kernel<true>"), "groups_decide": ("groups_decide_kernel",),
     "groups_filter": ("groups_filter_kernel",),
     "stencil_x": ("stencil_x_kernel",), "stencil_mass": ("stencil_mass_kernel",),
     "stencil_y": ("stencil_axis_kernel<false>",), "stencil_z": ("stencil_axis_kernel<true>",),

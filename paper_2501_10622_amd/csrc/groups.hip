@@ -36,13 +36,68 @@ __global__ void __launch_bounds__(GB) groups_clear_kernel(const int32_t *__restr
     if (bad) atomicOr(status, ST_INPUT);
 }
 
+constexpr int CELL_HT = 1024;  // entries of the LDS tables below
+
 // Step 5: the grid volume of every group, in cells.  One workgroup counts a
-// contiguous range of GCHUNK cells (a few grid rows, a few hundred labels) in
-// an LDS table and adds it to the counters once.  With MASKED the same count
-// runs over `count` labels of particles in the deposit's tile order (spatially
-// coherent, like cells), skipping those whose mask byte is nonzero.
+// CX x CY x CZ tile of cells in an LDS table and adds it to the counters once.  Each
+// run of equal labels of a row is counted by its first lane.  A compact tile meets
+// few groups: with 16384 consecutive cells per workgroup (47 rows at n = 350, more
+// groups than the table holds at scales of 2 to 3 cells) most adds went past the
+// table to memory: 576 us at 350^3 where this takes 127, 56 -> 32 us at 256^3, and 90
+// -> 86 at 384^3.  What is left is the loads of a tile, most of a short
+// workgroup's life (16 rows of planes each; tiles of 64 x 8 x 16 took 1.5 times as
+// long).
+constexpr int CX = 32, CY = 8, CZ = 16;
+
+__global__ void __launch_bounds__(CX *CY) groups_cells_kernel(const int32_t *__restrict__ label, int n, int ntx,
+                                                              int nty, uint32_t *__restrict__ cells,
+                                                              uint32_t *status) {
+    __shared__ int32_t hkey[CELL_HT];
+    __shared__ uint32_t hcnt[CELL_HT];
+    lds_tally_init<CELL_HT>(hkey, hcnt);
+    const uint32_t tile = blockIdx.x, row = tile / uint32_t(ntx);
+    const int x = int(tile % uint32_t(ntx)) * CX + int(threadIdx.x) % CX;
+    const int y = int(row % uint32_t(nty)) * CY + int(threadIdx.x) / CX, z0 = int(row / uint32_t(nty)) * CZ;
+    const uint32_t un = uint32_t(n), ncells = un * un * un, g = (uint32_t(z0) * un + uint32_t(y)) * un + uint32_t(x);
+    const bool there = x < n && y < n;
+    int32_t v[CZ];
+#pragma unroll
+    for (int k = 0; k < CZ; ++k) v[k] = there && z0 + k < n ? label[g + uint32_t(k) * un * un] : -1;
+    __syncthreads();
+    bool bad = false;
+    const int lane = int(threadIdx.x) & 63;
+    int32_t held = -1;  // a lane's runs of one label, plane after plane, are added together
+    uint32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < CZ; ++k) {  // a wavefront holds two rows: the first lane of each run counts it
+        int32_t l = v[k];
+        if (l < -1 || (l >= 0 && uint32_t(l) >= ncells)) {
+            bad = true;
+            l = -1;
+        }
+        const bool head = lane % CX == 0 || l != __shfl_up(l, 1, 64);
+        const unsigned long long after = __ballot(head) >> lane >> 1;
+        const uint32_t len = after ? uint32_t(__ffsll((long long)after)) : uint32_t(64 - lane);
+        if (head && l >= 0) {
+            if (l != held) {
+                if (held >= 0) lds_tally_add<CELL_HT>(hkey, hcnt, cells, held, sum);
+                held = l;
+                sum = 0;
+            }
+            sum += len;
+        }
+    }
+    if (held >= 0) lds_tally_add<CELL_HT>(hkey, hcnt, cells, held, sum);
+    __syncthreads();
+    lds_tally_flush<CELL_HT>(hkey, hcnt, cells);
+    if (bad) atomicOr(status, ST_INPUT);
+}
+
+// Step 6 groups from labels in the deposit's tile order, where neighbours share
+// groups as cells do.  One workgroup counts GCHUNK labels in an LDS table and adds
+// it to the counters once; with MASKED, labels whose mask byte is nonzero are
+// skipped.
 constexpr int GCHUNK = 16384;
-constexpr int CELL_HT = 1024;
 
 template <bool MASKED>
 __global__ void __launch_bounds__(GB) groups_tally_kernel(const int32_t *__restrict__ label,
@@ -78,17 +133,14 @@ __global__ void __launch_bounds__(GB) groups_tally_kernel(const int32_t *__restr
     if (bad) atomicOr(status, ST_INPUT);
 }
 
-// Step 5 by runs: each thread takes CELL_RUN consecutive cells of a row (one
-// vector load per four) and adds each run of equal labels to the LDS table
-// once, so a basin a few cells wide costs one insert per run instead of one
-// per cell.  With MASKED, the same over particle labels in the deposit's tile
-// order, skipping those whose mask byte is nonzero.  Both arrays 16-byte
-// aligned.
+// The same by runs: each thread takes CELL_RUN consecutive labels (one vector
+// load per four) and adds each run of equal labels to the LDS table once, so a run
+// costs one insert instead of one per label.  Both arrays 16-byte aligned.
 constexpr int CELL_RUN = 16;
 static_assert(CELL_RUN == 16, "one 16-byte load of mask bytes per run of labels");
 
 template <bool MASKED>
-__global__ void __launch_bounds__(GB) groups_runs_kernel(const int32_t *__restrict__ cell_label,
+__global__ void __launch_bounds__(GB) groups_runs_kernel(const int32_t *__restrict__ label,
                                                          const uint8_t *__restrict__ mask, int64_t count,
                                                          int64_t ncells, uint32_t *__restrict__ cells,
                                                          uint32_t *status) {
@@ -102,7 +154,7 @@ __global__ void __launch_bounds__(GB) groups_runs_kernel(const int32_t *__restri
     for (int64_t b = c0 + int64_t(threadIdx.x) * CELL_RUN; b < c1; b += int64_t(GB) * CELL_RUN) {
         int32_t v[CELL_RUN];
         if (b + CELL_RUN <= c1) {
-            const int4 *p = reinterpret_cast<const int4 *>(cell_label + b);
+            const int4 *p = reinterpret_cast<const int4 *>(label + b);
             uint32_t mw[CELL_RUN / 4] = {};  // the CELL_RUN mask bytes, four per word
             if (MASKED) {
                 const uint4 m = *reinterpret_cast<const uint4 *>(mask + b);
@@ -127,7 +179,7 @@ __global__ void __launch_bounds__(GB) groups_runs_kernel(const int32_t *__restri
         } else {
 #pragma unroll
             for (int q = 0; q < CELL_RUN; ++q) {
-                v[q] = b + q < c1 ? cell_label[b + q] : -1;
+                v[q] = b + q < c1 ? label[b + q] : -1;
                 if (MASKED && b + q < c1 && mask[b + q]) v[q] = -1;
             }
         }
@@ -753,13 +805,9 @@ hf_status hf::groups_count_cells(hf_ctx *ctx, const hf_box &box, const int32_t *
     if (cap <= 0) return HF_OK;
     HF_LAUNCH(ctx, K_GROUP_CLEAR, groups_clear_kernel, dim3(grid_of(ctx, cap, GB)), dim3(GB), 0, ctx->stream, roots,
               d_count, cap, ncells, g, ctx->d_status);
-    const dim3 grid(unsigned((ncells + GCHUNK - 1) / GCHUNK));
-    if (reinterpret_cast<uintptr_t>(cell_label) % sizeof(int4) == 0)
-        HF_LAUNCH(ctx, K_GROUP_CELLS, groups_runs_kernel<false>, grid, dim3(GB), 0, ctx->stream, cell_label, nullptr,
-                  ncells, ncells, g.cells, ctx->d_status);
-    else  // rows not 16-byte aligned: one label per lane
-        HF_LAUNCH(ctx, K_GROUP_CELLS, groups_tally_kernel<false>, grid, dim3(GB), 0, ctx->stream, cell_label, nullptr,
-                  ncells, ncells, g.cells, ctx->d_status);
+    const int n = box.n, ntx = (n + CX - 1) / CX, nty = (n + CY - 1) / CY, ntz = (n + CZ - 1) / CZ;
+    HF_LAUNCH(ctx, K_GROUP_CELLS, groups_cells_kernel, dim3(unsigned(ntx * nty * ntz)), dim3(CX * CY), 0, ctx->stream,
+              cell_label, n, ntx, nty, g.cells, ctx->d_status);
     return launch_status();
 }
 

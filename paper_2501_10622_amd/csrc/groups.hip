@@ -491,7 +491,8 @@ constexpr int GP_THREADS = 1024;
 constexpr int GP_PER = 8;
 constexpr int GP_CHUNK = GP_THREADS * GP_PER;  // labels per scatter workgroup
 constexpr int GP_HCHUNK = 8 * GP_CHUNK;        // labels per histogram workgroup
-constexpr int GP_CCHUNK = 32 * GP_CHUNK;       // partitioned labels per counting workgroup (few flushes per root)
+constexpr int GP_CCHUNK = 32 * GP_CHUNK;       // most partitioned labels per counting workgroup (few flushes per root)
+constexpr int64_t GP_MIN = 1 << 20;            // particles from which the partition is faster than atomics
 constexpr int GP_HT = 8192;                    // LDS tally slots of the counting pass
 
 struct GroupPart {
@@ -517,7 +518,9 @@ __device__ __forceinline__ bool gp_label_ok(int32_t l, int64_t ncells, bool &bad
     return l >= 0;
 }
 
-__global__ void __launch_bounds__(512) gp_hist_kernel(const int32_t *__restrict__ label, int64_t np, int64_t ncells,
+// (with skip, labels of particles whose skip entry is >= 0 are left out here and in the scatter)
+__global__ void __launch_bounds__(512) gp_hist_kernel(const int32_t *__restrict__ label,
+                                                      const int32_t *__restrict__ skip, int64_t np, int64_t ncells,
                                                       int shift, uint32_t *__restrict__ count, uint32_t *status) {
     __shared__ uint32_t h[GP_BUCKETS];
     for (int b = threadIdx.x; b < GP_BUCKETS; b += blockDim.x) h[b] = 0u;
@@ -531,6 +534,7 @@ __global__ void __launch_bounds__(512) gp_hist_kernel(const int32_t *__restrict_
         for (int k = 0; k < 8; ++k) {
             const int64_t i = i0 + int64_t(k) * blockDim.x;
             l[k] = i < c1 ? label[i] : -1;
+            if (skip && i < c1 && skip[i] >= 0) l[k] = -1;
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k)
@@ -565,7 +569,8 @@ __global__ void __launch_bounds__(GP_BUCKETS) gp_scan_kernel(uint32_t *__restric
     if (t == 0) count[GP_BUCKETS] = all;
 }
 
-__global__ void __launch_bounds__(GP_THREADS) gp_scatter_kernel(const int32_t *__restrict__ label, int64_t np,
+__global__ void __launch_bounds__(GP_THREADS) gp_scatter_kernel(const int32_t *__restrict__ label,
+                                                                const int32_t *__restrict__ skip, int64_t np,
                                                                 int64_t ncells, int shift, uint32_t *cursor,
                                                                 int32_t *__restrict__ sorted) {
     __shared__ int32_t stage[GP_CHUNK];
@@ -581,6 +586,7 @@ __global__ void __launch_bounds__(GP_THREADS) gp_scatter_kernel(const int32_t *_
     for (int k = 0; k < GP_PER; ++k) {
         const int64_t i = c0 + int64_t(k) * GP_THREADS + t;
         l[k] = i < np ? label[i] : -1;
+        if (skip && i < np && skip[i] >= 0) l[k] = -1;
         if (!gp_label_ok(l[k], ncells, bad)) l[k] = -1;
     }
 #pragma unroll
@@ -619,18 +625,22 @@ __global__ void __launch_bounds__(GP_THREADS) gp_scatter_kernel(const int32_t *_
     }
 }
 
+// A workgroup counts `chunk` partitioned labels.  Bound by the table's adds, each
+// label's own (neighbours in a bucket rarely share a group: merging them first cost
+// 50% more).  At GP_CCHUNK labels each, 13 million labels were 50 workgroups for 256
+// CUs: 142 us, 35 with two per CU.
 __global__ void __launch_bounds__(GP_THREADS) gp_count_kernel(const int32_t *__restrict__ sorted,
-                                                              const uint32_t *__restrict__ count,
+                                                              const uint32_t *__restrict__ count, int64_t chunk,
                                                               uint32_t *__restrict__ parts) {
     __shared__ int32_t hkey[GP_HT];
     __shared__ uint32_t hcnt[GP_HT];
     const uint32_t total = count[GP_BUCKETS];
-    const int64_t c0 = int64_t(blockIdx.x) * GP_CCHUNK;
+    const int64_t c0 = int64_t(blockIdx.x) * chunk;
     if (c0 >= int64_t(total)) return;  // the same for the whole workgroup
     lds_tally_init<GP_HT>(hkey, hcnt);
     __syncthreads();
-    const int64_t c1 = c0 + GP_CCHUNK < int64_t(total) ? c0 + GP_CCHUNK : int64_t(total);
-    for (int64_t b0 = c0; b0 < c1; b0 += int64_t(GP_THREADS) * 8) {  // the same trip count on every lane
+    const int64_t c1 = c0 + chunk < int64_t(total) ? c0 + chunk : int64_t(total);
+    for (int64_t b0 = c0; b0 < c1; b0 += int64_t(GP_THREADS) * 8) {
         int32_t l[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -638,7 +648,8 @@ __global__ void __launch_bounds__(GP_THREADS) gp_count_kernel(const int32_t *__r
             l[k] = i < c1 ? sorted[i] : -1;
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) lds_tally_wave<GP_HT>(hkey, hcnt, parts, l[k]);
+        for (int k = 0; k < 8; ++k)
+            if (l[k] >= 0) lds_tally_add<GP_HT>(hkey, hcnt, parts, l[k], 1u);
     }
     __syncthreads();
     lds_tally_flush<GP_HT>(hkey, hcnt, parts);
@@ -785,6 +796,22 @@ size_t part_layout(const hf_box &box, int64_t np, size_t base, void *ws, GroupPa
     return off - base;
 }
 
+// The particles' counts by partition: hist, scan, scatter, count (gp.count cleared before).
+hf_status part_count(hf_ctx *ctx, const int32_t *label, const int32_t *skip, int64_t np, int64_t ncells,
+                     const GroupPart &gp, uint32_t *parts) {
+    hipStream_t st = ctx->stream;
+    HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_hist_kernel, dim3(unsigned((np + GP_HCHUNK - 1) / GP_HCHUNK)), dim3(512), 0, st,
+              label, skip, np, ncells, gp.shift, gp.count, ctx->d_status);
+    HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_scan_kernel, dim3(1), dim3(GP_BUCKETS), 0, st, gp.count, gp.cursor);
+    HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_scatter_kernel, dim3(unsigned((np + GP_CHUNK - 1) / GP_CHUNK)),
+              dim3(GP_THREADS), 0, st, label, skip, np, ncells, gp.shift, gp.cursor, gp.sorted);
+    const int64_t share = (np + 2 * int64_t(ctx->cus) - 1) / (2 * int64_t(ctx->cus));
+    const int64_t whole = (share + GP_CHUNK - 1) / GP_CHUNK * GP_CHUNK, chunk = whole < GP_CCHUNK ? whole : GP_CCHUNK;
+    HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_count_kernel, dim3(unsigned((np + chunk - 1) / chunk)), dim3(GP_THREADS), 0,
+              st, gp.sorted, gp.count, chunk, parts);
+    return launch_status();
+}
+
 }  // namespace
 
 size_t hf::groups_part_ws_bytes(const hf_box &box, int64_t np) {
@@ -833,8 +860,18 @@ hf_status hf::groups_count_particles_tiled(hf_ctx *ctx, const hf_box &box, const
 }
 
 hf_status hf::groups_count_particles(hf_ctx *ctx, const hf_box &box, const int32_t *particle_label, int64_t np,
-                                     const GroupCounters &g, const int32_t *skip) {
+                                     const GroupCounters &g, const int32_t *skip, void *scratch,
+                                     size_t scratch_bytes) {
     if (np <= 0) return HF_OK;
+    // five launches against one: the atomics take 42 us per million particles, the
+    // partition 18 and about 20 us
+    if (np >= GP_MIN && scratch && scratch_bytes >= groups_part_ws_bytes(box, np)) {
+        GroupPart gp{};
+        part_layout(box, np, 0, scratch, &gp);
+        HF_LAUNCH(ctx, K_GROUP_CLEAR, gp_zero_kernel, dim3(1), dim3(GB), 0, ctx->stream, gp.count,
+                  int64_t(GP_BUCKETS + 1));
+        return part_count(ctx, particle_label, skip, np, cells_of(box), gp, g.parts);
+    }
     HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_particles_kernel, dim3(grid_of(ctx, np, GB * GPER)), dim3(GB), 0,
               ctx->stream, particle_label, skip, np, cells_of(box), g.parts, ctx->d_status);
     return launch_status();
@@ -948,15 +985,7 @@ extern "C" hf_status hf_groups(hf_ctx *ctx, const hf_box *box, int64_t np, const
     if (nroots > 0) {
         s = groups_count_cells(ctx, *box, roots, nullptr, nroots, cell_label, g);
         if (s == HF_OK && part && np > 0) {
-            HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_hist_kernel, dim3(unsigned((np + GP_HCHUNK - 1) / GP_HCHUNK)),
-                      dim3(512), 0, st, particle_label, np, ncells, gp.shift, gp.count, ctx->d_status);
-            HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_scan_kernel, dim3(1), dim3(GP_BUCKETS), 0, st, gp.count, gp.cursor);
-            const dim3 chunks(unsigned((np + GP_CHUNK - 1) / GP_CHUNK));
-            HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_scatter_kernel, chunks, dim3(GP_THREADS), 0, st, particle_label, np,
-                      ncells, gp.shift, gp.cursor, gp.sorted);
-            HF_LAUNCH(ctx, K_GROUP_PARTICLES, gp_count_kernel, dim3(unsigned((np + GP_CCHUNK - 1) / GP_CCHUNK)),
-                      dim3(GP_THREADS), 0, st, gp.sorted, gp.count, g.parts);
-            s = launch_status();
+            s = part_count(ctx, particle_label, nullptr, np, ncells, gp, g.parts);
         } else if (s == HF_OK) {
             s = groups_count_particles(ctx, *box, particle_label, np, g);
         }

@@ -191,9 +191,12 @@ GroupCounters group_counters_at(const hf_box &box, void *region);
 // null) and counts every group's cells.
 hf_status groups_count_cells(hf_ctx *ctx, const hf_box &box, const int32_t *roots, const int64_t *d_count,
                              int64_t cap, const int32_t *cell_label, const GroupCounters &g);
-// Counts particle labels in input order (one atomic per labelled particle).
+// Counts particle labels in input order: partitioned first where the scratch has
+// groups_part_ws_bytes, else one atomic per labelled particle.  Particles whose skip
+// entry is >= 0 are left out.
 hf_status groups_count_particles(hf_ctx *ctx, const hf_box &box, const int32_t *particle_label, int64_t np,
-                                 const GroupCounters &g, const int32_t *skip = nullptr);
+                                 const GroupCounters &g, const int32_t *skip = nullptr, void *scratch = nullptr,
+                                 size_t scratch_bytes = 0);
 // The same count over labels in the deposit's tile order (LDS tables; entries
 // whose mask byte is nonzero skipped; mask may be null).
 hf_status groups_count_particles_tiled(hf_ctx *ctx, const hf_box &box, const int32_t *label, const uint8_t *mask,

@@ -111,7 +111,9 @@ extern "C" hf_status hf_find_halos_filtered(hf_ctx *ctx, const hf_box *box, cons
         g = group_counters_at(*box, sw);
         s = hf_label(ctx, box, job->pos, job->dtype, job->np, job->cell_label, job->particle_label);
         if (s == HF_OK) s = groups_count_cells(ctx, *box, job->max_idx, job->d_count, cap, job->cell_label, g);
-        if (s == HF_OK && cap > 0) s = groups_count_particles(ctx, *box, job->particle_label, job->np, g);
+        if (s == HF_OK && cap > 0)
+            s = groups_count_particles(ctx, *box, job->particle_label, job->np, g, nullptr, sw + groups_ws_bytes(*box),
+                                       sb - groups_ws_bytes(*box));
         if (s == HF_OK)
             s = groups_decide(ctx, *box, job->max_idx, job->d_count, cap, g, gf->dens_th, job->np, gf->particle_th,
                               nullptr, gf->group_particles, gf->group_cells, gf->group_keep);
@@ -309,7 +311,7 @@ extern "C" hf_status hf_identify(hf_ctx *ctx, const hf_box *box, const void *pos
         // particles already claimed are not counted
         if (s == HF_OK && sj.max_cap > 0)
             s = order ? groups_count_particles_tiled(ctx, *box, lab, j > 0 ? cs8 : nullptr, np, g)
-                      : groups_count_particles(ctx, *box, lab, np, g, halo_scale);
+                      : groups_count_particles(ctx, *box, lab, np, g, halo_scale, sw, sb);
         if (s == HF_OK)
             s = groups_decide(ctx, *box, sj.max_idx, sj.d_count, sj.max_cap, g, dens_th, np, particle_th, pass,
                               gj.group_particles, gj.group_cells, gj.group_keep);
@@ -429,7 +431,8 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
                             last ? nullptr : scales[j + 1].cwt, pass);
         if (s == HF_OK) s = hf_label(ctx, &b, pos, dtype, np, sj.cell_label, sj.particle_label);
         if (s == HF_OK) s = groups_count_cells(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, sj.cell_label, g);
-        if (s == HF_OK && sj.max_cap > 0) s = groups_count_particles(ctx, b, sj.particle_label, np, g, halo_scale);
+        if (s == HF_OK && sj.max_cap > 0) s = 
+            s = groups_count_particles(ctx, b, sj.particle_label, np, g, halo_scale, w0, sb);  // the stage region is free
         if (s == HF_OK)
             s = groups_decide(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, g, dens_th, np, particle_th, pass,
                               sj.group_particles, sj.group_cells, sj.group_keep);

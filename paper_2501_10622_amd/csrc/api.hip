@@ -189,6 +189,10 @@ extern "C" hf_status hf_sync(hf_ctx *ctx) {
 }
 
 extern "C" hf_status hf_workspace_size(const hf_box *box, int64_t np, int stage_mask, size_t *bytes) {
+    return stage_ws_size(box, np, stage_mask, false, bytes);
+}
+
+hf_status hf::stage_ws_size(const hf_box *box, int64_t np, int stage_mask, bool least, size_t *bytes) {
     if (!bytes || np < 0) return HF_ERR_ARG;
     hf_status s = (stage_mask & HF_STAGE_CWT) ? check_box(box) : check_box_grid(box);
     if (s != HF_OK) return s;
@@ -199,7 +203,10 @@ extern "C" hf_status hf_workspace_size(const hf_box *box, int64_t np, int stage_
                        particle_order_supported(*box, np);
     size_t need = 0;
     auto take = [&need](size_t b) { need = need > b ? need : b; };
-    if (stage_mask & HF_STAGE_DEPOSIT) take(order ? deposit_tiled_ws_bytes(*box, np, true) : deposit_ws_bytes(*box, np));
+    // (the buffer sets of a group, whose transform has a workspace of its own, keep to the least)
+    const bool own = stage_mask == HF_STAGE_DEPOSIT || (stage_mask & (HF_STAGE_CWT | HF_STAGE_STENCIL));
+    if (stage_mask & HF_STAGE_DEPOSIT)
+        take(order ? deposit_tiled_ws_bytes(*box, np, true) : deposit_ws_bytes(*box, np, least || !own));
     if (stage_mask & HF_STAGE_CWT) take(cwt_ws_bytes(*box));
     if (stage_mask & HF_STAGE_STENCIL) take(stencil_ws_bytes(*box));
     if (stage_mask & HF_STAGE_MAXIMA) take(maxima_ws_bytes(*box));
@@ -222,7 +229,7 @@ extern "C" hf_status hf_find_halos_noalloc(hf_ctx *ctx, const hf_box *box, const
     hf_status s = check_box_for(box, job->kernel);
     if (s != HF_OK) return s;
     size_t need = 0;
-    s = hf_workspace_size(box, job->np, pipeline_stages(job->kernel), &need);
+    s = stage_ws_size(box, job->np, pipeline_stages(job->kernel), true, &need);
     if (s != HF_OK) return s;
     if (need > HF_NOALLOC_SCRATCH_BYTES) return HF_ERR_WORKSPACE;
     if (!ctx->scratch) return HF_ERR_DEVICE;

@@ -122,7 +122,8 @@ int grid_for(int64_t work, int block, int cap) {
 
 }  // namespace
 
-size_t hf::deposit_ws_bytes(const hf_box &box, int64_t np) {
+size_t hf::deposit_ws_bytes(const hf_box &box, int64_t np, bool least) {
+    if (least && deposit_ws_optional(box)) return 0;
     return deposit_tiled_supported(box, np) ? deposit_tiled_ws_bytes(box, np) : 0;
 }
 
@@ -132,11 +133,12 @@ extern "C" hf_status hf_deposit(hf_ctx *ctx, const hf_box *box, const void *pos,
     if (dtype != HF_F32 && dtype != HF_F64) return HF_ERR_ARG;
     hf_status s = check_box_grid(box);
     if (s != HF_OK) return s;
-    s = check_ws(ws, ws_bytes, deposit_ws_bytes(*box, np));
+    s = check_ws(ws, ws_bytes, deposit_ws_bytes(*box, np, true));
     if (s != HF_OK) return s;
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
-    if (deposit_tiled_supported(*box, np)) return deposit_tiled(ctx, *box, pos, dtype, np, rho, ws);
-    // direct form for grids the binned path does not cover: zero, then global atomics
+    if (deposit_tiled_supported(*box, np) && check_ws(ws, ws_bytes, deposit_ws_bytes(*box, np)) == HF_OK)
+        return deposit_tiled(ctx, *box, pos, dtype, np, rho, ws);
+    // direct form for what the binned path does not cover: zero, then global atomics
     const size_t cells = size_t(box->n) * box->n * box->n;
     auto *grid = reinterpret_cast<unsigned long long *>(rho);
     HF_LAUNCH(ctx, K_ZERO_GRID, fill_u64_kernel, dim3(grid_for(int64_t(cells), 256, 8192)), dim3(256), 0, ctx->stream, grid,

@@ -1100,13 +1100,15 @@ __global__ void __launch_bounds__(PART_THREADS) to_input_kernel(RunMaps m1, int6
 }
 
 // ---------------------------------------------------------------- host side
+int tile_tx(int n) { return n % 64 == 0 ? 64 : (n % 32 == 0 ? 32 : 16); }
+
 // Tile and bucket shape for an n^3 grid; false if the binned form cannot hold it
 // (at most MAX_DIGITS tiles per bucket and MAX_DIGITS buckets).
 bool make_geom(const hf_box &box, Geom &out) {
     Geom g{};
     g.n = box.n;
     g.bits = box.frac_bits;
-    g.tx = box.n % 64 == 0 ? 64 : (box.n % 32 == 0 ? 32 : 16);
+    g.tx = tile_tx(box.n);
     g.ltx = g.tx == 64 ? 6 : (g.tx == 32 ? 5 : 4);
     if (box.n % g.tx != 0 || box.n % TYZ != 0) return false;
     g.ntx = box.n / g.tx;
@@ -1172,12 +1174,48 @@ struct DepLayout {
         rec2, skirt, pad, total;
 };
 
-// Grid the binned form runs on for an n^3 box: n itself when its tiles fit
-// (n a multiple of 16), else the next multiple of 16 above n.  On the larger
-// grid the particles (cells 0..n-1) fill the low corner, their upper CIC
+// Grid the binned form runs on for an n^3 box: the first multiple of 16 from n
+// on (from n + 1 on where n is none) whose tiles fit into buckets; 1024 does.  On a
+// larger grid the particles (cells 0..n-1) fill the low corner, their upper CIC
 // corners reach cell n at most, and a last pass folds the planes at n onto
 // the planes at 0 along each axis and keeps the n^3 cells.
-int padded_n(int n) { return n % 16 == 0 ? n : (n + 1 + 15) / 16 * 16; }
+int first_n(int n) { return n % 16 == 0 ? n : (n + 1 + 15) / 16 * 16; }
+
+// Whether make_geom finds buckets for an n^3 grid (n a multiple of 16): a share of
+// MAX_DIGITS tiles at most, whole numbers of them along each axis, in MAX_DIGITS
+// buckets at most.
+bool fits(int n) {
+    const int ntx = n / tile_tx(n), nt = n / TYZ;
+    const long tiles = long(ntx) * nt * nt;
+    if (tiles > long(MAX_DIGITS) * MAX_DIGITS) return false;
+    int dx[64], d[128], nx = 0, nd = 0;  // divisors of ntx <= 64 and nt <= 128
+    for (int b = 1; b <= ntx; ++b)
+        if (ntx % b == 0) dx[nx++] = b;
+    for (int b = 1; b <= nt; ++b)
+        if (nt % b == 0) d[nd++] = b;
+    for (int i = 0; i < nx; ++i)
+        for (int j = 0; j < nd; ++j)
+            for (int k = 0; k <= j; ++k) {
+                const long share = long(dx[i]) * d[j] * d[k];
+                if (share <= MAX_DIGITS && tiles / share <= MAX_DIGITS) return true;
+            }
+    return false;
+}
+
+int padded_n(int n) {
+    int m = first_n(n);
+    while (!fits(m)) m += 16;
+    return m;
+}
+
+// Sizes whose first multiple of 16 has no buckets (a prime factor above 22 in its
+// tiles per axis, or too many tiles: 353-368, 449-464, 481-496 and 272 sizes from
+// 577 on).  They need the wider grid in the workspace where the direct form needs
+// nothing, so it is asked for but not insisted on, and it pays from n^3 / 32
+// particles on: 486^3 with 2 particles per cell 81 ms of atomics against 5.5 on
+// 512^3, with 0.6 per cell 24.3 against 2.3; with 1/64 per cell 0.8 against 1.0, most of
+// it the wider grid's writes and the fold.
+bool widened(const hf_box &box) { return padded_n(box.n) != first_n(box.n); }
 
 hf_box padded_box(const hf_box &box) {
     hf_box b = box;
@@ -1385,9 +1423,11 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
 bool hf::deposit_tiled_supported(const hf_box &box, int64_t np) {
     // packed tile records hold 12 + 3B <= 63 bits; counts are uint32
     if (box.frac_bits > 17 || np >= (int64_t(1) << 32)) return false;
-    Geom g;
-    return make_geom(padded_box(box), g);
+    if (widened(box) && np < int64_t(box.n) * box.n * box.n / 32) return false;
+    return true;
 }
+
+bool hf::deposit_ws_optional(const hf_box &box) { return widened(box); }
 
 size_t hf::deposit_tiled_ws_bytes(const hf_box &box, int64_t np, bool keep_order) {
     Geom g;

@@ -163,6 +163,8 @@ ParticleOrder particle_order_at(const hf_box &box, void *base, int64_t np);
 // records and tile offsets go to the order region and the slot maps are
 // written; the workspace is then deposit_tiled_ws_bytes(box, np, true).
 bool deposit_tiled_supported(const hf_box &box, int64_t np);
+// True where the binned form's workspace is asked for but the direct form runs without it.
+bool deposit_ws_optional(const hf_box &box);
 size_t deposit_tiled_ws_bytes(const hf_box &box, int64_t np, bool keep_order = false);
 hf_status deposit_tiled(hf_ctx *ctx, const hf_box &box, const void *pos, hf_dtype dtype, int64_t np, int64_t *rho,
                         void *ws, const ParticleOrder *order = nullptr);
@@ -243,7 +245,9 @@ hf_status label_back(hf_ctx *ctx, const hf_box &box, int64_t np, const ParticleO
                      const TileClaim *tile_claim = nullptr);
 
 // Workspace requirements of each stage (defined next to each stage).
-size_t deposit_ws_bytes(const hf_box &box, int64_t np);
+size_t deposit_ws_bytes(const hf_box &box, int64_t np, bool least = false);
+// hf_workspace_size; with `least`, without what a stage can do without.
+hf_status stage_ws_size(const hf_box *box, int64_t np, int stage_mask, bool least, size_t *bytes);
 size_t cwt_ws_bytes(const hf_box &box);
 size_t maxima_ws_bytes(const hf_box &box);
 size_t segment_ws_bytes(const hf_box &box);

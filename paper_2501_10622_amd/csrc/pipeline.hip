@@ -8,7 +8,7 @@ extern "C" hf_status hf_find_halos(hf_ctx *ctx, const hf_box *box, const hf_job 
     hf_status s = check_box_for(box, job->kernel);
     if (s != HF_OK) return s;
     size_t need = 0;
-    s = hf_workspace_size(box, job->np, pipeline_stages(job->kernel), &need);
+    s = stage_ws_size(box, job->np, pipeline_stages(job->kernel), true, &need);
     if (s != HF_OK) return s;
     s = check_ws(ws, ws_bytes, need);
     if (s != HF_OK) return s;
@@ -60,7 +60,7 @@ extern "C" hf_status hf_find_halos_filtered(hf_ctx *ctx, const hf_box *box, cons
     if (job->max_cap > 0 && (!gf->group_particles || !gf->group_cells || !gf->group_keep)) return HF_ERR_ARG;
     if (job->max_cap > ncells) return HF_ERR_ARG;
     size_t need = 0;
-    s = hf_workspace_size(box, job->np, pipeline_stages(job->kernel) | HF_STAGE_GROUPS, &need);
+    s = stage_ws_size(box, job->np, pipeline_stages(job->kernel) | HF_STAGE_GROUPS, true, &need);
     if (s != HF_OK) return s;
     s = check_ws(ws, ws_bytes, need);
     if (s != HF_OK) return s;
@@ -129,18 +129,24 @@ extern "C" hf_status hf_find_halos_filtered(hf_ctx *ctx, const hf_box *box, cons
 // one kept particle order), one forward transform shared by every scale
 // (hf_cwt_scales), then per scale the multiplier and inverse transform,
 // maxima and segmentation, and the labels through the same particle order.
-extern "C" hf_status hf_find_halos_scales_ws_size(const hf_box *box, int64_t np, int32_t count, size_t *bytes) {
+namespace {
+hf_status scales_ws_size(const hf_box *box, int64_t np, int32_t count, bool least, size_t *bytes) {
     if (!bytes || np < 0 || count < 1 || count > HF_CWT_BATCH_MAX) return HF_ERR_ARG;
     hf_status s = check_box(box);
     if (s != HF_OK) return s;
     size_t all = 0, cw = 0;
-    s = hf_workspace_size(box, np, HF_STAGE_ALL, &all);
+    s = stage_ws_size(box, np, HF_STAGE_ALL, least, &all);
     if (s == HF_OK) s = hf_cwt_batch_ws_size(box->n, count, &cw);
     if (s != HF_OK) return s;
     const size_t ord = particle_order_supported(*box, np) ? particle_order_bytes(*box, np) : 0;
     const size_t shared = all - ord;  // every stage's share, one transform included
     *bytes = ord + (shared > cw ? shared : cw);
     return HF_OK;
+}
+}  // namespace
+
+extern "C" hf_status hf_find_halos_scales_ws_size(const hf_box *box, int64_t np, int32_t count, size_t *bytes) {
+    return scales_ws_size(box, np, count, false, bytes);
 }
 
 extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const void *pos, hf_dtype dtype, int64_t np,
@@ -153,7 +159,7 @@ extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const 
     hf_status s = check_box(box);
     if (s != HF_OK) return s;
     size_t need = 0;
-    s = hf_find_halos_scales_ws_size(box, np, count, &need);
+    s = scales_ws_size(box, np, count, true, &need);
     if (s != HF_OK) return s;
     s = check_ws(ws, ws_bytes, need);
     if (s != HF_OK) return s;
@@ -200,10 +206,10 @@ struct IdentifyLayout {
     size_t base, groups, pass, claim, total;
 };
 
-hf_status identify_layout(const hf_box *box, int64_t np, int32_t count, const hf_scale_job *scales,
+hf_status identify_layout(const hf_box *box, int64_t np, int32_t count, const hf_scale_job *scales, bool least,
                           IdentifyLayout &L) {
     if (!scales) return HF_ERR_ARG;
-    hf_status s = hf_find_halos_scales_ws_size(box, np, count, &L.base);
+    hf_status s = scales_ws_size(box, np, count, least, &L.base);
     if (s != HF_OK) return s;
     int64_t cap = 0;
     for (int j = 0; j < count; ++j) {
@@ -223,7 +229,7 @@ extern "C" hf_status hf_identify_ws_size(const hf_box *box, int64_t np, int32_t 
                                         size_t *bytes) {
     if (!bytes) return HF_ERR_ARG;
     IdentifyLayout L{};
-    hf_status s = identify_layout(box, np, count, scales, L);
+    hf_status s = identify_layout(box, np, count, scales, false, L);
     if (s == HF_OK) *bytes = L.total;
     return s;
 }
@@ -265,7 +271,8 @@ extern "C" hf_status hf_identify(hf_ctx *ctx, const hf_box *box, const void *pos
     hf_status s = check_box(box);
     if (s != HF_OK) return s;
     IdentifyLayout L{};
-    s = identify_layout(box, np, count, scales, L);
+    s = identify_layout(box, np, count, scales, false, L);
+    if (s == HF_OK && ws_bytes < L.total) s = identify_layout(box, np, count, scales, true, L);
     if (s != HF_OK) return s;
     s = check_ws(ws, ws_bytes, L.total);
     if (s != HF_OK) return s;
@@ -338,7 +345,7 @@ struct GridsLayout {
 };
 
 hf_status grids_layout(double box_len, int32_t frac_bits, int64_t np, int32_t count, const hf_grid_scale *scales,
-                       bool with_vel, bool records, GridsLayout &L) {
+                       bool with_vel, bool records, bool least, GridsLayout &L) {
     if (!scales || count < 1 || count > HF_CWT_BATCH_MAX || np < 0) return HF_ERR_ARG;
     size_t shared = 0, groups = 0;
     int64_t cap = 0;
@@ -348,8 +355,7 @@ hf_status grids_layout(double box_len, int32_t frac_bits, int64_t np, int32_t co
         if (s != HF_OK) return s;
         if (scales[j].max_cap < 0) return HF_ERR_ARG;
         size_t need = 0;
-        s = hf_workspace_size(&b, np, HF_STAGE_DEPOSIT | HF_STAGE_STENCIL | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT,
-                              &need);
+        s = stage_ws_size(&b, np, HF_STAGE_DEPOSIT | HF_STAGE_STENCIL | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, least, &need);
         if (s != HF_OK) return s;
         shared = need > shared ? need : shared;
         if (with_vel) {  // steps 9-10 reuse the stage region once every scale's stages are done
@@ -371,7 +377,7 @@ extern "C" hf_status hf_identify_grids_ws_size(double box_len, int32_t frac_bits
                                               const hf_grid_scale *scales, int32_t with_velocities, size_t *bytes) {
     if (!bytes) return HF_ERR_ARG;
     GridsLayout L{};
-    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, true, L);
+    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, true, false, L);
     if (s == HF_OK) *bytes = L.total;
     return s;
 }
@@ -388,9 +394,9 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
     const bool with_vel = vel != nullptr;
     if (with_vel && (!(grav_mass > 0.0) || !(grav_mass < 1e300))) return HF_ERR_ARG;
     GridsLayout L{};
-    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, L);
-    if (s != HF_OK) return s;
-    if (ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, false, L);
+    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, false, L);
+    if (s == HF_OK && ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, true, L);
+    if (s == HF_OK && ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, false, true, L);
     if (s != HF_OK) return s;
     int32_t hw[HF_CWT_BATCH_MAX];
     for (int j = 0; j < count; ++j) {
@@ -463,7 +469,7 @@ extern "C" hf_status hf_find_halos_group(hf_ctx *ctx, int32_t n, int32_t frac_bi
         hf_status s = check_box(&box);
         if (s != HF_OK) return s;
         size_t need = 0;
-        s = hf_workspace_size(&box, job.np, HF_STAGE_DEPOSIT | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, &need);
+        s = stage_ws_size(&box, job.np, HF_STAGE_DEPOSIT | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, true, &need);
         if (s != HF_OK) return s;
         s = check_ws(items[j].ws, items[j].ws_bytes, need);
         if (s != HF_OK) return s;

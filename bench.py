@@ -44,7 +44,7 @@ TIMER_SYMBOLS = {
     "fft_y_fwd": ("fft_y_fwd_kernel",), "fft_z_mul": ("fft_z_mul_kernel",),
     "fft_y_inv": ("fft_y_inv_kernel",), "fft_x_inv": ("fft_x_inv_kernel",),
     "maxima_mark": ("max_tile_kernel", "max_direct_kernel"), "maxima_count": ("mask_count_kernel",),
-    "maxima_scan": ("one_scan_kernel<1>", "seg_reduce_kernel<1>", "seg_scan_kernel<1>"), "maxima_write": ("list_write_kernel",),
+    "maxima_scan": ("one_scan_kernel<1>", "seg_reduce_kernel<1>", "seg_scan_kernel<1>"), "maxima_write": ("list_write_kernel", "list_short_kernel"),
     "parent": ("parent_resolve_kernel",), "jump_flags": ("zero_words_kernel",),
     "jump": ("bnd_chase_kernel",), "finalize": ("seg_finalize_kernel",),
     "label_tiles": ("tile_label_kernel",), "label_level1": ("to_level1_kernel",), "label_input": ("to_input_kernel",),

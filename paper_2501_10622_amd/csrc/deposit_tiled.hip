@@ -1331,9 +1331,12 @@ unsigned resident_grid(const hf_ctx *ctx, const void *kernel, unsigned blocks) {
 // 128^3 (2^21), 53 -> 12 us at 96^3; 256^3 (2^24) level 1 61 -> 53 and level 2
 // 64 -> 42 us.  From 2^26 particles on HCHUNK fills the device and each
 // workgroup's up to 512 counter atomics are spread over most particles.
-int hist_chunk(const hf_ctx *ctx, int64_t np) {
+// The histogram over one bucket's tiles (`digits` > 0) keeps to chunks of 16
+// particles per counter and more, or its counter atomics are what it does: 128^3 (512
+// tiles) 27 -> 16 us, 96^3 12.3 -> 10.7.
+int hist_chunk(const hf_ctx *ctx, int64_t np, int digits = 0) {
     int c = HCHUNK;
-    while (c > HIST_MIN_CHUNK && np / c < HIST_FILL * int64_t(ctx->cus)) c >>= 1;
+    while (c > HIST_MIN_CHUNK && c / 2 >= 16 * digits && np / c < HIST_FILL * int64_t(ctx->cus)) c >>= 1;
     return c;
 }
 
@@ -1374,7 +1377,7 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
     const int64_t clear = (reinterpret_cast<char *>(count2) - reinterpret_cast<char *>(count1)) / 4 + g.ntiles;
     HF_LAUNCH(ctx, K_DEP_PREP, zero_u32_kernel, dim3(64), dim3(256), 0, st, count1, clear);
     const unsigned part_blocks = unsigned((np + CHUNK - 1) / CHUNK);
-    const int hchunk = hist_chunk(ctx, np);
+    const int hchunk = hist_chunk(ctx, np, g.nbuckets > 1 ? 0 : g.digits);
     const unsigned hist_blocks = unsigned((np + hchunk - 1) / hchunk);
     if (g.nbuckets > 1) {
         if (hist_blocks)

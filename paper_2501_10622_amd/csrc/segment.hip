@@ -166,7 +166,7 @@ constexpr int PLANE_BYTES = 4 * RHX * RHY;
 constexpr uint32_t NONE = 4 * RHCELLS;        // address of the place past the halo tile
 static_assert(NONE <= 0xffffu, "addresses fit 16 bits");
 static_assert(RZ % 8 == 0, "a column of addresses is whole 16-byte words");
-constexpr int CHASE_FLAGS = 8;  // one per launch of the boundary chase, at most 4 at n = 1024
+constexpr int CHASE_FLAGS = 8;  // one per round of the boundary chase, at most 3 at n = 1024
 
 // The words of a column's 16-bit addresses, RZ / 8 of 16 bytes.
 constexpr int COLUMN_WORDS = RZ / 8;
@@ -393,9 +393,10 @@ __global__ void zero_words_kernel(uint32_t *w, int64_t count) {
 //
 // One launch takes at most CHASE_HOPS hops per entry: after it every pointer
 // is final or has come CHASE_HOPS boundary cells along its chain, so each hop of
-// the next launch covers as many, and ceil(log_CHASE_HOPS(entries)) launches
+// the next launch covers as many, and ceil(log_CHASE_HOPS(entries)) rounds
 // reach the end of any chain.  A launch runs only if the one before left an
-// entry open.  Chains cross few tiles (one to three at scales of 1 to 4 cells),
+// entry open, and the last round is the final pass's, on the entries it reads
+// (follow).  Chains cross few tiles (one to three at scales of 1 to 4 cells),
 // so the first launch ends them all, and a hop is two dependent loads: the
 // latency of BATCH chains per thread is what bounds it.  Rounds of pointer
 // doubling with lists of the entries still open (one hop per launch,
@@ -404,6 +405,17 @@ __global__ void zero_words_kernel(uint32_t *w, int64_t count) {
 // 1024^3 where the chase takes 17 us, 47 us and 1.47 ms.
 constexpr int BATCH = 8;  // independent chains per thread, so their loads overlap
 constexpr int CHASE_HOPS = 1024;
+
+template <bool FULL>
+__device__ int32_t follow(const int32_t *__restrict__ bnd, const TileGrid &tg, int32_t p) {
+    while (p >= 0) {
+        const int64_t s = bnd_slot<FULL>(tg, p);
+        const int32_t q = s >= 0 ? bnd[s] : p;
+        if (q == p) break;
+        p = q;
+    }
+    return p;
+}
 
 template <bool FULL>
 __global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t count, TileGrid tg, uint32_t *flags,
@@ -462,6 +474,7 @@ __global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t co
 template <bool FULL>
 __global__ void __launch_bounds__(PR_THREADS) seg_finalize_kernel(const uint4 *__restrict__ ptr,
                                                                   const int32_t *__restrict__ bnd, TileGrid rg,
+                                                                  const uint32_t *__restrict__ open,
                                                                   int32_t *__restrict__ label) {
     __shared__ int32_t table[RHCELLS + 1];
     int x0, y0, z0;
@@ -518,6 +531,17 @@ __global__ void __launch_bounds__(PR_THREADS) seg_finalize_kernel(const uint4 *_
 #pragma unroll
     for (int i = 0; i < LOADS; ++i)
         if (at[i] >= 0) table[at[i]] = v[i];
+    __syncthreads();
+    if (*open != 0u) {  // the chase left entries open: the rest of the way, at most CHASE_HOPS steps
+#pragma unroll 1
+        for (int k = tid; k < RHCELLS; k += PR_THREADS) {
+            const int hx = k % RHX, hy = (k / RHX) % RHY, hz = k / (RHX * RHY);
+            if (hx >= ex || hy >= ey || hz >= ez) continue;
+            if (hx == 0 || hx == ex - 1 || hy == 0 || hy == ey - 1 || hz == 0 || hz == ez - 1)
+                table[k] = follow<FULL>(bnd, rg, bnd[bnd_slot_at<FULL>(rg, wrap(x0 + hx - 1, n), wrap(y0 + hy - 1, n),
+                                                                       wrap(z0 + hz - 1, n))]);
+        }
+    }
     if (tid == 0) table[RHCELLS] = -1;
     const bool column = x < wx && y < wy;
     const uint32_t g0 = ((uint32_t(z0) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
@@ -550,15 +574,13 @@ __global__ void __launch_bounds__(LIST_CHUNK_WORDS) mask_count_kernel(const uint
     if (threadIdx.x == 0) counts[blockIdx.x] = red[0] + red[1];
 }
 
-
-__global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint32_t *__restrict__ mask,
-                                                                      int64_t words,
-                                                                      const uint32_t *__restrict__ offsets,
-                                                                      int64_t cap, int32_t *__restrict__ out) {
+// Writes the cells of this thread's mask word (word w, value bits) of a chunk
+// whose first cell goes to place `base` of the list; returns the place after the
+// thread's last.
+__device__ __forceinline__ uint32_t write_cells(int64_t w, uint32_t bits, uint32_t base, int64_t cap,
+                                                int32_t *__restrict__ out) {
     static_assert(LIST_CHUNK_WORDS == 128, "two wavefronts");
     __shared__ uint32_t first;  // maxima of the first wavefront's words
-    const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
-    uint32_t bits = w < words ? mask[w] : 0u;
     const uint32_t count = uint32_t(__popc(bits));
     uint32_t upto = count;
     for (int off = 1; off < 64; off <<= 1) {
@@ -567,12 +589,51 @@ __global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint
     }
     if (threadIdx.x == 63) first = upto;
     __syncthreads();
-    uint32_t r = offsets[blockIdx.x] + upto - count + (threadIdx.x >= 64 ? first : 0u);
+    uint32_t r = base + upto - count + (threadIdx.x >= 64 ? first : 0u);
     while (bits) {
         const int b = __ffs(bits) - 1;
         bits &= bits - 1;
         if (int64_t(r) < cap) out[r] = int32_t(w * 32 + b);
         ++r;
+    }
+    return r;
+}
+
+__global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint32_t *__restrict__ mask,
+                                                                      int64_t words,
+                                                                      const uint32_t *__restrict__ offsets,
+                                                                      int64_t cap, int32_t *__restrict__ out) {
+    const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
+    write_cells(w, w < words ? mask[w] : 0u, offsets[blockIdx.x], cap, out);
+}
+
+// A short mask (up to LIST_SHORT chunks, n = 128) in one launch: a workgroup counts
+// the words before its chunk itself, and the last one has the total.  Three
+// launches of 3 to 5 us each are what the short lists took (12.2 us at 64^3, 13.4 at
+// 128^3, where this takes 4.4 and 11); at 256^3 the words would be read 2048 times.
+constexpr int LIST_SHORT = 512;
+
+__global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_short_kernel(const uint32_t *__restrict__ mask,
+                                                                      int64_t words, int64_t cap,
+                                                                      int32_t *__restrict__ out,
+                                                                      int64_t *__restrict__ d_count,
+                                                                      uint32_t *status) {
+    __shared__ uint32_t red[LIST_CHUNK_WORDS / 64];
+    const uint4 *before = reinterpret_cast<const uint4 *>(mask);  // whole chunks lie before this one
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (uint32_t k = threadIdx.x; k < blockIdx.x * (LIST_CHUNK_WORDS / 4); k += LIST_CHUNK_WORDS) {
+        const uint4 m = before[k];
+        sum += uint32_t(__popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w));
+    }
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
+    const uint32_t end = write_cells(w, w < words ? mask[w] : 0u, red[0] + red[1], cap, out);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == LIST_CHUNK_WORDS - 1) {
+        *d_count = int64_t(end);
+        if (int64_t(end) > cap) atomicOr(status, ST_CAPACITY);
     }
 }
 
@@ -586,10 +647,10 @@ TileGrid resolve_grid(int n) {
     return TileGrid{n, (n + RX - 1) / RX, (n + RY - 1) / RY, (n + RZ - 1) / RZ, FastDiv(uint32_t(n))};
 }
 
-// Launches that end every chain of at most `count` boundary cells.
-int chase_launches(uint64_t count) {
-    int k = 1;
-    for (uint64_t reach = CHASE_HOPS; reach < count; reach *= CHASE_HOPS) ++k;
+// Rounds that end every chain of at most `count` boundary cells (a launch at least, and the final pass's).
+int chase_rounds(uint64_t count) {
+    int k = 2;
+    for (uint64_t reach = uint64_t(CHASE_HOPS) * CHASE_HOPS; reach < count; reach *= CHASE_HOPS) ++k;
     return k;
 }
 
@@ -624,7 +685,7 @@ int stride_grid(int64_t work) {
 
 struct SegmentLayout {
     size_t flags, ptr, bnd, total;
-    int launches;  // of the boundary chase
+    int rounds;  // of the boundary chase, the last one the final pass's
     int64_t nbnd;
 };
 
@@ -633,7 +694,7 @@ SegmentLayout segment_layout(int n) {
     const TileGrid rg = resolve_grid(n);
     const uint64_t tiles = uint64_t(rg.ntx) * rg.nty * rg.ntz;
     L.nbnd = int64_t(tiles) * NBND;
-    L.launches = chase_launches(uint64_t(L.nbnd));
+    L.rounds = chase_rounds(uint64_t(L.nbnd));
     size_t off = 0;
     L.flags = off;
     off = align_up(off + sizeof(uint32_t) * CHASE_FLAGS);
@@ -660,6 +721,11 @@ hf_status mask_to_list(hf_ctx *ctx, const MaximaLayout &L, char *w8, int32_t *ma
     auto *mask = reinterpret_cast<uint32_t *>(w8 + L.mask);
     auto *counts = reinterpret_cast<uint32_t *>(w8 + L.counts);
     auto *offsets = reinterpret_cast<uint32_t *>(w8 + L.offsets);
+    if (L.nchunks <= LIST_SHORT) {
+        HF_LAUNCH(ctx, K_MAX_WRITE, list_short_kernel, dim3(L.nchunks), dim3(LIST_CHUNK_WORDS), 0, ctx->stream, mask,
+                  L.words, max_cap, max_idx, d_count, ctx->d_status);
+        return launch_status();
+    }
     HF_LAUNCH(ctx, K_MAX_COUNT, mask_count_kernel, dim3(L.nchunks), dim3(LIST_CHUNK_WORDS), 0, ctx->stream, mask,
               L.words, counts);
     const ScanJob sj = scan_job(counts, L.nchunks, reinterpret_cast<uint64_t *>(w8 + L.partial), offsets, nullptr,
@@ -703,7 +769,7 @@ hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, i
     auto *bnd = reinterpret_cast<int32_t *>(w8 + L.bnd);
     const bool full = all_full(n);
     const dim3 chase(stride_grid((L.nbnd + BATCH - 1) / BATCH));
-    for (int r = 0; r < L.launches; ++r) {
+    for (int r = 0; r + 1 < L.rounds; ++r) {
         if (full)
             HF_LAUNCH(ctx, K_JUMP, bnd_chase_kernel<true>, chase, dim3(256), 0, ctx->stream, bnd, L.nbnd, tg, flags,
                       r);
@@ -714,10 +780,10 @@ hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, i
     const dim3 grid(tg.ntx * tg.nty * tg.ntz);
     if (full)
         HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<true>, grid, dim3(PR_THREADS), 0, ctx->stream, ptr, bnd, tg,
-                  cell_label);
+                  flags + L.rounds - 1, cell_label);
     else
         HF_LAUNCH(ctx, K_FINALIZE, seg_finalize_kernel<false>, grid, dim3(PR_THREADS), 0, ctx->stream, ptr, bnd, tg,
-                  cell_label);
+                  flags + L.rounds - 1, cell_label);
     return launch_status();
 }
 

@@ -497,13 +497,14 @@ hf_status hf_unbind(hf_ctx *ctx, const hf_box *box, const void *pos, const void 
                     double grav_mass, int64_t particle_th, uint8_t *bound_keep, void *ws, size_t ws_bytes);
 
 /* Serving form of steps 2-6 for `count` (1..HF_CWT_BATCH_MAX) boxes of the same
- * grid size n: per-box deposits, ONE batched transform (hf_cwt_batch) for the
- * group, then per-box maxima, segmentation and labels, all on the context's
- * stream.  items[] is a host array read during the call.  Each item carries its
- * box length and its own workspace of hf_workspace_size(box, np,
- * HF_STAGE_DEPOSIT | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT) bytes; cwt_ws holds
- * hf_cwt_batch_ws_size(n, count) bytes.  All jobs must use `kernel`.  Every box
- * gets exactly the results hf_find_halos would give it alone. */
+ * grid size n: the deposits, ONE batched transform (hf_cwt_batch) for the group,
+ * then maxima, segmentation and labels, all on the context's stream; small boxes
+ * of one type whose buffers lie apart go through each stage in one launch.
+ * items[] is a host array read during the call.  Each item carries its box length
+ * and its own workspace of hf_workspace_size(box, np, HF_STAGE_DEPOSIT |
+ * HF_STAGE_MAXIMA | HF_STAGE_SEGMENT) bytes; cwt_ws holds hf_cwt_batch_ws_size(n,
+ * count) bytes.  All jobs must use `kernel`.  Every box gets exactly the results
+ * hf_find_halos would give it alone. */
 typedef struct {
     hf_job job;
     double box_len;

@@ -64,53 +64,61 @@ __global__ void __launch_bounds__(DEP_BLOCK) deposit_atomic_kernel(const T *__re
 }
 
 template <typename T>
-__global__ void __launch_bounds__(DEP_BLOCK) label_kernel(const T *__restrict__ pos, int64_t np, FixedPoint<T> fp,
-                                                          int n, const int32_t *__restrict__ cell_label,
-                                                          int32_t *__restrict__ out, uint32_t *status) {
-    const uint32_t half = 1u << (fp.bits - 1);
-    bool bad = false;
-    constexpr int B = 4;  // particles per thread whose loads are issued together
-    const int64_t step = int64_t(gridDim.x) * blockDim.x * B;
-    for (int64_t i0 = blockIdx.x * int64_t(blockDim.x) * B + threadIdx.x; i0 < np; i0 += step) {
-        T px[B], py[B], pz[B];
-        int32_t lab[B];
-        uint32_t cell[B];
-        bool ok[B];
+struct Label {
+    static __device__ __forceinline__ void run(int n, const T *__restrict__ pos, int64_t np, FixedPoint<T> fp,
+                                               const int32_t *__restrict__ cell_label, int32_t *__restrict__ out,
+                                               uint32_t *status) {
+        const uint32_t half = 1u << (fp.bits - 1);
+        bool bad = false;
+        constexpr int B = 4;  // particles per thread whose loads are issued together
+        const int64_t step = int64_t(gridDim.x) * blockDim.x * B;
+        for (int64_t i0 = blockIdx.x * int64_t(blockDim.x) * B + threadIdx.x; i0 < np; i0 += step) {
+            T px[B], py[B], pz[B];
+            int32_t lab[B];
+            uint32_t cell[B];
+            bool ok[B];
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            const int64_t i = i0 + k * int64_t(blockDim.x);
-            if (i < np) {
-                px[k] = pos[3 * i + 0];
-                py[k] = pos[3 * i + 1];
-                pz[k] = pos[3 * i + 2];
+            for (int k = 0; k < B; ++k) {
+                const int64_t i = i0 + k * int64_t(blockDim.x);
+                if (i < np) {
+                    px[k] = pos[3 * i + 0];
+                    py[k] = pos[3 * i + 1];
+                    pz[k] = pos[3 * i + 2];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                const int64_t i = i0 + k * int64_t(blockDim.x);
+                uint32_t qx = 0, qy = 0, qz = 0;
+                ok[k] = false;
+                if (i < np) {
+                    ok[k] = fp.q(px[k], qx);
+                    ok[k] = fp.q(py[k], qy) && ok[k];
+                    ok[k] = fp.q(pz[k], qz) && ok[k];
+                    bad |= !ok[k];
+                }
+                uint32_t x = (qx + half) >> fp.bits, y = (qy + half) >> fp.bits, z = (qz + half) >> fp.bits;
+                if (x == uint32_t(n)) x = 0;
+                if (y == uint32_t(n)) y = 0;
+                if (z == uint32_t(n)) z = 0;
+                cell[k] = (z * uint32_t(n) + y) * uint32_t(n) + x;
+            }
+#pragma unroll
+            for (int k = 0; k < B; ++k) lab[k] = ok[k] ? cell_label[cell[k]] : -1;
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                const int64_t i = i0 + k * int64_t(blockDim.x);
+                if (i < np) out[i] = lab[k];
             }
         }
-#pragma unroll
-        for (int k = 0; k < B; ++k) {
-            const int64_t i = i0 + k * int64_t(blockDim.x);
-            uint32_t qx = 0, qy = 0, qz = 0;
-            ok[k] = false;
-            if (i < np) {
-                ok[k] = fp.q(px[k], qx);
-                ok[k] = fp.q(py[k], qy) && ok[k];
-                ok[k] = fp.q(pz[k], qz) && ok[k];
-                bad |= !ok[k];
-            }
-            uint32_t x = (qx + half) >> fp.bits, y = (qy + half) >> fp.bits, z = (qz + half) >> fp.bits;
-            if (x == uint32_t(n)) x = 0;
-            if (y == uint32_t(n)) y = 0;
-            if (z == uint32_t(n)) z = 0;
-            cell[k] = (z * uint32_t(n) + y) * uint32_t(n) + x;
-        }
-#pragma unroll
-        for (int k = 0; k < B; ++k) lab[k] = ok[k] ? cell_label[cell[k]] : -1;
-#pragma unroll
-        for (int k = 0; k < B; ++k) {
-            const int64_t i = i0 + k * int64_t(blockDim.x);
-            if (i < np) out[i] = lab[k];
-        }
+        if (bad) atomicOr(status, ST_INPUT);
     }
-    if (bad) atomicOr(status, ST_INPUT);
+};
+
+template <typename T>
+__global__ void __launch_bounds__(DEP_BLOCK) label_kernel(const T *__restrict__ pos, int64_t np, FixedPoint<T> fp,
+                    int n, const int32_t *__restrict__ cell_label, int32_t *__restrict__ out, uint32_t *status) {
+    Label<T>::run(n, pos, np, fp, cell_label, out, status);
 }
 
 int grid_for(int64_t work, int block, int cap) {
@@ -155,6 +163,28 @@ extern "C" hf_status hf_deposit(hf_ctx *ctx, const hf_box *box, const void *pos,
                                ctx->d_status);
     }
     return launch_status();
+}
+
+namespace {
+template <typename T>
+hf_status run_label_group(hf_ctx *ctx, int n, int frac_bits, int count, const GroupBox *b) {
+    Boxes<const T *, int64_t, FixedPoint<T>, const int32_t *, int32_t *, uint32_t *> boxes{};
+    int most = 1;
+    for (int j = 0; j < count; ++j) {
+        pack(boxes.a[j], static_cast<const T *>(b[j].pos), b[j].np,
+             make_fixed_point<T>(hf_box{n, frac_bits, b[j].box_len}), static_cast<const int32_t *>(b[j].cell_label),
+             b[j].particle_label, ctx->d_status);
+        const int g = grid_for((b[j].np + 3) / 4, DEP_BLOCK, 65536);
+        most = g > most ? g : most;
+    }
+    launch_group<Label<T>, DEP_BLOCK>(ctx, K_LABEL, unsigned(most), count, boxes, n);
+    return launch_status();
+}
+}  // namespace
+
+hf_status hf::label_group(hf_ctx *ctx, int n, int frac_bits, hf_dtype dtype, int count, const GroupBox *b) {
+    return dtype == HF_F32 ? run_label_group<float>(ctx, n, frac_bits, count, b)
+                           : run_label_group<double>(ctx, n, frac_bits, count, b);
 }
 
 extern "C" hf_status hf_label(hf_ctx *ctx, const hf_box *box, const void *pos, hf_dtype dtype, int64_t np,

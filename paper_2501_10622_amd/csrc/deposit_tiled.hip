@@ -212,9 +212,15 @@ __device__ uint32_t block_exclusive_scan(uint32_t *s, uint32_t *tmp, int count) 
     return total;
 }
 
+struct ZeroU32 {
+    static __device__ __forceinline__ void run(int, uint32_t *p, int64_t count) {
+        for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < count; i += int64_t(gridDim.x) * blockDim.x)
+            p[i] = 0u;
+    }
+};
+
 __global__ void zero_u32_kernel(uint32_t *p, int64_t count) {
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < count; i += int64_t(gridDim.x) * blockDim.x)
-        p[i] = 0u;
+    ZeroU32::run(0, p, count);
 }
 
 // Scatter chunk of logical block b, or -1 for a spare block.  Workgroups go
@@ -519,107 +525,121 @@ __device__ __forceinline__ void l2_segments(const L2Input<T, FROM_REC> &in, int 
 }
 
 template <typename T, bool FROM_REC>
-__global__ void __launch_bounds__(HIST_THREADS) l2_hist_kernel(L2Input<T, FROM_REC> in, Geom g, uint32_t *count2,
-                                                               uint32_t *status) {
-    __shared__ uint32_t h[MAX_DIGITS], sv[REPLICAS], sp[REPLICAS];
-    int b;
-    int64_t lo, hi;
-    if (!l2_chunk(in, b, lo, hi)) return;
-    for (int d = threadIdx.x; d < MAX_DIGITS; d += blockDim.x) h[d] = 0u;
-    l2_segments(in, b, sv, sp);
-    __syncthreads();
-    const SegRange sg = FROM_REC ? seg_range(sv, sp, uint32_t(lo), uint32_t(hi)) : SegRange{true, 0u};
-    bool bad = false;
-    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += HIST_THREADS * LBATCH) {
-        Q3 q[LBATCH];
-        bool ok[LBATCH];
-        if (FROM_REC) {
+struct L2Hist {
+    static __device__ __forceinline__ void run(Geom g, L2Input<T, FROM_REC> in, uint32_t *count2, uint32_t *status) {
+        __shared__ uint32_t h[MAX_DIGITS], sv[REPLICAS], sp[REPLICAS];
+        int b;
+        int64_t lo, hi;
+        if (!l2_chunk(in, b, lo, hi)) return;
+        for (int d = threadIdx.x; d < MAX_DIGITS; d += blockDim.x) h[d] = 0u;
+        l2_segments(in, b, sv, sp);
+        __syncthreads();
+        const SegRange sg = FROM_REC ? seg_range(sv, sp, uint32_t(lo), uint32_t(hi)) : SegRange{true, 0u};
+        bool bad = false;
+        for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += HIST_THREADS * LBATCH) {
+            Q3 q[LBATCH];
+            bool ok[LBATCH];
+            if (FROM_REC) {
 #pragma unroll
-            for (int k = 0; k < LBATCH; ++k) {
-                const int64_t i = i0 + k * HIST_THREADS;
-                ok[k] = i < hi;
-                if (ok[k]) q[k] = in.rec1[seg_slot(sv, sp, sg, uint32_t(i))];
+                for (int k = 0; k < LBATCH; ++k) {
+                    const int64_t i = i0 + k * HIST_THREADS;
+                    ok[k] = i < hi;
+                    if (ok[k]) q[k] = in.rec1[seg_slot(sv, sp, sg, uint32_t(i))];
+                }
+            } else {
+                load_q_batch(in.pos, i0, HIST_THREADS, hi, in.fp, q, ok, bad);
             }
-        } else {
-            load_q_batch(in.pos, i0, HIST_THREADS, hi, in.fp, q, ok, bad);
-        }
 #pragma unroll
-        for (int k = 0; k < LBATCH; ++k)
-            if (ok[k]) atomicAdd(&h[tile_in_bucket(g, q[k].x >> g.bits, q[k].y >> g.bits, q[k].z >> g.bits)], 1u);
+            for (int k = 0; k < LBATCH; ++k)
+                if (ok[k]) atomicAdd(&h[tile_in_bucket(g, q[k].x >> g.bits, q[k].y >> g.bits, q[k].z >> g.bits)], 1u);
+        }
+        __syncthreads();
+        for (int d = threadIdx.x; d < g.digits; d += blockDim.x)
+            if (h[d]) atomicAdd(&count2[int64_t(b) * g.digits + d], h[d]);
+        if (bad) atomicOr(status, ST_INPUT);
     }
-    __syncthreads();
-    for (int d = threadIdx.x; d < g.digits; d += blockDim.x)
-        if (h[d]) atomicAdd(&count2[int64_t(b) * g.digits + d], h[d]);
-    if (bad) atomicOr(status, ST_INPUT);
+};
+
+template <typename T, bool FROM_REC>
+__global__ void __launch_bounds__(HIST_THREADS) l2_hist_kernel(L2Input<T, FROM_REC> in, Geom g, uint32_t *count2,
+                    uint32_t *status) {
+    L2Hist<T, FROM_REC>::run(g, in, count2, status);
 }
 
 
 // maps (optional, FROM_REC only) records where every level-1 record went.
 template <typename T, bool FROM_REC>
-__global__ void __launch_bounds__(PART_THREADS) l2_scatter_kernel(L2Input<T, FROM_REC> in, Geom g,
-                                                                  uint32_t *cursor2, uint64_t *__restrict__ rec2,
-                                                                  RunMaps maps) {
-    __shared__ uint64_t stage[CHUNK];
-    __shared__ uint16_t sdig[CHUNK];
-    __shared__ uint32_t h[MAX_DIGITS], off[MAX_DIGITS], gbase[MAX_DIGITS], tmp[MAX_DIGITS], sv[REPLICAS],
-        sp[REPLICAS];
-    int b;
-    int64_t lo, hi;
-    if (!l2_chunk(in, b, lo, hi)) return;
-    for (int d = threadIdx.x; d < MAX_DIGITS; d += blockDim.x) h[d] = 0u;
-    l2_segments(in, b, sv, sp);
-    __syncthreads();
-    const SegRange sg = FROM_REC ? seg_range(sv, sp, uint32_t(lo), uint32_t(hi)) : SegRange{true, 0u};
-    uint64_t r[PART_PER];
-    int dg[PART_PER];
-    uint32_t rank[PART_PER];
-    Q3 q[PART_PER];
-    bool ok[PART_PER];
-    if (FROM_REC) {
+struct L2Scatter {
+    static __device__ __forceinline__ void run(Geom g, L2Input<T, FROM_REC> in, uint32_t *cursor2,
+                                               uint64_t *__restrict__ rec2, RunMaps maps) {
+        __shared__ uint64_t stage[CHUNK];
+        __shared__ uint16_t sdig[CHUNK];
+        __shared__ uint32_t h[MAX_DIGITS], off[MAX_DIGITS], gbase[MAX_DIGITS], tmp[MAX_DIGITS], sv[REPLICAS],
+            sp[REPLICAS];
+        int b;
+        int64_t lo, hi;
+        if (!l2_chunk(in, b, lo, hi)) return;
+        for (int d = threadIdx.x; d < MAX_DIGITS; d += blockDim.x) h[d] = 0u;
+        l2_segments(in, b, sv, sp);
+        __syncthreads();
+        const SegRange sg = FROM_REC ? seg_range(sv, sp, uint32_t(lo), uint32_t(hi)) : SegRange{true, 0u};
+        uint64_t r[PART_PER];
+        int dg[PART_PER];
+        uint32_t rank[PART_PER];
+        Q3 q[PART_PER];
+        bool ok[PART_PER];
+        if (FROM_REC) {
+#pragma unroll
+            for (int k = 0; k < PART_PER; ++k) {
+                const int64_t i = lo + k * PART_THREADS + threadIdx.x;
+                ok[k] = i < hi;
+                if (ok[k]) q[k] = in.rec1[seg_slot(sv, sp, sg, uint32_t(i))];
+            }
+        } else {
+            bool bad = false;  // reported by the histogram pass
+            load_q_batch(in.pos, lo + threadIdx.x, PART_THREADS, hi, in.fp, q, ok, bad);
+        }
 #pragma unroll
         for (int k = 0; k < PART_PER; ++k) {
-            const int64_t i = lo + k * PART_THREADS + threadIdx.x;
-            ok[k] = i < hi;
-            if (ok[k]) q[k] = in.rec1[seg_slot(sv, sp, sg, uint32_t(i))];
+            dg[k] = -1;
+            if (ok[k]) {
+                dg[k] = tile_in_bucket(g, q[k].x >> g.bits, q[k].y >> g.bits, q[k].z >> g.bits);
+                r[k] = pack_local(g, q[k]);
+                rank[k] = atomicAdd(&h[dg[k]], 1u);
+            }
         }
-    } else {
-        bool bad = false;  // reported by the histogram pass
-        load_q_batch(in.pos, lo + threadIdx.x, PART_THREADS, hi, in.fp, q, ok, bad);
-    }
-#pragma unroll
-    for (int k = 0; k < PART_PER; ++k) {
-        dg[k] = -1;
-        if (ok[k]) {
-            dg[k] = tile_in_bucket(g, q[k].x >> g.bits, q[k].y >> g.bits, q[k].z >> g.bits);
-            r[k] = pack_local(g, q[k]);
-            rank[k] = atomicAdd(&h[dg[k]], 1u);
-        }
-    }
-    __syncthreads();
-    for (int d = threadIdx.x; d < g.digits; d += blockDim.x) off[d] = h[d];
-    __syncthreads();
-    const uint32_t total = block_exclusive_scan(off, tmp, g.digits);
-    for (int d = threadIdx.x; d < g.digits; d += blockDim.x)
-        if (h[d]) gbase[d] = atomicAdd(&cursor2[int64_t(b) * g.digits + d], h[d]);
-#pragma unroll
-    for (int k = 0; k < PART_PER; ++k)
-        if (dg[k] >= 0) {
-            const uint32_t s = off[dg[k]] + rank[k];
-            stage[s] = r[k];
-            sdig[s] = uint16_t(dg[k]);
-        }
-    __syncthreads();
-    const bool keep = FROM_REC && maps.pos;
-    for (uint32_t s = threadIdx.x; s < total; s += PART_THREADS) {
-        const int d = sdig[s];
-        rec2[gbase[d] + (s - off[d])] = stage[s];
-    }
-    if (keep) {
-        save_run_table(maps, l2_chunk_index(), g.digits, h, off, gbase, total);
+        __syncthreads();
+        for (int d = threadIdx.x; d < g.digits; d += blockDim.x) off[d] = h[d];
+        __syncthreads();
+        const uint32_t total = block_exclusive_scan(off, tmp, g.digits);
+        for (int d = threadIdx.x; d < g.digits; d += blockDim.x)
+            if (h[d]) gbase[d] = atomicAdd(&cursor2[int64_t(b) * g.digits + d], h[d]);
 #pragma unroll
         for (int k = 0; k < PART_PER; ++k)
-            if (dg[k] >= 0) maps.pos[lo + k * PART_THREADS + threadIdx.x] = uint16_t(off[dg[k]] + rank[k]);
+            if (dg[k] >= 0) {
+                const uint32_t s = off[dg[k]] + rank[k];
+                stage[s] = r[k];
+                sdig[s] = uint16_t(dg[k]);
+            }
+        __syncthreads();
+        const bool keep = FROM_REC && maps.pos;
+        for (uint32_t s = threadIdx.x; s < total; s += PART_THREADS) {
+            const int d = sdig[s];
+            rec2[gbase[d] + (s - off[d])] = stage[s];
+        }
+        if (keep) {
+            save_run_table(maps, l2_chunk_index(), g.digits, h, off, gbase, total);
+#pragma unroll
+            for (int k = 0; k < PART_PER; ++k)
+                if (dg[k] >= 0) maps.pos[lo + k * PART_THREADS + threadIdx.x] = uint16_t(off[dg[k]] + rank[k]);
+        }
     }
+};
+
+template <typename T, bool FROM_REC>
+__global__ void __launch_bounds__(PART_THREADS) l2_scatter_kernel(L2Input<T, FROM_REC> in, Geom g, uint32_t *cursor2,
+                    uint64_t *__restrict__ rec2, RunMaps maps) {
+    L2Scatter<T, FROM_REC>::run(g, in, cursor2, rec2, maps);
 }
 
 // ---------------------------------------------------------------- accumulate and fold
@@ -722,142 +742,155 @@ __device__ __forceinline__ int tile_slot(const Geom &g, int tx, int ty, int tz) 
 // the x = 0 plane of the next tile, so no x face is ever folded through memory.
 // The last tile's x face belongs to the first tile of the row (periodic): it
 // is added to that tile's cells and side-buffer entries at the end.
-__global__ void __launch_bounds__(ACC_THREADS) tile_accum_kernel(const uint64_t *__restrict__ rec2,
-                                                                 const uint32_t *__restrict__ start2, Geom g,
-                                                                 unsigned long long *__restrict__ rho,
-                                                                 unsigned long long *__restrict__ skirt,
-                                                                 uint32_t *status) {
-    __shared__ unsigned long long acc[MAX_ACC_CELLS];
-    int ty, tz;
-    if (g.btx == g.ntx) {
-        // rows of a bucket are whole rows: bucket-major row order, so each row's
-        // records are one run of the level-2 order and neighbouring workgroups
-        // read neighbouring runs
-        const int rows = g.bty * g.btz, b = int(blockIdx.x) / rows, r = int(blockIdx.x) % rows;
-        ty = ((b / g.nbx) % g.nby) * g.bty + r % g.bty;
-        tz = (b / (g.nbx * g.nby)) * g.btz + r / g.bty;
-    } else {
-        ty = int(blockIdx.x) % g.nty;
-        tz = int(blockIdx.x) / g.nty;
-    }
-    const int ax = g.tx + 1;
-    const int ncells = ax * AYZ * AYZ;
-    const size_t n = size_t(g.n);
-    const size_t gy0 = size_t(ty) * TYZ, gz0 = size_t(tz) * TYZ;
-    const int owned = g.tx * TYZ * TYZ;
-    constexpr int FACE = AYZ * AYZ;  // cells of the x face
-    bool overflow = false;
-    uint32_t prev = 0;  // particles of the previous tile, whose x face is carried in
-    // each tile's first batch of records is loaded before the previous tile
-    // is written out, so that its latency hides behind the stores
-    uint32_t lo = start2[tile_slot(g, 0, ty, tz)], hi = start2[tile_slot(g, 0, ty, tz) + 1];
-    uint64_t rr[ACC_RB];
-    load_records(rec2, lo + threadIdx.x, hi, rr);
-    for (int tx = 0; tx < g.ntx; ++tx) {
-        unsigned long long carried = 0ull;
-        if (tx > 0 && threadIdx.x < FACE) carried = acc[threadIdx.x * ax + g.tx];  // (z, y) = (k / 9, k % 9)
-        __syncthreads();
-        for (int c = threadIdx.x; c < ncells; c += ACC_THREADS) acc[c] = 0ull;
-        __syncthreads();
-        if (tx > 0 && threadIdx.x < FACE) acc[threadIdx.x * ax] = carried;
-        __syncthreads();
-        // fewer than 2^(63 - 3B) particles (with those carried in) cannot carry
-        // any cell of this tile past 2^63 - 1
-        if (uint64_t(hi - lo) + prev < (1ull << (63 - 3 * g.bits)))
-            accumulate<false>(rec2, lo, hi, g.bits, ax, acc, overflow, rr);
-        else
-            accumulate<true>(rec2, lo, hi, g.bits, ax, acc, overflow, rr);
-        prev = hi - lo;
-        if (tx + 1 < g.ntx) {
-            const int next = tile_slot(g, tx + 1, ty, tz);
-            lo = start2[next];
-            hi = start2[next + 1];
-            load_records(rec2, lo + threadIdx.x, hi, rr);
-        }
-        __syncthreads();
-        const size_t gx0 = size_t(tx) * g.tx;
-        for (int c = threadIdx.x; c < owned; c += ACC_THREADS) {
-            const int x = c & (g.tx - 1), y = (c >> g.ltx) & (TYZ - 1), z = c >> (g.ltx + 3);
-            rho[((gz0 + z) * n + gy0 + y) * n + gx0 + x] = acc[(z * AYZ + y) * ax + x];
-        }
-        const size_t tglob = (size_t(tz) * g.nty + ty) * g.ntx + tx;
-        for (int k = threadIdx.x; k < g.skirt; k += ACC_THREADS) {
-            int x, y, z;
-            skirt_cell(g.tx, k, x, y, z);
-            skirt[tglob * g.skirt + k] = acc[(z * AYZ + y) * ax + x];
-        }
-    }
-    // the last x face onto the row's first tile (x = 0 there): its owned cells
-    // in the grid, its y = 8 and z = 8 cells in the side buffer, all written by
-    // this workgroup above (the barrier's workgroup-scope ordering makes them
-    // visible here; a device-scope fence would write the L2 back)
-    __syncthreads();
-    if (threadIdx.x < FACE) {
-        const int y = threadIdx.x % AYZ, z = threadIdx.x / AYZ;
-        const unsigned long long w = acc[threadIdx.x * ax + g.tx];
-        unsigned long long *at;
-        if (y < TYZ && z < TYZ) {
-            at = rho + ((gz0 + z) * n + gy0 + y) * n;
+struct TileAccum {
+    static __device__ __forceinline__ void run(Geom g, const uint64_t *__restrict__ rec2,
+                                               const uint32_t *__restrict__ start2,
+                                               unsigned long long *__restrict__ rho,
+                                               unsigned long long *__restrict__ skirt, uint32_t *status) {
+        __shared__ unsigned long long acc[MAX_ACC_CELLS];
+        int ty, tz;
+        if (g.btx == g.ntx) {
+            // rows of a bucket are whole rows: bucket-major row order, so each row's
+            // records are one run of the level-2 order and neighbouring workgroups
+            // read neighbouring runs
+            const int rows = g.bty * g.btz, b = int(blockIdx.x) / rows, r = int(blockIdx.x) % rows;
+            ty = ((b / g.nbx) % g.nby) * g.bty + r % g.bty;
+            tz = (b / (g.nbx * g.nby)) * g.btz + r / g.bty;
         } else {
-            const size_t t0 = (size_t(tz) * g.nty + ty) * g.ntx;
-            at = skirt + t0 * g.skirt + (y == TYZ ? z * g.tx : g.tx * AYZ + y * g.tx);
+            ty = int(blockIdx.x) % g.nty;
+            tz = int(blockIdx.x) / g.nty;
         }
-        const unsigned long long v = *at, t = v + w;
-        // both parts are below 2^63 unless already reported; the sum must be too
-        if (t < v || (t >> 63)) overflow = true;
-        *at = t;
+        const int ax = g.tx + 1;
+        const int ncells = ax * AYZ * AYZ;
+        const size_t n = size_t(g.n);
+        const size_t gy0 = size_t(ty) * TYZ, gz0 = size_t(tz) * TYZ;
+        const int owned = g.tx * TYZ * TYZ;
+        constexpr int FACE = AYZ * AYZ;  // cells of the x face
+        bool overflow = false;
+        uint32_t prev = 0;  // particles of the previous tile, whose x face is carried in
+        // each tile's first batch of records is loaded before the previous tile
+        // is written out, so that its latency hides behind the stores
+        uint32_t lo = start2[tile_slot(g, 0, ty, tz)], hi = start2[tile_slot(g, 0, ty, tz) + 1];
+        uint64_t rr[ACC_RB];
+        load_records(rec2, lo + threadIdx.x, hi, rr);
+        for (int tx = 0; tx < g.ntx; ++tx) {
+            unsigned long long carried = 0ull;
+            if (tx > 0 && threadIdx.x < FACE) carried = acc[threadIdx.x * ax + g.tx];  // (z, y) = (k / 9, k % 9)
+            __syncthreads();
+            for (int c = threadIdx.x; c < ncells; c += ACC_THREADS) acc[c] = 0ull;
+            __syncthreads();
+            if (tx > 0 && threadIdx.x < FACE) acc[threadIdx.x * ax] = carried;
+            __syncthreads();
+            // fewer than 2^(63 - 3B) particles (with those carried in) cannot carry
+            // any cell of this tile past 2^63 - 1
+            if (uint64_t(hi - lo) + prev < (1ull << (63 - 3 * g.bits)))
+                accumulate<false>(rec2, lo, hi, g.bits, ax, acc, overflow, rr);
+            else
+                accumulate<true>(rec2, lo, hi, g.bits, ax, acc, overflow, rr);
+            prev = hi - lo;
+            if (tx + 1 < g.ntx) {
+                const int next = tile_slot(g, tx + 1, ty, tz);
+                lo = start2[next];
+                hi = start2[next + 1];
+                load_records(rec2, lo + threadIdx.x, hi, rr);
+            }
+            __syncthreads();
+            const size_t gx0 = size_t(tx) * g.tx;
+            for (int c = threadIdx.x; c < owned; c += ACC_THREADS) {
+                const int x = c & (g.tx - 1), y = (c >> g.ltx) & (TYZ - 1), z = c >> (g.ltx + 3);
+                rho[((gz0 + z) * n + gy0 + y) * n + gx0 + x] = acc[(z * AYZ + y) * ax + x];
+            }
+            const size_t tglob = (size_t(tz) * g.nty + ty) * g.ntx + tx;
+            for (int k = threadIdx.x; k < g.skirt; k += ACC_THREADS) {
+                int x, y, z;
+                skirt_cell(g.tx, k, x, y, z);
+                skirt[tglob * g.skirt + k] = acc[(z * AYZ + y) * ax + x];
+            }
+        }
+        // the last x face onto the row's first tile (x = 0 there): its owned cells
+        // in the grid, its y = 8 and z = 8 cells in the side buffer, all written by
+        // this workgroup above (the barrier's workgroup-scope ordering makes them
+        // visible here; a device-scope fence would write the L2 back)
+        __syncthreads();
+        if (threadIdx.x < FACE) {
+            const int y = threadIdx.x % AYZ, z = threadIdx.x / AYZ;
+            const unsigned long long w = acc[threadIdx.x * ax + g.tx];
+            unsigned long long *at;
+            if (y < TYZ && z < TYZ) {
+                at = rho + ((gz0 + z) * n + gy0 + y) * n;
+            } else {
+                const size_t t0 = (size_t(tz) * g.nty + ty) * g.ntx;
+                at = skirt + t0 * g.skirt + (y == TYZ ? z * g.tx : g.tx * AYZ + y * g.tx);
+            }
+            const unsigned long long v = *at, t = v + w;
+            // both parts are below 2^63 unless already reported; the sum must be too
+            if (t < v || (t >> 63)) overflow = true;
+            *at = t;
+        }
+        if (overflow) atomicOr(status, ST_OVERFLOW);
     }
-    if (overflow) atomicOr(status, ST_OVERFLOW);
+};
+
+__global__ void __launch_bounds__(ACC_THREADS) tile_accum_kernel(const uint64_t *__restrict__ rec2,
+                    const uint32_t *__restrict__ start2, Geom g, unsigned long long *__restrict__ rho,
+                    unsigned long long *__restrict__ skirt, uint32_t *status) {
+    TileAccum::run(g, rec2, start2, rho, skirt, status);
 }
 
 // One workgroup per tile: its y = 0 and z = 0 cells (the z = 0 plane, then the
 // y = 0 row of each plane z = 1..7: 15 tx cells, all in whole rows) gather the
 // y- and z-face sums that the lower neighbours in y and z computed for them
 // (the x faces were carried along the rows already).
-__global__ void __launch_bounds__(ACC_THREADS) skirt_fold_kernel(const unsigned long long *__restrict__ skirt, Geom g,
-                                                                 unsigned long long *__restrict__ rho,
-                                                                 uint32_t *status) {
-    const int t = blockIdx.x;
-    const int tx = t % g.ntx, ty = (t / g.ntx) % g.nty, tz = t / (g.ntx * g.nty);
-    const size_t n = size_t(g.n);
-    const size_t gx0 = size_t(tx) * g.tx, gy0 = size_t(ty) * TYZ, gz0 = size_t(tz) * TYZ;
-    const int sy = ty == 0 ? g.nty - 1 : ty - 1, sz = tz == 0 ? g.ntz - 1 : tz - 1;
-    const size_t below_y = (size_t(tz) * g.nty + sy) * g.ntx + tx;   // tile - y
-    const size_t below_z = (size_t(sz) * g.nty + ty) * g.ntx + tx;   // tile - z
-    const size_t below_yz = (size_t(sz) * g.nty + sy) * g.ntx + tx;  // tile - y - z
-    const int yface = g.tx * AYZ;  // start of the z face in a tile's side-buffer entries
-    bool overflow = false;
-    const int nface = 15 * g.tx;
-    for (int k = threadIdx.x; k < nface; k += ACC_THREADS) {
-        int x, y, z;
-        if (k < 8 * g.tx) {
-            z = 0;
-            y = k >> g.ltx;
-            x = k & (g.tx - 1);
-        } else {
-            const int j = k - 8 * g.tx;
-            z = 1 + (j >> g.ltx);
-            y = 0;
-            x = j & (g.tx - 1);
+struct SkirtFold {
+    static __device__ __forceinline__ void run(Geom g, const unsigned long long *__restrict__ skirt,
+                                               unsigned long long *__restrict__ rho, uint32_t *status) {
+        const int t = blockIdx.x;
+        const int tx = t % g.ntx, ty = (t / g.ntx) % g.nty, tz = t / (g.ntx * g.nty);
+        const size_t n = size_t(g.n);
+        const size_t gx0 = size_t(tx) * g.tx, gy0 = size_t(ty) * TYZ, gz0 = size_t(tz) * TYZ;
+        const int sy = ty == 0 ? g.nty - 1 : ty - 1, sz = tz == 0 ? g.ntz - 1 : tz - 1;
+        const size_t below_y = (size_t(tz) * g.nty + sy) * g.ntx + tx;   // tile - y
+        const size_t below_z = (size_t(sz) * g.nty + ty) * g.ntx + tx;   // tile - z
+        const size_t below_yz = (size_t(sz) * g.nty + sy) * g.ntx + tx;  // tile - y - z
+        const int yface = g.tx * AYZ;  // start of the z face in a tile's side-buffer entries
+        bool overflow = false;
+        const int nface = 15 * g.tx;
+        for (int k = threadIdx.x; k < nface; k += ACC_THREADS) {
+            int x, y, z;
+            if (k < 8 * g.tx) {
+                z = 0;
+                y = k >> g.ltx;
+                x = k & (g.tx - 1);
+            } else {
+                const int j = k - 8 * g.tx;
+                z = 1 + (j >> g.ltx);
+                y = 0;
+                x = j & (g.tx - 1);
+            }
+            const size_t at = ((gz0 + z) * n + gy0 + y) * n + gx0 + x;
+            const unsigned long long v = rho[at];
+            unsigned long long lo = 0ull, hi = 0ull;
+            auto add = [&](unsigned long long w) {
+                const unsigned long long s = lo + w;
+                hi += s < w;
+                lo = s;
+            };
+            if (z == 0) add(skirt[below_z * g.skirt + yface + y * g.tx + x]);            // (x, y, 8) of tile - z
+            if (y == 0) add(skirt[below_y * g.skirt + z * g.tx + x]);                    // (x, 8, z) of tile - y
+            if (y == 0 && z == 0) add(skirt[below_yz * g.skirt + TYZ * g.tx + x]);       // (x, 8, 8) of tile - y - z
+            // every part is below 2^63 unless already reported; the total must be too
+            const unsigned long long s = lo + v;
+            hi += s < v;
+            if (hi != 0 || (s >> 63)) overflow = true;
+            rho[at] = s;
         }
-        const size_t at = ((gz0 + z) * n + gy0 + y) * n + gx0 + x;
-        const unsigned long long v = rho[at];
-        unsigned long long lo = 0ull, hi = 0ull;
-        auto add = [&](unsigned long long w) {
-            const unsigned long long s = lo + w;
-            hi += s < w;
-            lo = s;
-        };
-        if (z == 0) add(skirt[below_z * g.skirt + yface + y * g.tx + x]);            // (x, y, 8) of tile - z
-        if (y == 0) add(skirt[below_y * g.skirt + z * g.tx + x]);                    // (x, 8, z) of tile - y
-        if (y == 0 && z == 0) add(skirt[below_yz * g.skirt + TYZ * g.tx + x]);       // (x, 8, 8) of tile - y - z
-        // every part is below 2^63 unless already reported; the total must be too
-        const unsigned long long s = lo + v;
-        hi += s < v;
-        if (hi != 0 || (s >> 63)) overflow = true;
-        rho[at] = s;
+        if (overflow) atomicOr(status, ST_OVERFLOW);
     }
-    if (overflow) atomicOr(status, ST_OVERFLOW);
+};
+
+__global__ void __launch_bounds__(ACC_THREADS) skirt_fold_kernel(const unsigned long long *__restrict__ skirt, Geom g,
+                    unsigned long long *__restrict__ rho, uint32_t *status) {
+    SkirtFold::run(g, skirt, rho, status);
 }
 
 // ---------------------------------------------------------------- step 6 through the particle order
@@ -1421,7 +1454,68 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
     return launch_status();
 }
 
+template <typename T>
+hf_status run_group(hf_ctx *ctx, int n, int frac_bits, int count, const GroupBox *b) {
+    Geom g;
+    if (!make_geom(hf_box{n, frac_bits, 1.0}, g)) return HF_ERR_SIZE;
+    Boxes<uint32_t *, int64_t> zero{};
+    Boxes<L2Input<T, false>, uint32_t *, uint32_t *> hist{};
+    Boxes<ScanJob> scan{};
+    Boxes<L2Input<T, false>, uint32_t *, uint64_t *, RunMaps> scatter{};
+    Boxes<const uint64_t *, const uint32_t *, unsigned long long *, unsigned long long *, uint32_t *> accum{};
+    Boxes<const unsigned long long *, unsigned long long *, uint32_t *> fold{};
+    unsigned hist_blocks = 0, part_blocks = 0;
+    for (int j = 0; j < count; ++j) {
+        const GroupBox &x = b[j];
+        const DepLayout L = dep_layout(g, x.np, false);
+        char *ws = x.ws;
+        auto *count2 = reinterpret_cast<uint32_t *>(ws + L.count2);
+        auto *start2 = reinterpret_cast<uint32_t *>(ws + L.start2);
+        auto *cursor2 = reinterpret_cast<uint32_t *>(ws + L.cursor2);
+        auto *rec2 = reinterpret_cast<uint64_t *>(ws + L.rec2);
+        auto *skirt = reinterpret_cast<unsigned long long *>(ws + L.skirt);
+        auto *rho = reinterpret_cast<unsigned long long *>(x.rho);
+        const auto *pos = static_cast<const T *>(x.pos);
+        const FixedPoint<T> fp = make_fixed_point<T>(hf_box{n, frac_bits, x.box_len});
+        const int hchunk = hist_chunk(ctx, x.np * count, g.digits);  // all boxes fill the device together
+        const L2Input<T, false> hin{pos, x.np, fp, nullptr, nullptr, nullptr, nullptr, nullptr, 1, hchunk};
+        const L2Input<T, false> sin{pos, x.np, fp, nullptr, nullptr, nullptr, nullptr, nullptr, 1, CHUNK};
+        pack(zero.a[j], count2, int64_t(g.ntiles));
+        pack(hist.a[j], hin, count2, ctx->d_status);
+        pack(scan.a[j], scan_job(count2, g.ntiles, reinterpret_cast<uint64_t *>(ws + L.partial), start2, cursor2));
+        pack(scatter.a[j], sin, cursor2, rec2, RunMaps{});
+        pack(accum.a[j], static_cast<const uint64_t *>(rec2), static_cast<const uint32_t *>(start2), rho, skirt,
+             ctx->d_status);
+        pack(fold.a[j], static_cast<const unsigned long long *>(skirt), rho, ctx->d_status);
+        const unsigned h = unsigned((x.np + hchunk - 1) / hchunk), p = unsigned((x.np + CHUNK - 1) / CHUNK);
+        hist_blocks = h > hist_blocks ? h : hist_blocks;
+        part_blocks = p > part_blocks ? p : part_blocks;
+    }
+    launch_group<ZeroU32, 256>(ctx, K_DEP_PREP, 1, count, zero, 0);
+    if (hist_blocks) launch_group<L2Hist<T, false>, HIST_THREADS>(ctx, K_DEP_L2_HIST, hist_blocks, count, hist, g);
+    launch_group<OneScan<SCAN_TILES>, SCAN_THREADS>(ctx, K_DEP_PREP, 1, count, scan, 0);
+    if (part_blocks)
+        launch_group<L2Scatter<T, false>, PART_THREADS>(ctx, K_DEP_L2_SCATTER, part_blocks, count, scatter, g);
+    launch_group<TileAccum, ACC_THREADS>(ctx, K_DEPOSIT, unsigned(g.nty * g.ntz), count, accum, g);
+    launch_group<SkirtFold, ACC_THREADS>(ctx, K_DEP_FOLD, unsigned(g.ntiles), count, fold, g);
+    return launch_status();
+}
+
 }  // namespace
+
+// One bucket, whole tiles, and the tiles' scan by one workgroup.
+bool hf::deposit_group_supported(int n, int frac_bits, int count, const GroupBox *b) {
+    Geom g;
+    if (n % 16 || !make_geom(hf_box{n, frac_bits, 1.0}, g) || g.nbuckets != 1 || g.ntiles > SCAN_SMALL) return false;
+    for (int j = 0; j < count; ++j)
+        if (!deposit_tiled_supported(hf_box{n, frac_bits, b[j].box_len}, b[j].np)) return false;
+    return true;
+}
+
+hf_status hf::deposit_group(hf_ctx *ctx, int n, int frac_bits, hf_dtype dtype, int count, const GroupBox *b) {
+    return dtype == HF_F32 ? run_group<float>(ctx, n, frac_bits, count, b)
+                           : run_group<double>(ctx, n, frac_bits, count, b);
+}
 
 bool hf::deposit_tiled_supported(const hf_box &box, int64_t np) {
     // packed tile records hold 12 + 3B <= 63 bits; counts are uint32

@@ -169,6 +169,30 @@ size_t deposit_tiled_ws_bytes(const hf_box &box, int64_t np, bool keep_order = f
 hf_status deposit_tiled(hf_ctx *ctx, const hf_box &box, const void *pos, hf_dtype dtype, int64_t np, int64_t *rho,
                         void *ws, const ParticleOrder *order = nullptr);
 
+// The stages of several boxes of one size in one launch per kernel instead of one
+// per box: where the deposits have a single bucket, the maxima lists are short and
+// every resolve tile is whole, each launch of one box leaves most of the device
+// idle.  Each box has its own workspace, as for the calls above.
+struct GroupBox {
+    const void *pos;
+    int64_t np;
+    double box_len;
+    int64_t *rho;
+    const float *cwt;
+    float tau;
+    int32_t *max_idx;
+    int64_t max_cap;
+    int64_t *d_count;
+    int32_t *cell_label;
+    int32_t *particle_label;
+    char *ws;
+};
+bool deposit_group_supported(int n, int frac_bits, int count, const GroupBox *b);
+hf_status deposit_group(hf_ctx *ctx, int n, int frac_bits, hf_dtype dtype, int count, const GroupBox *b);
+bool segment_group_supported(int n);
+hf_status segment_group(hf_ctx *ctx, int n, int count, const GroupBox *b);
+hf_status label_group(hf_ctx *ctx, int n, int frac_bits, hf_dtype dtype, int count, const GroupBox *b);
+
 // Step 6 through a kept particle order, with label_scratch_bytes(np) of
 // scratch.  Same result as hf_label on the positions the order was built from.
 size_t label_scratch_bytes(int64_t np);
@@ -342,6 +366,54 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t G) {
     const uint32_t q = G / NUM_XCD, r = G % NUM_XCD;
     const uint32_t x = b % NUM_XCD, k = b / NUM_XCD;
     return x * q + (x < r ? x : r) + k;
+}
+
+// ---------------------------------------------------------------------------
+// One launch over several boxes: Body::run(shared, arguments...) is a kernel's
+// body, box y of the grid's second dimension takes the arguments of boxes.a[y].
+// GROUP_MOST boxes' arguments (up to 240 bytes each) fit a launch's 4 KB.
+// ---------------------------------------------------------------------------
+constexpr int GROUP_MOST = 16;
+
+template <class... A>
+struct Pack {};
+template <class H, class... T>
+struct Pack<H, T...> {
+    H head;
+    Pack<T...> tail;
+};
+
+template <class... A>
+struct Boxes {
+    Pack<A...> a[GROUP_MOST];
+};
+
+template <class Body, class... Done>
+__device__ __forceinline__ void spread(const Pack<> &, const Done &...d) {
+    Body::run(d...);
+}
+template <class Body, class H, class... T, class... Done>
+__device__ __forceinline__ void spread(const Pack<H, T...> &p, const Done &...d) {
+    spread<Body>(p.tail, d..., p.head);
+}
+
+template <class Body, int THREADS, class S, class... A>
+__global__ void __launch_bounds__(THREADS) group_kernel(Boxes<A...> boxes, S shared) {
+    spread<Body>(boxes.a[blockIdx.y], shared);
+}
+
+inline void pack(Pack<> &) {}
+template <class H, class... T>
+inline void pack(Pack<H, T...> &p, const H &h, const T &...t) {
+    p.head = h;
+    pack(p.tail, t...);
+}
+
+template <class Body, int THREADS, class S, class... A>
+inline void launch_group(hf_ctx *ctx, int kid, unsigned blocks, int count, const Boxes<A...> &boxes, const S &shared) {
+    static_assert(sizeof(Boxes<A...>) + sizeof(S) <= 4096, "kernel arguments");
+    HF_LAUNCH(ctx, kid, (group_kernel<Body, THREADS, S, A...>), dim3(blocks ? blocks : 1u, unsigned(count)),
+              dim3(THREADS), 0, ctx->stream, boxes, shared);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,6 +1,8 @@
 // Steps 2-6 of one box in a single native call (Sec. 2, identification steps).
 #include "hf_internal.h"
 
+#include <algorithm>
+
 using namespace hf;
 
 extern "C" hf_status hf_find_halos(hf_ctx *ctx, const hf_box *box, const hf_job *job, void *ws, size_t ws_bytes) {
@@ -152,7 +154,8 @@ extern "C" hf_status hf_find_halos_scales_ws_size(const hf_box *box, int64_t np,
 extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const void *pos, hf_dtype dtype, int64_t np,
                                           hf_kernel kernel, float tau, int64_t *rho, int32_t count,
                                           const hf_scale_job *scales, void *ws, size_t ws_bytes) {
-    if (!ctx || !rho || !scales || count < 1 || count > HF_CWT_BATCH_MAX || np < 0 || (np > 0 && !pos)) return HF_ERR_ARG;
+    if (!ctx || !rho || !scales || count < 1 || count > HF_CWT_BATCH_MAX || np < 0 || (np > 0 && !pos))
+        return HF_ERR_ARG;
     if ((dtype != HF_F32 && dtype != HF_F64) || (kernel != HF_KERNEL_SAMPLED && kernel != HF_KERNEL_ANALYTIC) ||
         tau != tau)
         return HF_ERR_ARG;
@@ -355,7 +358,8 @@ hf_status grids_layout(double box_len, int32_t frac_bits, int64_t np, int32_t co
         if (s != HF_OK) return s;
         if (scales[j].max_cap < 0) return HF_ERR_ARG;
         size_t need = 0;
-        s = stage_ws_size(&b, np, HF_STAGE_DEPOSIT | HF_STAGE_STENCIL | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, least, &need);
+        s = stage_ws_size(&b, np, HF_STAGE_DEPOSIT | HF_STAGE_STENCIL | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, least,
+                          &need);
         if (s != HF_OK) return s;
         shared = need > shared ? need : shared;
         if (with_vel) {  // steps 9-10 reuse the stage region once every scale's stages are done
@@ -395,8 +399,11 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
     if (with_vel && (!(grav_mass > 0.0) || !(grav_mass < 1e300))) return HF_ERR_ARG;
     GridsLayout L{};
     hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, false, L);
-    if (s == HF_OK && ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, true, L);
-    if (s == HF_OK && ws_bytes < L.total) s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, false, true, L);
+    // less than asked for: without the optional deposit regions, then without the members' records
+    if (s == HF_OK && ws_bytes < L.total)
+        s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, true, true, L);
+    if (s == HF_OK && ws_bytes < L.total)
+        s = grids_layout(box_len, frac_bits, np, count, scales, with_vel, false, true, L);
     if (s != HF_OK) return s;
     int32_t hw[HF_CWT_BATCH_MAX];
     for (int j = 0; j < count; ++j) {
@@ -438,7 +445,7 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
         if (s == HF_OK) s = hf_label(ctx, &b, pos, dtype, np, sj.cell_label, sj.particle_label);
         if (s == HF_OK) s = groups_count_cells(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, sj.cell_label, g);
         if (s == HF_OK && sj.max_cap > 0) s = 
-            s = groups_count_particles(ctx, b, sj.particle_label, np, g, halo_scale, w0, sb);  // the stage region is free
+            s = groups_count_particles(ctx, b, sj.particle_label, np, g, halo_scale, w0, sb);  // a free region
         if (s == HF_OK)
             s = groups_decide(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, g, dens_th, np, particle_th, pass,
                               sj.group_particles, sj.group_cells, sj.group_keep);
@@ -454,21 +461,59 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
     return s;
 }
 
-// A group of same-n boxes: per-box deposits, one batched transform for all of
-// them, then per-box maxima, segmentation and labels, in that order on the
-// context's stream.
+namespace {
+// Whether no box writes memory that another one uses, so that their stages may run
+// side by side (box by box, a workspace or an output may serve several in turn).
+bool apart(int n, int count, const GroupBox *b, size_t item, const size_t *ws_need) {
+    struct Span {
+        uintptr_t begin, end;
+        int box;
+        bool write;
+    };
+    Span v[8 * HF_CWT_BATCH_MAX];
+    int m = 0;
+    const size_t cells = size_t(n) * n * n;
+    for (int j = 0; j < count; ++j) {
+        const GroupBox &x = b[j];
+        auto add = [&](const void *p, size_t bytes, bool write) {
+            if (p && bytes) v[m++] = Span{uintptr_t(p), uintptr_t(p) + bytes, j, write};
+        };
+        add(x.pos, size_t(x.np) * 3 * item, false);
+        add(x.rho, 8 * cells, true);
+        add(x.cwt, 4 * cells, true);
+        add(x.max_idx, 4 * size_t(x.max_cap), true);
+        add(x.d_count, 8, true);
+        add(x.cell_label, 4 * cells, true);
+        add(x.particle_label, 4 * size_t(x.np), true);
+        add(x.ws, ws_need[j], true);
+    }
+    std::sort(v, v + m, [](const Span &a, const Span &c) { return a.begin < c.begin; });
+    for (int i = 0; i < m; ++i)
+        for (int k = i + 1; k < m && v[k].begin < v[i].end; ++k)
+            if (v[i].box != v[k].box && (v[i].write || v[k].write)) return false;
+    return true;
+}
+}  // namespace
+
+// A group of same-n boxes: the deposits, one batched transform for all of them,
+// then maxima, segmentation and labels, in that order on the context's stream.
+// Small boxes of one type go through every stage together (GroupBox), up to
+// GROUP_MOST at a time: box by box, one launch after the other with a tenth of the
+// device at work, twelve boxes of 96^3 took 1611 us, 566 together.
 extern "C" hf_status hf_find_halos_group(hf_ctx *ctx, int32_t n, int32_t frac_bits, int32_t count,
                                          const hf_group_item *items, hf_kernel kernel, void *cwt_ws,
                                          size_t cwt_ws_bytes) {
     if (!ctx || !items || count < 1 || count > HF_CWT_BATCH_MAX) return HF_ERR_ARG;
     if (kernel != HF_KERNEL_SAMPLED && kernel != HF_KERNEL_ANALYTIC) return HF_ERR_ARG;
     hf_cwt_item cw[HF_CWT_BATCH_MAX];
+    size_t ws_need[HF_CWT_BATCH_MAX];
     for (int j = 0; j < count; ++j) {
         const hf_job &job = items[j].job;
         const hf_box box{n, frac_bits, items[j].box_len};
         hf_status s = check_box(&box);
         if (s != HF_OK) return s;
-        size_t need = 0;
+        size_t &need = ws_need[j];
+        need = 0;
         s = stage_ws_size(&box, job.np, HF_STAGE_DEPOSIT | HF_STAGE_MAXIMA | HF_STAGE_SEGMENT, true, &need);
         if (s != HF_OK) return s;
         s = check_ws(items[j].ws, items[j].ws_bytes, need);
@@ -485,21 +530,45 @@ extern "C" hf_status hf_find_halos_group(hf_ctx *ctx, int32_t n, int32_t frac_bi
     if (s != HF_OK) return s;
     s = check_ws(cwt_ws, cwt_ws_bytes, need);
     if (s != HF_OK) return s;
+    bool together = count > 1 && segment_group_supported(n);
+    GroupBox boxes[HF_CWT_BATCH_MAX];
     for (int j = 0; j < count; ++j) {
         const hf_job &job = items[j].job;
-        const hf_box box{n, frac_bits, items[j].box_len};
-        s = hf_deposit(ctx, &box, job.pos, job.dtype, job.np, job.rho, items[j].ws, items[j].ws_bytes);
+        together = together && job.dtype == items[0].job.dtype;
+        boxes[j] = GroupBox{job.pos, job.np, items[j].box_len, job.rho, job.cwt, job.tau, job.max_idx, job.max_cap,
+                            job.d_count, job.cell_label, job.particle_label, static_cast<char *>(items[j].ws)};
+    }
+    const hf_dtype dtype = items[0].job.dtype;
+    together = together && deposit_group_supported(n, frac_bits, count, boxes) &&
+               apart(n, count, boxes, dtype == HF_F32 ? sizeof(float) : sizeof(double), ws_need);
+    if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
+    for (int j = 0; j < count; ++j) {
+        if (together) {
+            if (j % GROUP_MOST) continue;
+            s = deposit_group(ctx, n, frac_bits, dtype, count - j < GROUP_MOST ? count - j : GROUP_MOST, boxes + j);
+        } else {
+            const hf_job &job = items[j].job;
+            const hf_box box{n, frac_bits, items[j].box_len};
+            s = hf_deposit(ctx, &box, job.pos, job.dtype, job.np, job.rho, items[j].ws, items[j].ws_bytes);
+        }
         if (s != HF_OK) return s;
     }
     s = hf_cwt_batch(ctx, n, count, cw, kernel, cwt_ws, cwt_ws_bytes);
     if (s != HF_OK) return s;
     for (int j = 0; j < count; ++j) {
-        const hf_job &job = items[j].job;
-        const hf_box box{n, frac_bits, items[j].box_len};
-        s = maxima_segment(ctx, box, job.cwt, job.tau, job.max_idx, job.max_cap, job.d_count, job.cell_label,
-                           items[j].ws, items[j].ws_bytes);
-        if (s != HF_OK) return s;
-        s = hf_label(ctx, &box, job.pos, job.dtype, job.np, job.cell_label, job.particle_label);
+        if (together) {
+            if (j % GROUP_MOST) continue;
+            const int some = count - j < GROUP_MOST ? count - j : GROUP_MOST;
+            s = segment_group(ctx, n, some, boxes + j);
+            if (s == HF_OK) s = label_group(ctx, n, frac_bits, dtype, some, boxes + j);
+        } else {
+            const hf_job &job = items[j].job;
+            const hf_box box{n, frac_bits, items[j].box_len};
+            s = maxima_segment(ctx, box, job.cwt, job.tau, job.max_idx, job.max_cap, job.d_count, job.cell_label,
+                               items[j].ws, items[j].ws_bytes);
+            if (s == HF_OK)
+                s = hf_label(ctx, &box, job.pos, job.dtype, job.np, job.cell_label, job.particle_label);
+        }
         if (s != HF_OK) return s;
     }
     return HF_OK;

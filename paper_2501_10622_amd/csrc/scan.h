@@ -1,6 +1,6 @@
 // Exclusive scan of n uint32 counts, short ones by one workgroup
-// (one_scan_kernel), others in two launches over many workgroups, in a fixed order (no atomics), for the offset tables of the partition and list
-// passes:
+// (one_scan_kernel), others in two launches over many workgroups, in a fixed
+// order (no atomics), for the offset tables of the partition and list passes:
 //   seg_reduce_kernel: workgroup g sums the values [g S, min(n, (g+1) S)) into
 //                      partial[g];
 //   seg_scan_kernel:   workgroup g adds partial[0 .. g) and scans its segment.
@@ -127,47 +127,54 @@ constexpr int SCAN_PER = 8;
 constexpr int SCAN_SMALL = SCAN_THREADS * SCAN_PER;
 
 template <int TAG>
+struct OneScan {
+    static __device__ __forceinline__ void run(int, ScanJob j) {
+        __shared__ uint32_t wsum[SCAN_THREADS / 64];
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int n = int(j.n), len = int(scan_len(j));
+        const int per = (n + SCAN_THREADS - 1) / SCAN_THREADS;
+        const int lo = int(threadIdx.x) * per;
+        uint32_t v[SCAN_PER], sum = 0;
+#pragma unroll
+        for (int k = 0; k < SCAN_PER; ++k) {
+            v[k] = k < per && lo + k < len ? j.in[lo + k] : 0u;
+            sum += v[k];
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += y;
+        }
+        if (lane == 63) wsum[wave] = inc;
+        __syncthreads();
+        uint32_t e = inc - sum;
+        uint64_t total = 0;
+        for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+            e += w < wave ? wsum[w] : 0u;
+            total += wsum[w];
+        }
+#pragma unroll
+        for (int k = 0; k < SCAN_PER; ++k) {
+            if (k < per && lo + k < n) {
+                j.out[lo + k] = e;
+                if (j.out2) j.out2[lo + k] = e;
+            }
+            e += v[k];
+        }
+        if (threadIdx.x == 0) {
+            j.out[n] = uint32_t(total);
+            if (j.total64) {
+                *j.total64 = int64_t(total);
+                if (int64_t(total) > j.cap) atomicOr(j.status, hf::ST_CAPACITY);
+            }
+        }
+    }
+};
+
+template <int TAG>
 __global__ void __launch_bounds__(SCAN_THREADS) one_scan_kernel(ScanJob j) {
-    __shared__ uint32_t wsum[SCAN_THREADS / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = int(j.n), len = int(scan_len(j));
-    const int per = (n + SCAN_THREADS - 1) / SCAN_THREADS;
-    const int lo = int(threadIdx.x) * per;
-    uint32_t v[SCAN_PER], sum = 0;
-#pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-        v[k] = k < per && lo + k < len ? j.in[lo + k] : 0u;
-        sum += v[k];
-    }
-    uint32_t inc = sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += y;
-    }
-    if (lane == 63) wsum[wave] = inc;
-    __syncthreads();
-    uint32_t e = inc - sum;
-    uint64_t total = 0;
-    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
-        e += w < wave ? wsum[w] : 0u;
-        total += wsum[w];
-    }
-#pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-        if (k < per && lo + k < n) {
-            j.out[lo + k] = e;
-            if (j.out2) j.out2[lo + k] = e;
-        }
-        e += v[k];
-    }
-    if (threadIdx.x == 0) {
-        j.out[n] = uint32_t(total);
-        if (j.total64) {
-            *j.total64 = int64_t(total);
-            if (int64_t(total) > j.cap) atomicOr(j.status, hf::ST_CAPACITY);
-        }
-    }
+    OneScan<TAG>::run(0, j);
 }
 
 // Enqueues the scan.

@@ -172,211 +172,219 @@ constexpr int CHASE_FLAGS = 8;  // one per round of the boundary chase, at most 
 constexpr int COLUMN_WORDS = RZ / 8;
 
 template <bool FULL, bool CHAINS>
-__global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float *__restrict__ c, TileGrid rg,
-                                                                    uint32_t tau_ord, uint4 *__restrict__ ptr,
-                                                                    int32_t *__restrict__ bnd,
-                                                                    uint32_t *__restrict__ mask,
-                                                                    uint32_t *__restrict__ flags, uint32_t *status) {
-    __shared__ uint32_t V[RHCELLS + 1];
-    __shared__ uint32_t rowbase[RHY * RHZ];  // index of the first cell of each halo row's grid row
-    if (CHAINS && blockIdx.x == 0 && threadIdx.x < CHASE_FLAGS) flags[threadIdx.x] = 0u;  // of the chase that follows
-    int x0, y0, z0;
-    const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
-    rtile_origin(rg, int(tile), x0, y0, z0);
-    const int n = rg.n;
-    const uint32_t un = uint32_t(n);
-    // a tile at the far end of an axis is short where n is not a multiple of
-    // the tile: its cells past n are absent (never pointed to, never written)
-    const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
-              wz = FULL ? RZ : tile_extent(z0, RZ, n);
-    const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
-    if (tid < RHY * RHZ) {
-        const int hy = tid % RHY, hz = tid / RHY;
-        const bool there = FULL || (hy <= wy + 1 && hz <= wz + 1);
-        rowbase[tid] = there ? (wrap(z0 + hz - 1, n) * un + wrap(y0 + hy - 1, n)) * un : 0u;
-    }
-    __syncthreads();
-    bool nan = false;
-    {
-        // all loads of the halo tile are issued before any is used: the rows'
-        // inner columns, 32 lanes to a row, then their two ends
-        constexpr int ROWS = RHY * RHZ, STEP = PR_THREADS / RX, LOADS = (ROWS + STEP - 1) / STEP;
-        constexpr int ENDS = (2 * ROWS + PR_THREADS - 1) / PR_THREADS;
-        float v[LOADS], w[ENDS];
-        // (past a short tile's shell any cell will do: nothing looks there)
-        const uint32_t gx = FULL ? uint32_t(x0 + x) : (x <= wx ? wrap(x0 + x, n) : 0u);
-        const uint32_t ends[2] = {wrap(x0 - 1, n), FULL || wx == RX ? wrap(x0 + RX, n) : 0u};
-#pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int r = y + i * STEP;
-            if (r < ROWS) v[i] = c[rowbase[r] + gx];
+struct ParentResolve {
+    static __device__ __forceinline__ void run(TileGrid rg, const float *__restrict__ c, uint32_t tau_ord,
+                                               uint4 *__restrict__ ptr, int32_t *__restrict__ bnd,
+                                               uint32_t *__restrict__ mask, uint32_t *__restrict__ flags,
+                                               uint32_t *status) {
+        __shared__ uint32_t V[RHCELLS + 1];
+        __shared__ uint32_t rowbase[RHY * RHZ];  // index of the first cell of each halo row's grid row
+        if (CHAINS && blockIdx.x == 0 && threadIdx.x < CHASE_FLAGS) flags[threadIdx.x] = 0u;  // of the chase that follows
+        int x0, y0, z0;
+        const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
+        rtile_origin(rg, int(tile), x0, y0, z0);
+        const int n = rg.n;
+        const uint32_t un = uint32_t(n);
+        // a tile at the far end of an axis is short where n is not a multiple of
+        // the tile: its cells past n are absent (never pointed to, never written)
+        const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
+                  wz = FULL ? RZ : tile_extent(z0, RZ, n);
+        const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
+        if (tid < RHY * RHZ) {
+            const int hy = tid % RHY, hz = tid / RHY;
+            const bool there = FULL || (hy <= wy + 1 && hz <= wz + 1);
+            rowbase[tid] = there ? (wrap(z0 + hz - 1, n) * un + wrap(y0 + hy - 1, n)) * un : 0u;
         }
+        __syncthreads();
+        bool nan = false;
+        {
+            // all loads of the halo tile are issued before any is used: the rows'
+            // inner columns, 32 lanes to a row, then their two ends
+            constexpr int ROWS = RHY * RHZ, STEP = PR_THREADS / RX, LOADS = (ROWS + STEP - 1) / STEP;
+            constexpr int ENDS = (2 * ROWS + PR_THREADS - 1) / PR_THREADS;
+            float v[LOADS], w[ENDS];
+            // (past a short tile's shell any cell will do: nothing looks there)
+            const uint32_t gx = FULL ? uint32_t(x0 + x) : (x <= wx ? wrap(x0 + x, n) : 0u);
+            const uint32_t ends[2] = {wrap(x0 - 1, n), FULL || wx == RX ? wrap(x0 + RX, n) : 0u};
 #pragma unroll
-        for (int i = 0; i < ENDS; ++i) {
-            const int e = tid + i * PR_THREADS;
-            if (e < 2 * ROWS) w[i] = c[rowbase[e >> 1] + ends[e & 1]];
+            for (int i = 0; i < LOADS; ++i) {
+                const int r = y + i * STEP;
+                if (r < ROWS) v[i] = c[rowbase[r] + gx];
+            }
+#pragma unroll
+            for (int i = 0; i < ENDS; ++i) {
+                const int e = tid + i * PR_THREADS;
+                if (e < 2 * ROWS) w[i] = c[rowbase[e >> 1] + ends[e & 1]];
+            }
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int r = y + i * STEP;
+                if (r < ROWS) V[r * RHX + x + 1] = ordered_bits(v[i], nan);
+            }
+#pragma unroll
+            for (int i = 0; i < ENDS; ++i) {
+                const int e = tid + i * PR_THREADS;
+                if (e < 2 * ROWS) V[(e >> 1) * RHX + (e & 1) * (RHX - 1)] = ordered_bits(w[i], nan);
+            }
         }
+        __syncthreads();
+        char *const lds = reinterpret_cast<char *>(V);
+        auto at = [lds](uint32_t a) { return reinterpret_cast<uint32_t *>(lds + a); };
+        // addresses in halo plane 0 of the columns around (x, y), in the order of
+        // their linear indices: of rows y - 1, y, y + 1 and columns x - 1, x, x + 1 the
+        // one beyond the end of the box comes last or first
+        const uint32_t own = 4u * uint32_t((y + 1) * RHX + x + 1);
+        uint32_t a[9];
+        {
+            const int xr = x0 + x == 0 ? 1 : (x0 + x == n - 1 ? 2 : 0), yr = y0 + y == 0 ? 1 : (y0 + y == n - 1 ? 2 : 0);
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int r = y + i * STEP;
-            if (r < ROWS) V[r * RHX + x + 1] = ordered_bits(v[i], nan);
+            for (int k = 0; k < 9; ++k) {
+                const int dy = (k / 3 + yr) % 3 - 1, dx = (k % 3 + xr) % 3 - 1;
+                a[k] = own + uint32_t(4 * (dy * RHX + dx));
+            }
         }
+        // value and address of the largest key of halo plane hz around the column
+        auto plane_arg = [&](int hz, uint32_t &bv, uint32_t &ba) {
+            bv = *at(a[0] + uint32_t(hz * PLANE_BYTES));
+            ba = a[0];
 #pragma unroll
-        for (int i = 0; i < ENDS; ++i) {
-            const int e = tid + i * PR_THREADS;
-            if (e < 2 * ROWS) V[(e >> 1) * RHX + (e & 1) * (RHX - 1)] = ordered_bits(w[i], nan);
-        }
-    }
-    __syncthreads();
-    char *const lds = reinterpret_cast<char *>(V);
-    auto at = [lds](uint32_t a) { return reinterpret_cast<uint32_t *>(lds + a); };
-    // addresses in halo plane 0 of the columns around (x, y), in the order of
-    // their linear indices: of rows y - 1, y, y + 1 and columns x - 1, x, x + 1 the
-    // one beyond the end of the box comes last or first
-    const uint32_t own = 4u * uint32_t((y + 1) * RHX + x + 1);
-    uint32_t a[9];
-    {
-        const int xr = x0 + x == 0 ? 1 : (x0 + x == n - 1 ? 2 : 0), yr = y0 + y == 0 ? 1 : (y0 + y == n - 1 ? 2 : 0);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int dy = (k / 3 + yr) % 3 - 1, dx = (k % 3 + xr) % 3 - 1;
-            a[k] = own + uint32_t(4 * (dy * RHX + dx));
-        }
-    }
-    // value and address of the largest key of halo plane hz around the column
-    auto plane_arg = [&](int hz, uint32_t &bv, uint32_t &ba) {
-        bv = *at(a[0] + uint32_t(hz * PLANE_BYTES));
-        ba = a[0];
-#pragma unroll
-        for (int k = 1; k < 9; ++k) {
-            const uint32_t v = *at(a[k] + uint32_t(hz * PLANE_BYTES));
+            for (int k = 1; k < 9; ++k) {
+                const uint32_t v = *at(a[k] + uint32_t(hz * PLANE_BYTES));
+                const bool up = v >= bv;
+                bv = up ? v : bv;
+                ba = up ? a[k] : ba;
+            }
+            ba += uint32_t(hz * PLANE_BYTES);
+        };
+        auto larger = [](uint32_t &bv, uint32_t &ba, uint32_t v, uint32_t va) {
             const bool up = v >= bv;
             bv = up ? v : bv;
-            ba = up ? a[k] : ba;
-        }
-        ba += uint32_t(hz * PLANE_BYTES);
-    };
-    auto larger = [](uint32_t &bv, uint32_t &ba, uint32_t v, uint32_t va) {
-        const bool up = v >= bv;
-        bv = up ? v : bv;
-        ba = up ? va : ba;
-    };
-    const bool column = FULL || (x < wx && y < wy);
-    uint32_t l[RZ];
-    uint32_t maxima = 0;  // of the column
-    {
-        uint32_t v0, p0, v1, p1;
-        plane_arg(0, v0, p0);
-        plane_arg(1, v1, p1);
+            ba = up ? va : ba;
+        };
+        const bool column = FULL || (x < wx && y < wy);
+        uint32_t l[RZ];
+        uint32_t maxima = 0;  // of the column
+        {
+            uint32_t v0, p0, v1, p1;
+            plane_arg(0, v0, p0);
+            plane_arg(1, v1, p1);
 #pragma unroll
-        for (int z = 0; z < RZ; ++z) {
-            uint32_t v2, p2, bv, ba;
-            plane_arg(z + 2, v2, p2);
-            if (z0 + z == 0) {  // plane z - 1 is the last of the box
-                bv = v1;
-                ba = p1;
-                larger(bv, ba, v2, p2);
-                larger(bv, ba, v0, p0);
-            } else if (z0 + z == n - 1) {  // plane z + 1 is the first
-                bv = v2;
-                ba = p2;
-                larger(bv, ba, v0, p0);
-                larger(bv, ba, v1, p1);
-            } else {
-                bv = v0;
-                ba = p0;
-                larger(bv, ba, v1, p1);
-                larger(bv, ba, v2, p2);
-            }
-            const bool self = ba == own + uint32_t((z + 1) * PLANE_BYTES);
-            const bool high = bv > tau_ord;
-            if (FULL && mask) {  // a wavefront covers rows y and y + 1: two aligned mask words
-                const unsigned long long bits = __ballot(self && high);
-                if ((tid & 63) == 0) {
-                    const uint32_t g = (uint32_t(z0 + z) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-                    mask[g >> 5] = uint32_t(bits);
-                    mask[(g + un) >> 5] = uint32_t(bits >> 32);
+            for (int z = 0; z < RZ; ++z) {
+                uint32_t v2, p2, bv, ba;
+                plane_arg(z + 2, v2, p2);
+                if (z0 + z == 0) {  // plane z - 1 is the last of the box
+                    bv = v1;
+                    ba = p1;
+                    larger(bv, ba, v2, p2);
+                    larger(bv, ba, v0, p0);
+                } else if (z0 + z == n - 1) {  // plane z + 1 is the first
+                    bv = v2;
+                    ba = p2;
+                    larger(bv, ba, v0, p0);
+                    larger(bv, ba, v1, p1);
+                } else {
+                    bv = v0;
+                    ba = p0;
+                    larger(bv, ba, v1, p1);
+                    larger(bv, ba, v2, p2);
                 }
+                const bool self = ba == own + uint32_t((z + 1) * PLANE_BYTES);
+                const bool high = bv > tau_ord;
+                if (FULL && mask) {  // a wavefront covers rows y and y + 1: two aligned mask words
+                    const unsigned long long bits = __ballot(self && high);
+                    if ((tid & 63) == 0) {
+                        const uint32_t g = (uint32_t(z0 + z) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+                        mask[g >> 5] = uint32_t(bits);
+                        mask[(g + un) >> 5] = uint32_t(bits >> 32);
+                    }
+                }
+                maxima |= self && high ? 1u << z : 0u;
+                l[z] = self && !high ? NONE : ba;
+                v0 = v1;
+                p0 = p1;
+                v1 = v2;
+                p1 = p2;
             }
-            maxima |= self && high ? 1u << z : 0u;
-            l[z] = self && !high ? NONE : ba;
-            v0 = v1;
-            p0 = p1;
-            v1 = v2;
-            p1 = p2;
         }
-    }
-    if (nan) atomicOr(status, ST_INPUT);
-    if (!FULL && mask && column) {  // rows straddle words: the mask was cleared first
-        const uint32_t g = (uint32_t(z0) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-        for (int z = 0; z < wz; ++z) {
-            const uint32_t gz = g + uint32_t(z) * un * un;
-            if (maxima >> z & 1u) atomicOr(&mask[gz >> 5], 1u << (gz & 31u));
+        if (nan) atomicOr(status, ST_INPUT);
+        if (!FULL && mask && column) {  // rows straddle words: the mask was cleared first
+            const uint32_t g = (uint32_t(z0) * un + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+            for (int z = 0; z < wz; ++z) {
+                const uint32_t gz = g + uint32_t(z) * un * un;
+                if (maxima >> z & 1u) atomicOr(&mask[gz >> 5], 1u << (gz & 31u));
+            }
         }
-    }
-    if (!CHAINS) return;
-    __syncthreads();  // every read of the field is done
-    for (uint32_t e = tid; e <= uint32_t(RHCELLS); e += PR_THREADS) V[e] = 4u * e;
-    __syncthreads();
-    // where the column's pointers are; an absent cell's goes to NONE, which it holds
-    auto slot = [=](int z) {
-        return FULL || (column && z < wz) ? own + uint32_t((z + 1) * PLANE_BYTES) : NONE;
-    };
-#pragma unroll
-    for (int z = 0; z < RZ; ++z) {
-        if (!FULL && slot(z) == NONE) l[z] = NONE;
-        *at(slot(z)) = l[z];
-    }
-    __syncthreads();
-    // (relaxed atomic accesses: other wavefronts write while this one reads)
-    bool open = true;
-    while (open) {
-        uint32_t w[RZ];
-        uint32_t moved = 0;
-#pragma unroll
-        for (int z = 0; z < RZ; ++z) w[z] = __hip_atomic_load(at(l[z]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (!CHAINS) return;
+        __syncthreads();  // every read of the field is done
+        for (uint32_t e = tid; e <= uint32_t(RHCELLS); e += PR_THREADS) V[e] = 4u * e;
+        __syncthreads();
+        // where the column's pointers are; an absent cell's goes to NONE, which it holds
+        auto slot = [=](int z) {
+            return FULL || (column && z < wz) ? own + uint32_t((z + 1) * PLANE_BYTES) : NONE;
+        };
 #pragma unroll
         for (int z = 0; z < RZ; ++z) {
-            moved |= w[z] ^ l[z];
-            l[z] = w[z];
+            if (!FULL && slot(z) == NONE) l[z] = NONE;
+            *at(slot(z)) = l[z];
         }
-#pragma unroll
-        for (int z = 0; z < RZ; ++z)
-            __hip_atomic_store(at(slot(z)), w[z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        open = __any(moved != 0u);
-    }
-    uint4 *out = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
-#pragma unroll
-    for (int q = 0; q < COLUMN_WORDS; ++q)
-        out[q] = make_uint4(l[8 * q] | (l[8 * q + 1] << 16), l[8 * q + 2] | (l[8 * q + 3] << 16),
-                            l[8 * q + 4] | (l[8 * q + 5] << 16), l[8 * q + 6] | (l[8 * q + 7] << 16));
-    if (!FULL && !(wx == RX && wy == RY && wz == RZ)) {
-        // a short tile leaves some of its boundary slots unused: they hold -1
-        // (final), so that the chase, which visits every slot, reads no
-        // stale entry
-        for (int k = tid; k < NBND; k += PR_THREADS) bnd[int64_t(tile) * NBND + k] = -1;
         __syncthreads();
-    }
-    if (!column) return;
-    // index of the cell at address p
-    auto cell_at = [&](uint32_t p) {
-        if (p == NONE) return -1;
-        const uint32_t r = p / (4u * RHX), hx = p / 4u - r * RHX;
-        return int32_t(rowbase[r] + wrap(x0 + int(hx) - 1, n));
-    };
-    const int bx = x == wx - 1 ? RX - 1 : x, by = y == wy - 1 ? RY - 1 : y;  // a short tile's far edge: bnd_rank_in
-    int32_t *mine = bnd + int64_t(tile) * NBND;
-    const int ring = bnd_rank(bx, by, 1);  // of plane 1; later inner planes' ranks follow at equal distances
+        // (relaxed atomic accesses: other wavefronts write while this one reads)
+        bool open = true;
+        while (open) {
+            uint32_t w[RZ];
+            uint32_t moved = 0;
 #pragma unroll
-    for (int z = 0; z < RZ; ++z) {
-        if (!FULL && z >= wz) continue;
-        if (z == wz - 1)
-            mine[bnd_rank(bx, by, RZ - 1)] = cell_at(l[z]);
-        else if (z == 0)
-            mine[bnd_rank(bx, by, 0)] = cell_at(l[z]);
-        else if (ring >= 0)
-            mine[ring + (z - 1) * RING] = cell_at(l[z]);
+            for (int z = 0; z < RZ; ++z) w[z] = __hip_atomic_load(at(l[z]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int z = 0; z < RZ; ++z) {
+                moved |= w[z] ^ l[z];
+                l[z] = w[z];
+            }
+#pragma unroll
+            for (int z = 0; z < RZ; ++z)
+                __hip_atomic_store(at(slot(z)), w[z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            open = __any(moved != 0u);
+        }
+        uint4 *out = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
+#pragma unroll
+        for (int q = 0; q < COLUMN_WORDS; ++q)
+            out[q] = make_uint4(l[8 * q] | (l[8 * q + 1] << 16), l[8 * q + 2] | (l[8 * q + 3] << 16),
+                                l[8 * q + 4] | (l[8 * q + 5] << 16), l[8 * q + 6] | (l[8 * q + 7] << 16));
+        if (!FULL && !(wx == RX && wy == RY && wz == RZ)) {
+            // a short tile leaves some of its boundary slots unused: they hold -1
+            // (final), so that the chase, which visits every slot, reads no
+            // stale entry
+            for (int k = tid; k < NBND; k += PR_THREADS) bnd[int64_t(tile) * NBND + k] = -1;
+            __syncthreads();
+        }
+        if (!column) return;
+        // index of the cell at address p
+        auto cell_at = [&](uint32_t p) {
+            if (p == NONE) return -1;
+            const uint32_t r = p / (4u * RHX), hx = p / 4u - r * RHX;
+            return int32_t(rowbase[r] + wrap(x0 + int(hx) - 1, n));
+        };
+        const int bx = x == wx - 1 ? RX - 1 : x, by = y == wy - 1 ? RY - 1 : y;  // a short tile's far edge: bnd_rank_in
+        int32_t *mine = bnd + int64_t(tile) * NBND;
+        const int ring = bnd_rank(bx, by, 1);  // of plane 1; later inner planes' ranks follow at equal distances
+#pragma unroll
+        for (int z = 0; z < RZ; ++z) {
+            if (!FULL && z >= wz) continue;
+            if (z == wz - 1)
+                mine[bnd_rank(bx, by, RZ - 1)] = cell_at(l[z]);
+            else if (z == 0)
+                mine[bnd_rank(bx, by, 0)] = cell_at(l[z]);
+            else if (ring >= 0)
+                mine[ring + (z - 1) * RING] = cell_at(l[z]);
+        }
     }
+};
+
+template <bool FULL, bool CHAINS>
+__global__ void __launch_bounds__(PR_THREADS) parent_resolve_kernel(const float *__restrict__ c, TileGrid rg,
+                    uint32_t tau_ord, uint4 *__restrict__ ptr, int32_t *__restrict__ bnd, uint32_t *__restrict__ mask,
+                    uint32_t *__restrict__ flags, uint32_t *status) {
+    ParentResolve<FULL, CHAINS>::run(rg, c, tau_ord, ptr, bnd, mask, flags, status);
 }
 
 __global__ void zero_words_kernel(uint32_t *w, int64_t count) {
@@ -418,49 +426,56 @@ __device__ int32_t follow(const int32_t *__restrict__ bnd, const TileGrid &tg, i
 }
 
 template <bool FULL>
-__global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t count, TileGrid tg, uint32_t *flags,
-                                                        int round) {
-    if (round > 0 && flags[round] == 0u) return;
-    bool open = false;
-    const int64_t step = int64_t(gridDim.x) * blockDim.x * BATCH;
-    for (int64_t k0 = blockIdx.x * int64_t(blockDim.x) * BATCH + threadIdx.x; k0 < count; k0 += step) {
-        int32_t p0[BATCH], p[BATCH];
-        bool on[BATCH];
-        bool any = false;
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t k = k0 + int64_t(i) * blockDim.x;
-            p0[i] = k < count ? bnd[k] : -1;
-        }
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            p[i] = p0[i];
-            on[i] = p[i] >= 0;
-            any |= on[i];
-        }
-        for (int hop = 0; any && hop < CHASE_HOPS; ++hop) {
-            int32_t q[BATCH];
+struct BndChase {
+    static __device__ __forceinline__ void run(TileGrid tg, int32_t *bnd, int64_t count, uint32_t *flags, int round) {
+        if (round > 0 && flags[round] == 0u) return;
+        bool open = false;
+        const int64_t step = int64_t(gridDim.x) * blockDim.x * BATCH;
+        for (int64_t k0 = blockIdx.x * int64_t(blockDim.x) * BATCH + threadIdx.x; k0 < count; k0 += step) {
+            int32_t p0[BATCH], p[BATCH];
+            bool on[BATCH];
+            bool any = false;
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                const int64_t s = on[i] ? bnd_slot<FULL>(tg, p[i]) : -1;
-                q[i] = s >= 0 ? bnd[s] : p[i];
+                const int64_t k = k0 + int64_t(i) * blockDim.x;
+                p0[i] = k < count ? bnd[k] : -1;
             }
-            any = false;
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                on[i] = q[i] != p[i] && q[i] >= 0;
-                p[i] = q[i];
+                p[i] = p0[i];
+                on[i] = p[i] >= 0;
                 any |= on[i];
             }
-        }
-        open |= any;
+            for (int hop = 0; any && hop < CHASE_HOPS; ++hop) {
+                int32_t q[BATCH];
 #pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const int64_t k = k0 + int64_t(i) * blockDim.x;
-            if (p[i] != p0[i]) bnd[k] = p[i];
+                for (int i = 0; i < BATCH; ++i) {
+                    const int64_t s = on[i] ? bnd_slot<FULL>(tg, p[i]) : -1;
+                    q[i] = s >= 0 ? bnd[s] : p[i];
+                }
+                any = false;
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) {
+                    on[i] = q[i] != p[i] && q[i] >= 0;
+                    p[i] = q[i];
+                    any |= on[i];
+                }
+            }
+            open |= any;
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int64_t k = k0 + int64_t(i) * blockDim.x;
+                if (p[i] != p0[i]) bnd[k] = p[i];
+            }
         }
+        if (__ballot(open) && (threadIdx.x & 63) == 0) flags[round + 1] = 1u;
     }
-    if (__ballot(open) && (threadIdx.x & 63) == 0) flags[round + 1] = 1u;
+};
+
+template <bool FULL>
+__global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t count, TileGrid tg, uint32_t *flags,
+                    int round) {
+    BndChase<FULL>::run(tg, bnd, count, flags, round);
 }
 
 // One workgroup per resolve tile.  A table in LDS holds, at each place of the
@@ -472,92 +487,100 @@ __global__ void __launch_bounds__(256) bnd_chase_kernel(int32_t *bnd, int64_t co
 // 4 written per cell (1024^3: 1.57 ms, 4.1 TB/s).  With 32-bit indices in ptr, taken
 // apart into coordinates for every cell, 2.38 ms; 256^3 40 -> 22 us.
 template <bool FULL>
-__global__ void __launch_bounds__(PR_THREADS) seg_finalize_kernel(const uint4 *__restrict__ ptr,
-                                                                  const int32_t *__restrict__ bnd, TileGrid rg,
-                                                                  const uint32_t *__restrict__ open,
-                                                                  int32_t *__restrict__ label) {
-    __shared__ int32_t table[RHCELLS + 1];
-    int x0, y0, z0;
-    const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
-    rtile_origin(rg, int(tile), x0, y0, z0);
-    const int n = rg.n;
-    const uint32_t un = uint32_t(n);
-    const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
-              wz = FULL ? RZ : tile_extent(z0, RZ, n);
-    // this column's addresses and the shell's entries, all loads issued before any is used
-    const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
-    uint4 t[COLUMN_WORDS];
-    const uint4 *in = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
+struct SegFinalize {
+    static __device__ __forceinline__ void run(TileGrid rg, const uint4 *__restrict__ ptr,
+                                               const int32_t *__restrict__ bnd, const uint32_t *__restrict__ open,
+                                               int32_t *__restrict__ label) {
+        __shared__ int32_t table[RHCELLS + 1];
+        int x0, y0, z0;
+        const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
+        rtile_origin(rg, int(tile), x0, y0, z0);
+        const int n = rg.n;
+        const uint32_t un = uint32_t(n);
+        const int wx = FULL ? RX : tile_extent(x0, RX, n), wy = FULL ? RY : tile_extent(y0, RY, n),
+                  wz = FULL ? RZ : tile_extent(z0, RZ, n);
+        // this column's addresses and the shell's entries, all loads issued before any is used
+        const int tid = threadIdx.x, x = tid % RX, y = tid / RX;
+        uint4 t[COLUMN_WORDS];
+        const uint4 *in = ptr + (size_t(tile) * PR_THREADS + uint32_t(tid)) * COLUMN_WORDS;
 #pragma unroll
-    for (int q = 0; q < COLUMN_WORDS; ++q) t[q] = in[q];
-    // the one-cell shell around the tile's (wx, wy, wz) cells, enumerated: the
-    // two z planes, then per inner plane the two y rows and the two x ends of
-    // the rows between them; shell cell (hx, hy, hz) sits at LDS place
-    // (hz RHY + hy) RHX + hx, with the tile's cells at 1..wx, 1..wy, 1..wz
-    const int ex = wx + 2, ey = wy + 2, ez = wz + 2;
-    const int zplane = ex * ey, ring = 2 * ex + 2 * (ey - 2);
-    const int nshell = 2 * zplane + (ez - 2) * ring;
-    constexpr int LOADS = (RHCELLS - RCELLS + PR_THREADS - 1) / PR_THREADS;
-    int32_t v[LOADS];
-    int at[LOADS];
+        for (int q = 0; q < COLUMN_WORDS; ++q) t[q] = in[q];
+        // the one-cell shell around the tile's (wx, wy, wz) cells, enumerated: the
+        // two z planes, then per inner plane the two y rows and the two x ends of
+        // the rows between them; shell cell (hx, hy, hz) sits at LDS place
+        // (hz RHY + hy) RHX + hx, with the tile's cells at 1..wx, 1..wy, 1..wz
+        const int ex = wx + 2, ey = wy + 2, ez = wz + 2;
+        const int zplane = ex * ey, ring = 2 * ex + 2 * (ey - 2);
+        const int nshell = 2 * zplane + (ez - 2) * ring;
+        constexpr int LOADS = (RHCELLS - RCELLS + PR_THREADS - 1) / PR_THREADS;
+        int32_t v[LOADS];
+        int at[LOADS];
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int k = tid + i * PR_THREADS;
-        at[i] = -1;
-        if (k >= nshell) continue;
-        int hx, hy, hz;
-        if (k < 2 * zplane) {
-            hz = k < zplane ? 0 : ez - 1;
-            const int j = k % zplane;
-            hy = j / ex;
-            hx = j % ex;
-        } else {
-            const int j = k - 2 * zplane;
-            hz = 1 + j / ring;
-            const int r = j % ring;
-            if (r < 2 * ex) {
-                hy = r < ex ? 0 : ey - 1;
-                hx = r % ex;
+        for (int i = 0; i < LOADS; ++i) {
+            const int k = tid + i * PR_THREADS;
+            at[i] = -1;
+            if (k >= nshell) continue;
+            int hx, hy, hz;
+            if (k < 2 * zplane) {
+                hz = k < zplane ? 0 : ez - 1;
+                const int j = k % zplane;
+                hy = j / ex;
+                hx = j % ex;
             } else {
-                const int q = r - 2 * ex;
-                hy = 1 + q / 2;
-                hx = (q & 1) ? ex - 1 : 0;
+                const int j = k - 2 * zplane;
+                hz = 1 + j / ring;
+                const int r = j % ring;
+                if (r < 2 * ex) {
+                    hy = r < ex ? 0 : ey - 1;
+                    hx = r % ex;
+                } else {
+                    const int q = r - 2 * ex;
+                    hy = 1 + q / 2;
+                    hx = (q & 1) ? ex - 1 : 0;
+                }
+            }
+            const uint32_t gx = wrap(x0 + hx - 1, n), gy = wrap(y0 + hy - 1, n), gz = wrap(z0 + hz - 1, n);
+            v[i] = bnd[bnd_slot_at<FULL>(rg, gx, gy, gz)];  // on its tile's boundary
+            at[i] = (hz * RHY + hy) * RHX + hx;
+        }
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            if (at[i] >= 0) table[at[i]] = v[i];
+        __syncthreads();
+        if (*open != 0u) {  // the chase left entries open: the rest of the way, at most CHASE_HOPS steps
+#pragma unroll 1
+            for (int k = tid; k < RHCELLS; k += PR_THREADS) {
+                const int hx = k % RHX, hy = (k / RHX) % RHY, hz = k / (RHX * RHY);
+                if (hx >= ex || hy >= ey || hz >= ez) continue;
+                if (hx == 0 || hx == ex - 1 || hy == 0 || hy == ey - 1 || hz == 0 || hz == ez - 1)
+                    table[k] = follow<FULL>(bnd, rg, bnd[bnd_slot_at<FULL>(rg, wrap(x0 + hx - 1, n), wrap(y0 + hy - 1, n),
+                                                                           wrap(z0 + hz - 1, n))]);
             }
         }
-        const uint32_t gx = wrap(x0 + hx - 1, n), gy = wrap(y0 + hy - 1, n), gz = wrap(z0 + hz - 1, n);
-        v[i] = bnd[bnd_slot_at<FULL>(rg, gx, gy, gz)];  // on its tile's boundary
-        at[i] = (hz * RHY + hy) * RHX + hx;
-    }
+        if (tid == 0) table[RHCELLS] = -1;
+        const bool column = x < wx && y < wy;
+        const uint32_t g0 = ((uint32_t(z0) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
+        const int own = (RHY + y + 1) * RHX + x + 1;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i)
-        if (at[i] >= 0) table[at[i]] = v[i];
-    __syncthreads();
-    if (*open != 0u) {  // the chase left entries open: the rest of the way, at most CHASE_HOPS steps
-#pragma unroll 1
-        for (int k = tid; k < RHCELLS; k += PR_THREADS) {
-            const int hx = k % RHX, hy = (k / RHX) % RHY, hz = k / (RHX * RHY);
-            if (hx >= ex || hy >= ey || hz >= ez) continue;
-            if (hx == 0 || hx == ex - 1 || hy == 0 || hy == ey - 1 || hz == 0 || hz == ez - 1)
-                table[k] = follow<FULL>(bnd, rg, bnd[bnd_slot_at<FULL>(rg, wrap(x0 + hx - 1, n), wrap(y0 + hy - 1, n),
-                                                                       wrap(z0 + hz - 1, n))]);
+        for (int z = 0; z < RZ; ++z)
+            if (FULL || (column && z < wz)) table[own + z * RHX * RHY] = int32_t(g0 + uint32_t(z) * un * un);
+        __syncthreads();
+        if (!column) return;
+        const char *lds = reinterpret_cast<const char *>(table);
+#pragma unroll
+        for (int z = 0; z < RZ; ++z) {
+            if (!FULL && z >= wz) continue;
+            const uint32_t word = (&t[z / 8].x)[(z % 8) / 2], a = z & 1 ? word >> 16 : word & 0xffffu;
+            label[g0 + uint32_t(z) * un * un] = *reinterpret_cast<const int32_t *>(lds + a);
         }
     }
-    if (tid == 0) table[RHCELLS] = -1;
-    const bool column = x < wx && y < wy;
-    const uint32_t g0 = ((uint32_t(z0) * un) + uint32_t(y0 + y)) * un + uint32_t(x0 + x);
-    const int own = (RHY + y + 1) * RHX + x + 1;
-#pragma unroll
-    for (int z = 0; z < RZ; ++z)
-        if (FULL || (column && z < wz)) table[own + z * RHX * RHY] = int32_t(g0 + uint32_t(z) * un * un);
-    __syncthreads();
-    if (!column) return;
-    const char *lds = reinterpret_cast<const char *>(table);
-#pragma unroll
-    for (int z = 0; z < RZ; ++z) {
-        if (!FULL && z >= wz) continue;
-        const uint32_t word = (&t[z / 8].x)[(z % 8) / 2], a = z & 1 ? word >> 16 : word & 0xffffu;
-        label[g0 + uint32_t(z) * un * un] = *reinterpret_cast<const int32_t *>(lds + a);
-    }
+};
+
+template <bool FULL>
+__global__ void __launch_bounds__(PR_THREADS) seg_finalize_kernel(const uint4 *__restrict__ ptr,
+                    const int32_t *__restrict__ bnd, TileGrid rg, const uint32_t *__restrict__ open,
+                    int32_t *__restrict__ label) {
+    SegFinalize<FULL>::run(rg, ptr, bnd, open, label);
 }
 
 // ------------------------------------------------------------------ mask -> sorted list
@@ -613,28 +636,34 @@ __global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_write_kernel(const uint
 // 128^3, where this takes 4.4 and 11); at 256^3 the words would be read 2048 times.
 constexpr int LIST_SHORT = 512;
 
-__global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_short_kernel(const uint32_t *__restrict__ mask,
-                                                                      int64_t words, int64_t cap,
-                                                                      int32_t *__restrict__ out,
-                                                                      int64_t *__restrict__ d_count,
-                                                                      uint32_t *status) {
-    __shared__ uint32_t red[LIST_CHUNK_WORDS / 64];
-    const uint4 *before = reinterpret_cast<const uint4 *>(mask);  // whole chunks lie before this one
-    uint32_t sum = 0;
+struct ListShort {
+    static __device__ __forceinline__ void run(int64_t words, const uint32_t *__restrict__ mask, int64_t cap,
+                                               int32_t *__restrict__ out, int64_t *__restrict__ d_count,
+                                               uint32_t *status) {
+        __shared__ uint32_t red[LIST_CHUNK_WORDS / 64];
+        const uint4 *before = reinterpret_cast<const uint4 *>(mask);  // whole chunks lie before this one
+        uint32_t sum = 0;
 #pragma unroll 8
-    for (uint32_t k = threadIdx.x; k < blockIdx.x * (LIST_CHUNK_WORDS / 4); k += LIST_CHUNK_WORDS) {
-        const uint4 m = before[k];
-        sum += uint32_t(__popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w));
+        for (uint32_t k = threadIdx.x; k < blockIdx.x * (LIST_CHUNK_WORDS / 4); k += LIST_CHUNK_WORDS) {
+            const uint4 m = before[k];
+            sum += uint32_t(__popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w));
+        }
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
+        const uint32_t end = write_cells(w, w < words ? mask[w] : 0u, red[0] + red[1], cap, out);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == LIST_CHUNK_WORDS - 1) {
+            *d_count = int64_t(end);
+            if (int64_t(end) > cap) atomicOr(status, ST_CAPACITY);
+        }
     }
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    const int64_t w = int64_t(blockIdx.x) * LIST_CHUNK_WORDS + threadIdx.x;
-    const uint32_t end = write_cells(w, w < words ? mask[w] : 0u, red[0] + red[1], cap, out);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == LIST_CHUNK_WORDS - 1) {
-        *d_count = int64_t(end);
-        if (int64_t(end) > cap) atomicOr(status, ST_CAPACITY);
-    }
+};
+
+__global__ void __launch_bounds__(LIST_CHUNK_WORDS) list_short_kernel(const uint32_t *__restrict__ mask,
+                    int64_t words, int64_t cap, int32_t *__restrict__ out, int64_t *__restrict__ d_count,
+                    uint32_t *status) {
+    ListShort::run(words, mask, cap, out, d_count, status);
 }
 
 // ------------------------------------------------------------------ host side
@@ -788,6 +817,39 @@ hf_status segment_finish(hf_ctx *ctx, const SegmentLayout &L, char *w8, int n, i
 }
 
 }  // namespace
+
+bool hf::segment_group_supported(int n) { return all_full(n) && maxima_layout(n).nchunks <= LIST_SHORT; }
+
+hf_status hf::segment_group(hf_ctx *ctx, int n, int count, const GroupBox *b) {
+    const SegmentLayout L = segment_layout(n);
+    const MaximaLayout ML = maxima_layout(n);
+    const TileGrid tg = resolve_grid(n);
+    const unsigned tiles = unsigned(tg.ntx * tg.nty * tg.ntz);
+    Boxes<const float *, uint32_t, uint4 *, int32_t *, uint32_t *, uint32_t *, uint32_t *> parent{};
+    Boxes<const uint32_t *, int64_t, int32_t *, int64_t *, uint32_t *> list{};
+    Boxes<int32_t *, int64_t, uint32_t *, int> chase{};
+    Boxes<const uint4 *, const int32_t *, const uint32_t *, int32_t *> last{};
+    for (int j = 0; j < count; ++j) {
+        auto *ptr = reinterpret_cast<uint4 *>(b[j].ws + L.ptr);
+        auto *bnd = reinterpret_cast<int32_t *>(b[j].ws + L.bnd);
+        auto *flags = reinterpret_cast<uint32_t *>(b[j].ws + L.flags);
+        auto *mask = reinterpret_cast<uint32_t *>(b[j].ws + L.total + ML.mask);
+        pack(parent.a[j], b[j].cwt, host_ordered_bits(b[j].tau), ptr, bnd, mask, flags, ctx->d_status);
+        pack(list.a[j], static_cast<const uint32_t *>(mask), b[j].max_cap, b[j].max_idx, b[j].d_count, ctx->d_status);
+        pack(chase.a[j], bnd, L.nbnd, flags, 0);
+        pack(last.a[j], static_cast<const uint4 *>(ptr), static_cast<const int32_t *>(bnd),
+             static_cast<const uint32_t *>(flags + L.rounds - 1), b[j].cell_label);
+    }
+    launch_group<ParentResolve<true, true>, PR_THREADS>(ctx, K_PARENT, tiles, count, parent, tg);
+    launch_group<ListShort, LIST_CHUNK_WORDS>(ctx, K_MAX_WRITE, unsigned(ML.nchunks), count, list, ML.words);
+    for (int r = 0; r + 1 < L.rounds; ++r) {
+        for (int j = 0; j < count; ++j) pack(chase.a[j], chase.a[j].head, L.nbnd, chase.a[j].tail.tail.head, r);
+        launch_group<BndChase<true>, 256>(ctx, K_JUMP, unsigned(stride_grid((L.nbnd + BATCH - 1) / BATCH)), count, chase,
+                                          tg);
+    }
+    launch_group<SegFinalize<true>, PR_THREADS>(ctx, K_FINALIZE, tiles, count, last, tg);
+    return launch_status();
+}
 
 size_t hf::maxima_segment_ws_bytes(const hf_box &box) {
     return segment_layout(box.n).total + maxima_layout(box.n).total;

@@ -159,7 +159,7 @@ bool particle_order_supported(const hf_box &box, int64_t np);  // binned, more t
 size_t particle_order_bytes(const hf_box &box, int64_t np);
 ParticleOrder particle_order_at(const hf_box &box, void *base, int64_t np);
 
-// Binned deposit (n % 16 == 0, B <= 17, np < 2^32).  With `order`, the level-2
+// Binned deposit (B <= 17, np < 2^32; on a wider grid where n's own tiles do not do).  With `order`, the level-2
 // records and tile offsets go to the order region and the slot maps are
 // written; the workspace is then deposit_tiled_ws_bytes(box, np, true).
 bool deposit_tiled_supported(const hf_box &box, int64_t np);
@@ -199,8 +199,7 @@ size_t label_scratch_bytes(int64_t np);
 hf_status label_from_order(hf_ctx *ctx, const hf_box &box, int64_t np, const ParticleOrder &order,
                            const int32_t *cell_label, int32_t *particle_label, void *scratch);
 
-// Steps 4 and 5 in one pass over the field where the grid is tiled (n % 32 ==
-// 0), else hf_maxima then hf_segment; workspace maxima_segment_ws_bytes(box).
+// Steps 4 and 5 in one pass over the field; workspace maxima_segment_ws_bytes(box).
 size_t maxima_segment_ws_bytes(const hf_box &box);
 hf_status maxima_segment(hf_ctx *ctx, const hf_box &box, const float *cwt, float tau, int32_t *max_idx,
                          int64_t max_cap, int64_t *d_count, int32_t *cell_label, void *ws, size_t ws_bytes);

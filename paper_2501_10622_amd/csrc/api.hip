@@ -200,7 +200,7 @@ hf_status hf::stage_ws_size(const hf_box *box, int64_t np, int stage_mask, bool 
     // deposit + label: the deposit's particle order is kept for the labels in
     // a region of its own in front of the part the stages share in turn
     const bool order = (stage_mask & HF_STAGE_DEPOSIT) && (stage_mask & HF_STAGE_LABEL) &&
-                       particle_order_supported(*box, np);
+                       particle_order_supported(*box, np) && !(least && particle_order_optional(*box));
     size_t need = 0;
     auto take = [&need](size_t b) { need = need > b ? need : b; };
     // (the buffer sets of a group, whose transform has a workspace of its own, keep to the least)

@@ -156,6 +156,8 @@ struct ParticleOrder {
     alignas(8) unsigned char maps[2][32];
 };
 bool particle_order_supported(const hf_box &box, int64_t np);  // binned, more than one bucket
+// True where the calls that keep the order also run without it, in a smaller workspace.
+bool particle_order_optional(const hf_box &box);
 size_t particle_order_bytes(const hf_box &box, int64_t np);
 ParticleOrder particle_order_at(const hf_box &box, void *base, int64_t np);
 

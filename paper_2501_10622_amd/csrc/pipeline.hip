@@ -5,6 +5,14 @@
 
 using namespace hf;
 
+namespace {
+// Whether a call with `ws_bytes` of workspace keeps the deposit's particle order;
+// `full` is what the call asks for.
+bool keeps_order(const hf_box &box, int64_t np, size_t ws_bytes, size_t full) {
+    return particle_order_supported(box, np) && (!particle_order_optional(box) || ws_bytes >= full);
+}
+}  // namespace
+
 extern "C" hf_status hf_find_halos(hf_ctx *ctx, const hf_box *box, const hf_job *job, void *ws, size_t ws_bytes) {
     if (!ctx || !job) return HF_ERR_ARG;
     hf_status s = check_box_for(box, job->kernel);
@@ -24,7 +32,10 @@ extern "C" hf_status hf_find_halos(hf_ctx *ctx, const hf_box *box, const hf_job 
         return HF_ERR_ARG;
     // With the binned deposit the particle order it builds is kept (in front of
     // the workspace) and step 6 reuses it; every other stage gets the rest.
-    const bool order = particle_order_supported(*box, job->np);
+    size_t full = 0;
+    s = stage_ws_size(box, job->np, pipeline_stages(job->kernel), false, &full);
+    if (s != HF_OK) return s;
+    const bool order = keeps_order(*box, job->np, ws_bytes, full);
     char *sw = static_cast<char *>(ws);
     size_t sb = ws_bytes;
     ParticleOrder po{};
@@ -74,7 +85,10 @@ extern "C" hf_status hf_find_halos_filtered(hf_ctx *ctx, const hf_box *box, cons
         job->tau != job->tau)
         return HF_ERR_ARG;
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
-    const bool order = particle_order_supported(*box, job->np);
+    size_t full = 0;
+    s = stage_ws_size(box, job->np, pipeline_stages(job->kernel) | HF_STAGE_GROUPS, false, &full);
+    if (s != HF_OK) return s;
+    const bool order = keeps_order(*box, job->np, ws_bytes, full);
     char *sw = static_cast<char *>(ws);
     size_t sb = ws_bytes;
     ParticleOrder po{};
@@ -140,7 +154,8 @@ hf_status scales_ws_size(const hf_box *box, int64_t np, int32_t count, bool leas
     s = stage_ws_size(box, np, HF_STAGE_ALL, least, &all);
     if (s == HF_OK) s = hf_cwt_batch_ws_size(box->n, count, &cw);
     if (s != HF_OK) return s;
-    const size_t ord = particle_order_supported(*box, np) ? particle_order_bytes(*box, np) : 0;
+    const bool order = particle_order_supported(*box, np) && !(least && particle_order_optional(*box));
+    const size_t ord = order ? particle_order_bytes(*box, np) : 0;
     const size_t shared = all - ord;  // every stage's share, one transform included
     *bytes = ord + (shared > cw ? shared : cw);
     return HF_OK;
@@ -177,7 +192,10 @@ extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const 
         cwts[j] = sj.cwt;
     }
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
-    const bool order = particle_order_supported(*box, np);
+    size_t full = 0;
+    s = scales_ws_size(box, np, count, false, &full);
+    if (s != HF_OK) return s;
+    const bool order = keeps_order(*box, np, ws_bytes, full);
     char *sw = static_cast<char *>(ws);
     size_t sb = ws_bytes;
     ParticleOrder po{};
@@ -207,6 +225,7 @@ extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const 
 namespace {
 struct IdentifyLayout {
     size_t base, groups, pass, claim, total;
+    bool order;  // the deposit's particle order is kept
 };
 
 hf_status identify_layout(const hf_box *box, int64_t np, int32_t count, const hf_scale_job *scales, bool least,
@@ -222,8 +241,8 @@ hf_status identify_layout(const hf_box *box, int64_t np, int32_t count, const hf
     L.groups = align_up(L.base);
     L.pass = L.groups + groups_ws_bytes(*box);
     L.claim = L.pass + align_up(size_t(cap));
-    const bool order = particle_order_supported(*box, np);
-    L.total = L.claim + (order ? align_up(size_t(np)) : 0);  // one claim byte per particle, tile order
+    L.order = particle_order_supported(*box, np) && !(least && particle_order_optional(*box));
+    L.total = L.claim + (L.order ? align_up(size_t(np)) : 0);  // one claim byte per particle, tile order
     return HF_OK;
 }
 }  // namespace
@@ -280,7 +299,7 @@ extern "C" hf_status hf_identify(hf_ctx *ctx, const hf_box *box, const void *pos
     s = check_ws(ws, ws_bytes, L.total);
     if (s != HF_OK) return s;
     if (hipSetDevice(ctx->device) != hipSuccess) return HF_ERR_DEVICE;
-    const bool order = particle_order_supported(*box, np);
+    const bool order = L.order;
     char *w0 = static_cast<char *>(ws);
     char *sw = w0;
     size_t sb = L.base;

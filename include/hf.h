@@ -299,9 +299,10 @@ hf_status hf_cwt_batch(hf_ctx *ctx, int32_t n, int32_t count, const hf_cwt_item 
  * context's stream, all sharing one workspace of
  * hf_workspace_size(box, np, HF_STAGE_ALL) bytes (| HF_STAGE_STENCIL with
  * HF_KERNEL_STENCIL).  Where the deposit bins the
- * particles (n a multiple of 16 with more than 512 tiles of 16-64 x 8 x 8
- * cells, frac_bits <= 17, np < 2^32) the binned order is kept and step 6 runs
- * through it: records are labelled tile by tile and the labels brought back
+ * particles into more than one bucket (more than 512 tiles of 16-64 x 8 x 8
+ * cells, frac_bits <= 17, np < 2^32) on the grid itself, or from 2^23 particles
+ * on a wider one (n no multiple of 16, for one), and the workspace has the size
+ * asked for, the binned order is kept and step 6 runs through it: records are labelled tile by tile and the labels brought back
  * to input order, with the same result as hf_label.  Device-detected errors are
  * reported by hf_sync as for the separate calls. */
 typedef struct {

@@ -75,7 +75,8 @@ __global__ void __launch_bounds__(CX *CY) groups_cells_kernel(const int32_t *__r
             bad = true;
             l = -1;
         }
-        const bool head = lane % CX == 0 || l != __shfl_up(l, 1, 64);
+        const int32_t prev = __shfl_up(l, 1, 64);  // on every lane: the shuffle reads 0 from lanes that are off
+        const bool head = lane % CX == 0 || l != prev;
         const unsigned long long after = __ballot(head) >> lane >> 1;
         const uint32_t len = after ? uint32_t(__ffsll((long long)after)) : uint32_t(64 - lane);
         if (head && l >= 0) {

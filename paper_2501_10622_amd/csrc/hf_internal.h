@@ -297,15 +297,17 @@ size_t stencil_ws_bytes(const hf_box &box);
 // Steps 9-10 for the kept groups (keep[i]) of the roots: afterwards only the
 // bound particles of the groups that pass keep their labels; bound_keep[i]
 // receives the decision.  nroots is the list's capacity; with d_count the
-// list holds min(*d_count, nroots) roots.  members (optional) holds the number
-// of labels of every kept group where the caller has counted them (every label
-// is then a kept group's or -1).  Workspace: unbind_ws_bytes(box, np, nroots,
-// records); with ws_bytes enough for the members' records they are used.
+// list holds min(*d_count, nroots) roots.  counted (optional): the counters after
+// groups_decide where the caller has filtered the labels by them and claimed; parts
+// of a listed root whose flag in cells is set is then the number of its labels.
+// Labels that are no listed root's are reported and dropped either way.  Workspace:
+// unbind_ws_bytes(box, np, nroots, records); with ws_bytes enough for the members'
+// records they are used.
 size_t unbind_ws_bytes(const hf_box &box, int64_t np, int64_t nroots, bool records);
 hf_status unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const void *vel, hf_dtype dtype, int64_t np,
                      const int32_t *roots, int64_t nroots, const uint8_t *keep, int32_t *label, double grav_mass,
                      int64_t particle_th, uint8_t *bound_keep, void *ws, size_t ws_bytes, const int64_t *d_count,
-                     const uint32_t *members);
+                     const GroupCounters *counted);
 // Particles that scale `scale` claimed and whose label is now -1 are free again.
 hf_status unclaim(hf_ctx *ctx, const int32_t *label, int64_t np, int32_t scale, int32_t *halo_scale,
                   int32_t *halo_root);

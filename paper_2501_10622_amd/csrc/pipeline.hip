@@ -473,7 +473,7 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
         // removes (all of a discarded group's) are free again for later scales
         if (s == HF_OK && with_vel && sj.max_cap > 0) {
             s = unbind_dev(ctx, b, pos, vel, dtype, np, sj.max_idx, sj.max_cap, sj.group_keep, sj.particle_label,
-                           grav_mass, particle_th, sj.bound_keep, w0, sb, sj.d_count, sj.group_particles);
+                           grav_mass, particle_th, sj.bound_keep, w0, sb, sj.d_count, &g);
             if (s == HF_OK) s = unclaim(ctx, sj.particle_label, np, j, halo_scale, halo_root);
         }
     }

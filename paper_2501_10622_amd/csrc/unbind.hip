@@ -113,12 +113,12 @@ unsigned ub_grid(const hf_ctx *ctx, int64_t work) {
 }
 
 // slot[root_i] = i and cursor[i] = 0 for every root; cnt[i] = 0, or, where the
-// members have been counted already, counts[i] of a kept group; the group
-// lists' counters to 0.
+// members have been counted already, the parts of a group whose keep flag is set
+// (the counters of the cells, GroupCounters); the group lists' counters to 0.
 __global__ void __launch_bounds__(UB_THREADS) ub_slots_kernel(const int32_t *__restrict__ roots,
                                                               const int64_t *d_count, int64_t cap, int64_t ncells,
-                                                              const uint8_t *__restrict__ keep,
-                                                              const uint32_t *__restrict__ counts,
+                                                              const uint32_t *__restrict__ parts,
+                                                              const uint32_t *__restrict__ kept,
                                                               uint32_t *__restrict__ slot, uint32_t *__restrict__ cnt,
                                                               uint32_t *__restrict__ cur, uint32_t *__restrict__ queue,
                                                               uint32_t *status) {
@@ -127,13 +127,14 @@ __global__ void __launch_bounds__(UB_THREADS) ub_slots_kernel(const int32_t *__r
     bool bad = false;
     for (int64_t i = blockIdx.x * int64_t(UB_THREADS) + threadIdx.x; i < nroots;
          i += int64_t(gridDim.x) * UB_THREADS) {
-        cnt[i] = counts && keep[i] ? counts[i] : 0u;
         cur[i] = 0u;
         const int32_t r = roots[i];
         if (r < 0 || r >= ncells) {
+            cnt[i] = 0u;
             bad = true;
             continue;
         }
+        cnt[i] = parts && kept[r] ? parts[r] : 0u;
         slot[r] = uint32_t(i);
     }
     if (bad) atomicOr(status, ST_INPUT);
@@ -176,20 +177,32 @@ __global__ void __launch_bounds__(UB_THREADS) ub_count_kernel(int32_t *__restric
     if (bad) atomicOr(status, ST_INPUT);
 }
 
-// One slot per member in its group's run (in the order the cursors give).
-// With rec, the member's position and velocity are put into the slot too
+// One slot per member in its group's run (in the order the cursors give).  Where
+// the members have been counted before (guard), labels come as the loop over scales
+// left them: those of roots past the end of a list that is too short for its maxima
+// are among them, have no slot, and are reported and dropped, as ub_count_kernel does
+// where it runs.  With rec, the member's position and velocity are put into the slot too
 // (6 values): here they stream by in input order, while the check would fetch
 // two lines from all over the arrays for every member and pass over them.
 template <typename T>
-__global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(const int32_t *__restrict__ label, int64_t np,
+__global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restrict__ label, int64_t np, bool guard,
+                                                               const int32_t *__restrict__ roots,
+                                                               const int64_t *d_count, int64_t cap, int64_t ncells,
+                                                               const uint8_t *__restrict__ keep,
                                                                const uint32_t *__restrict__ slot,
                                                                const uint32_t *__restrict__ start,
                                                                uint32_t *__restrict__ cur, int32_t *__restrict__ pid,
                                                                const T *__restrict__ pos, const T *__restrict__ vel,
-                                                               T *__restrict__ rec) {
+                                                               T *__restrict__ rec, uint32_t *status) {
+    const int64_t nroots = ub_roots(d_count, cap);
+    bool bad = false;
     for (int64_t p = blockIdx.x * int64_t(UB_THREADS) + threadIdx.x; p < np; p += int64_t(gridDim.x) * UB_THREADS) {
         const int32_t l = label[p];
-        if (l < 0) continue;  // every label left is a kept group's
+        if (l < 0) continue;
+        if (guard && group_of(l, roots, nroots, ncells, slot, keep, bad) < 0) {
+            label[p] = -1;
+            continue;
+        }
         T v[6];
         if (rec) {
 #pragma unroll
@@ -200,12 +213,18 @@ __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(const int32_t *__
         }
         const uint32_t g = slot[l];
         const int64_t k = int64_t(start[g]) + atomicAdd(cur + g, 1u);
+        if (guard && k >= int64_t(start[g + 1])) {  // more members than were counted: the run is full
+            label[p] = -1;
+            bad = true;
+            continue;
+        }
         pid[k] = int32_t(p);
         if (rec) {
 #pragma unroll
             for (int a = 0; a < 6; ++a) rec[6 * k + a] = v[a];
         }
     }
+    if (bad) atomicOr(status, ST_INPUT);
 }
 
 // The kept groups by size: the huge ones at the front of `big`, the middle ones
@@ -1034,7 +1053,7 @@ size_t hf::unbind_ws_bytes(const hf_box &box, int64_t np, int64_t nroots, bool r
 hf_status hf::unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const void *vel, hf_dtype dtype,
                          int64_t np, const int32_t *roots, int64_t nroots, const uint8_t *keep, int32_t *label,
                          double grav_mass, int64_t particle_th, uint8_t *bound_keep, void *ws, size_t ws_bytes,
-                         const int64_t *d_count, const uint32_t *members) {
+                         const int64_t *d_count, const GroupCounters *counted) {
     if (nroots <= 0) return HF_OK;
     const UnbindLayout L = unbind_layout(box.n, np, nroots);
     char *w = static_cast<char *>(ws);
@@ -1048,8 +1067,9 @@ hf_status hf::unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const 
     const int64_t ncells = int64_t(box.n) * box.n * box.n;
     hipStream_t st = ctx->stream;
     HF_LAUNCH(ctx, K_UNBIND, ub_slots_kernel, dim3(ub_grid(ctx, nroots)), dim3(UB_THREADS), 0, st, roots, d_count,
-              nroots, ncells, keep, members, slot, cnt, cur, queue, ctx->d_status);
-    if (np > 0 && !members)
+              nroots, ncells, counted ? counted->parts : nullptr, counted ? counted->cells : nullptr, slot, cnt, cur,
+              queue, ctx->d_status);
+    if (np > 0 && !counted)
         HF_LAUNCH(ctx, K_UNBIND, ub_count_kernel, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np, roots,
                   d_count, nroots, ncells, slot, keep, cnt, ctx->d_status);
     ScanJob sj = scan_job(cnt, nroots, partial, start);
@@ -1058,8 +1078,9 @@ hf_status hf::unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const 
     const bool records = ws_bytes >= L.full;
     auto gather = [&](auto *p, auto *v) {
         using T = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
-        HF_LAUNCH(ctx, K_UNBIND, ub_gather_kernel<T>, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np, slot,
-                  start, cur, pid, p, v, records ? reinterpret_cast<T *>(w + L.rec) : nullptr);
+        HF_LAUNCH(ctx, K_UNBIND, ub_gather_kernel<T>, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np,
+                  counted != nullptr, roots, d_count, nroots, ncells, keep, slot, start, cur, pid, p, v,
+                  records ? reinterpret_cast<T *>(w + L.rec) : nullptr, ctx->d_status);
     };
     if (np > 0 && dtype == HF_F32) gather(static_cast<const float *>(pos), static_cast<const float *>(vel));
     else if (np > 0) gather(static_cast<const double *>(pos), static_cast<const double *>(vel));

@@ -196,3 +196,68 @@ def test_identify_grids_with_velocities():
     print(f"identify grids with velocities: agreement {agree:.6f}", flush=True)
     assert agree >= LABEL_AGREEMENT
     assert (ref["halo_scale"] >= 0).any()
+
+
+def _guarded(size, dtype, align=256, guard=4096):
+    """A tensor of `size` elements between two guards, and a check that they are untouched."""
+    item = torch.empty(0, dtype=dtype).element_size()
+    room = torch.full((2 * guard + (size * item + align - 1) // align * align,), 0xA5, dtype=torch.uint8, device="cuda")
+    assert room.data_ptr() % align == 0
+
+    def untouched():
+        return bool((room[:guard] == 0xA5).all()) and bool((room[guard + size * item:] == 0xA5).all())
+    return room[guard:guard + size * item].view(dtype), untouched
+
+
+@pytest.mark.parametrize("npt", [300_000, (1 << 20) + 7])  # members counted by atomics and by partition
+def test_identify_grids_with_velocities_and_lists_too_short(npt):
+    """More maxima than the lists hold: an error is reported, the listed groups come
+    out as those of the separate calls on the listed roots, labels of the others are
+    dropped, and nothing outside the buffers is written."""
+    from paper_2501_10622_amd.hf import HF_ERR_CAPACITY, HF_ERR_INPUT, HFError
+    import synth
+    L, grids = 64.0, (48, 64)
+    pos_np, vel_np, m_p = synth.make_phase_box(L, npt, 250, "f32", 25)
+    pos, vel, gm = cuda(pos_np), cuda(vel_np), O.GRAV * m_p
+    kws = [64 / (1000.0 * a) for a in (2.0, 1.5)]
+    fields = [hfm().cwt_stencil(hfm().deposit(pos, L, g_), L, kw).clone() for g_, kw in zip(grids, kws)]
+    lists = [hfm().maxima(f).clone() for f in fields]
+    caps = [r.numel() // 2 for r in lists]
+    bufs = hfm().identify_grids_buffers(grids, npt, pos.device, L, with_velocities=True)
+    checks = []
+    for key in ("maxima", "group_particles", "group_cells", "group_keep", "bound_keep", "particle_label"):
+        for j, cap in enumerate(caps):
+            bufs[key][j], ok = _guarded(npt if key == "particle_label" else cap, bufs[key][j].dtype)
+            checks.append((key, ok))
+    for key in ("halo_scale", "halo_root", "ws"):
+        bufs[key], ok = _guarded(bufs[key].numel(), bufs[key].dtype)
+        checks.append((key, ok))
+    bufs["ws"].fill_(0x41)  # what the slots of unlisted roots hold: far outside every list
+    hfm().identify_grids_async(pos, L, kws, bufs, 2.0, 15, vel=vel, grav_mass=gm)
+    with pytest.raises(HFError) as e:
+        hfm().sync()
+    assert e.value.code in (HF_ERR_CAPACITY, HF_ERR_INPUT)
+    assert [key for key, ok in checks if not ok()] == []
+    claimed = torch.full((npt,), -1, dtype=torch.int32, device="cuda")
+    root = torch.full((npt,), -1, dtype=torch.int32, device="cuda")
+    for j, (g_, cap) in enumerate(zip(grids, caps)):
+        roots = lists[j][:cap]
+        assert int(bufs["count"][j].item()) == lists[j].numel() and torch.equal(bufs["maxima"][j], roots)
+        listed = torch.zeros(g_ ** 3, dtype=torch.bool, device="cuda")
+        listed[roots.long()] = True
+        cell = hfm().segment(fields[j])
+        lab = hfm().label(pos, L, g_, cell)
+        nxt = fields[j + 1] if j + 1 < len(grids) else torch.zeros_like(fields[j])
+        ok = hfm().cross_scale(fields[j], nxt, roots)
+        free = torch.where((claimed < 0) & listed[lab.clamp_min(0).long()], lab, -1)
+        gs = hfm().groups(torch.where(listed[cell.clamp_min(0).long()], cell, -1), free, roots, npt, 2.0, 15, root_ok=ok)
+        want = gs["particle_label"].clone()
+        bound = hfm().unbind(pos, vel, L, g_, roots, gs["keep"], want, gm, 15)
+        hfm().sync()
+        for key, value in (("group_particles", gs["particles"]), ("group_cells", gs["cells"]),
+                           ("group_keep", gs["keep"]), ("bound_keep", bound), ("particle_label", want)):
+            assert torch.equal(bufs[key][j], value), key
+        claimed = torch.where(want >= 0, j, claimed)
+        root = torch.where(want >= 0, want, root)
+    assert torch.equal(bufs["halo_scale"], claimed) and torch.equal(bufs["halo_root"], root)
+    assert int((claimed >= 0).sum()) > 0

@@ -97,20 +97,21 @@ __global__ void __launch_bounds__(CX *CY) groups_cells_kernel(const int32_t *__r
 // Step 6 groups from labels in the deposit's tile order, where neighbours share
 // groups as cells do.  One workgroup counts GCHUNK labels in an LDS table and adds
 // it to the counters once; with MASKED, labels whose mask byte is nonzero are
-// skipped.
+// skipped.  *nrec labels are there: particles that the deposit rejected have none.
 constexpr int GCHUNK = 16384;
 
 template <bool MASKED>
 __global__ void __launch_bounds__(GB) groups_tally_kernel(const int32_t *__restrict__ label,
-                                                          const uint8_t *__restrict__ mask, int64_t count,
-                                                          int64_t ncells, uint32_t *__restrict__ cells,
+                                                          const uint8_t *__restrict__ mask,
+                                                          const uint32_t *__restrict__ nrec, int64_t ncells,
+                                                          uint32_t *__restrict__ cells,
                                                           uint32_t *status) {
     __shared__ int32_t hkey[CELL_HT];
     __shared__ uint32_t hcnt[CELL_HT];
     lds_tally_init<CELL_HT>(hkey, hcnt);
     __syncthreads();
     bool bad = false;
-    const int64_t c0 = int64_t(blockIdx.x) * GCHUNK;
+    const int64_t c0 = int64_t(blockIdx.x) * GCHUNK, count = *nrec;
     const int64_t c1 = c0 + GCHUNK < count ? c0 + GCHUNK : count;
     for (int64_t base = c0; base < c1; base += int64_t(GB) * GPER) {
         int32_t l[GPER];
@@ -142,15 +143,16 @@ static_assert(CELL_RUN == 16, "one 16-byte load of mask bytes per run of labels"
 
 template <bool MASKED>
 __global__ void __launch_bounds__(GB) groups_runs_kernel(const int32_t *__restrict__ label,
-                                                         const uint8_t *__restrict__ mask, int64_t count,
-                                                         int64_t ncells, uint32_t *__restrict__ cells,
+                                                         const uint8_t *__restrict__ mask,
+                                                         const uint32_t *__restrict__ nrec, int64_t ncells,
+                                                         uint32_t *__restrict__ cells,
                                                          uint32_t *status) {
     __shared__ int32_t hkey[CELL_HT];
     __shared__ uint32_t hcnt[CELL_HT];
     lds_tally_init<CELL_HT>(hkey, hcnt);
     __syncthreads();
     bool bad = false;
-    const int64_t c0 = int64_t(blockIdx.x) * GCHUNK;
+    const int64_t c0 = int64_t(blockIdx.x) * GCHUNK, count = *nrec;
     const int64_t c1 = c0 + GCHUNK < count ? c0 + GCHUNK : count;
     for (int64_t b = c0 + int64_t(threadIdx.x) * CELL_RUN; b < c1; b += int64_t(GB) * CELL_RUN) {
         int32_t v[CELL_RUN];
@@ -840,22 +842,22 @@ hf_status hf::groups_count_cells(hf_ctx *ctx, const hf_box &box, const int32_t *
 }
 
 hf_status hf::groups_count_particles_tiled(hf_ctx *ctx, const hf_box &box, const int32_t *label, const uint8_t *mask,
-                                           int64_t np, const GroupCounters &g) {
+                                           const uint32_t *nrec, int64_t np, const GroupCounters &g) {
     if (np <= 0) return HF_OK;
     const dim3 grid(unsigned((np + GCHUNK - 1) / GCHUNK));
     const bool aligned = reinterpret_cast<uintptr_t>(label) % sizeof(int4) == 0 &&
                          reinterpret_cast<uintptr_t>(mask) % sizeof(int4) == 0;
     if (!mask && aligned)
         HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<false>, grid, dim3(GB), 0, ctx->stream, label, nullptr,
-                  np, cells_of(box), g.parts, ctx->d_status);
+                  nrec, cells_of(box), g.parts, ctx->d_status);
     else if (!mask)
         HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_tally_kernel<false>, grid, dim3(GB), 0, ctx->stream, label, nullptr,
-                  np, cells_of(box), g.parts, ctx->d_status);
+                  nrec, cells_of(box), g.parts, ctx->d_status);
     else if (aligned)
-        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, np,
+        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, nrec,
                   cells_of(box), g.parts, ctx->d_status);
     else
-        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_tally_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, np,
+        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_tally_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, nrec,
                   cells_of(box), g.parts, ctx->d_status);
     return launch_status();
 }

@@ -339,7 +339,7 @@ extern "C" hf_status hf_identify(hf_ctx *ctx, const hf_box *box, const void *pos
         if (s == HF_OK) s = groups_count_cells(ctx, *box, sj.max_idx, sj.d_count, sj.max_cap, sj.cell_label, g);
         // particles already claimed are not counted
         if (s == HF_OK && sj.max_cap > 0)
-            s = order ? groups_count_particles_tiled(ctx, *box, lab, j > 0 ? cs8 : nullptr, np, g)
+            s = order ? groups_count_particles_tiled(ctx, *box, lab, j > 0 ? cs8 : nullptr, po.nrec, np, g)
                       : groups_count_particles(ctx, *box, lab, np, g, halo_scale, sw, sb);
         if (s == HF_OK)
             s = groups_decide(ctx, *box, sj.max_idx, sj.d_count, sj.max_cap, g, dens_th, np, particle_th, pass,

@@ -164,3 +164,34 @@ def test_scale_order_and_arguments_checked():
     with pytest.raises(HFError) as e:
         hfm().identify_async(cuda(pos), L, n, [0.008, 0.016], bufs, dens_th=-1.0)
     assert e.value.code == HF_ERR_ARG
+
+
+@pytest.mark.parametrize("n,np_", [(144, 2_500_000), (216, 1 << 23)])
+def test_rejected_positions_are_in_no_group(n, np_):
+    """Particles that the deposit rejects are skipped, labelled -1 and counted
+    nowhere, on grids whose loop runs in the deposit's order (216^3: that of a
+    wider grid), whatever the workspace held."""
+    from paper_2501_10622_amd.hf import HF_ERR_INPUT, HFError
+    L, kws = float(n), [n / 3000.0, n / 1500.0]
+    pos = torch.as_tensor(small_box(n, L, np_, 400, "f32", 3)).cuda()
+    pos[::8, 1] = float("nan")
+    bufs = hfm().identify_buffers(n, np_, 2, "cuda")
+    bufs["ws"].view(torch.int32).fill_(n ** 3 // 2)  # a valid label
+    hfm().identify_async(pos, L, n, kws, bufs, 2.0, 15)
+    with pytest.raises(HFError) as e:
+        hfm().sync()
+    assert e.value.code == HF_ERR_INPUT
+    claimed = torch.zeros(np_, dtype=torch.bool, device="cuda")
+    good = torch.ones(np_, dtype=torch.bool, device="cuda")
+    good[::8] = False
+    for j in range(2):
+        lab = hfm().label(torch.nan_to_num(pos), L, n, bufs["cell_label"][j])
+        free = good & ~claimed & (lab >= 0)
+        roots = bufs["maxima"][j][:int(bufs["count"][j].item())]
+        count = torch.bincount(lab[free].long(), minlength=n ** 3)[roots.long()]
+        assert torch.equal(bufs["group_particles"][j][:roots.numel()].long(), count)
+        kept = torch.zeros(n ** 3, dtype=torch.bool, device="cuda")
+        kept[roots[bufs["group_keep"][j][:roots.numel()] > 0].long()] = True
+        mine = free & kept[lab.clamp_min(0).long()]
+        assert torch.equal(bufs["particle_label"][j][:np_], torch.where(mine, lab, -1))
+        claimed |= mine

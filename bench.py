@@ -40,7 +40,7 @@ TIMER_SYMBOLS = {
     "deposit_l1_hist": ("l1_hist_kernel",), "deposit_l1_scatter": ("l1_scatter_kernel",),
     "deposit_l2_hist": ("l2_hist_kernel",), "deposit_l2_scatter": ("l2_scatter_kernel",),
     "deposit_fold": ("skirt_fold_kernel",),
-    "tables_1": ("tables_kernel",), "fft_x_fwd": ("fft_x_fwd_kernel",),
+    "tables_1": ("tables_kernel", "factors_kernel"), "fft_x_fwd": ("fft_x_fwd_kernel",),
     "fft_y_fwd": ("fft_y_fwd_kernel",), "fft_z_mul": ("fft_z_mul_kernel",),
     "fft_y_inv": ("fft_y_inv_kernel",), "fft_x_inv": ("fft_x_inv_kernel",),
     "maxima_mark": ("max_tile_kernel", "max_direct_kernel"), "maxima_count": ("mask_count_kernel",),
@@ -66,7 +66,7 @@ def log(msg: str):
 STAGES = {
     "deposit": ("zero_grid", "deposit_atomic", "deposit_prep", "deposit_l1_hist", "deposit_l1_scatter",
                 "deposit_l2_hist", "deposit_l2_scatter", "deposit", "deposit_fold"),
-    "cwt_x_fwd": ("tables_1", "fft_x_fwd"),
+    "cwt_x_fwd": ("tables_1", "tables_2", "fft_x_fwd"),
     "cwt_y_fwd": ("fft_y_fwd",),
     "cwt_z_mul": ("fft_z_mul",),
     "cwt_y_inv": ("fft_y_inv",),

@@ -24,11 +24,47 @@ namespace {
 //            minimum-image offset of node j;
 //  analytic: B = exp(-k^2/w^2), P = 32 pi^1.5 w^-3.5 k^2 B (the transform of Eq. (4)).
 // Thread t sums the terms j = t, t + TAB_THREADS, ... and the partial sums are
-// added in a fixed order.  Every workgroup forms the G_j and Hs_j it sums over:
-// a few hundred FP64 exponentials, less than a second launch that would read
-// them from a first one (4.7 us each).
+// added in a fixed order.  Every workgroup forms the G_j and Hs_j it sums over,
+// n (2 images + 1) FP64 exponentials, or (READ) takes them from where
+// factors_kernel put them.
 constexpr int TAB_THREADS = 256;
 
+// n times the images up to which the workgroups form the factors themselves.  Each
+// does all of them, which takes longer than a launch for them where there are many
+// images (scales larger than the box) and the device is full of workgroups.  With
+// the timer's events, 25 to 30 us a launch: n = 1024 71 us with one image, 83 with two,
+// 110 with four (76 in two launches), 720 with 53 (110), 19.4 ms with 1600 (1.36); n =
+// 256 39 us with six, 50 with 16 (69), 1.53 ms with 1600 (1.30).
+constexpr int64_t TAB_OWN_MOST = 2048;
+
+struct Factors {
+    double G, Hs;
+};
+
+__device__ __forceinline__ Factors factors_of(int j, int n, double box_len, double w, int images) {
+    const double dx = box_len / n;
+    const int jc = (j + n / 2) % n - n / 2;
+    Factors f{0.0, 0.0};
+    for (int m = -images; m <= images; ++m) {
+        const double x = jc * dx + m * box_len;
+        const double g = exp(-0.25 * w * w * x * x);
+        f.G += g;
+        f.Hs += x * x * g;
+    }
+    return f;
+}
+
+// Where the factors of a job lie: in its half spectrum, which the x pass writes later.
+__device__ __forceinline__ Factors *factors_at(const CwtJobs &J, const CwtLayout &L, int job) {
+    return reinterpret_cast<Factors *>(J.ws + size_t(job) * J.stride + L.spec);
+}
+
+__global__ void __launch_bounds__(64) factors_kernel(CwtJobs J, CwtLayout L, int n) {
+    const int j = blockIdx.x * 64 + threadIdx.x, job = blockIdx.y;
+    if (j < n) factors_at(J, L, job)[j] = factors_of(j, n, J.box_len[job], J.w[job], J.images[job]);
+}
+
+template <bool READ>
 __global__ void __launch_bounds__(TAB_THREADS) tables_kernel(CwtJobs J, CwtLayout L, int n) {
     const int k = blockIdx.x, job = blockIdx.y;
     char *ws = J.ws + size_t(job) * J.stride;
@@ -55,17 +91,10 @@ __global__ void __launch_bounds__(TAB_THREADS) tables_kernel(CwtJobs J, CwtLayou
     const int step = int((int64_t(TAB_THREADS) * k) % n);  // phase step between a thread's terms
     int ph = int((int64_t(threadIdx.x) * k) % n);
     for (int j = threadIdx.x; j < n; j += TAB_THREADS) {
-        const int jc = (j + n / 2) % n - n / 2;
-        double G = 0.0, Hs = 0.0;
-        for (int m = -J.images[job]; m <= J.images[job]; ++m) {
-            const double x = jc * dx + m * box_len;
-            const double g = exp(-0.25 * w * w * x * x);
-            G += g;
-            Hs += x * x * g;
-        }
+        const Factors f = READ ? factors_at(J, L, job)[j] : factors_of(j, n, box_len, w, J.images[job]);
         const double c = cospi(2.0 * double(ph) / double(n));
-        B += G * c;
-        A += Hs * c;
+        B += f.G * c;
+        A += f.Hs * c;
         ph += step;
         if (ph >= n) ph -= n;
     }
@@ -119,7 +148,15 @@ CwtLayout cwt_layout(int n) {
 // Enqueues the whole transform for J.count same-n jobs.
 hf_status run_cwt(hf_ctx *ctx, int n, const CwtJobs &J) {
     const CwtLayout L = cwt_layout(n);
-    HF_LAUNCH(ctx, K_TABLES_1, tables_kernel, dim3(n, unsigned(J.count)), dim3(TAB_THREADS), 0, ctx->stream, J, L, n);
+    const dim3 each(n, unsigned(J.count));
+    int images = 0;
+    for (int j = 0; j < J.count; ++j) images = J.images[j] > images ? J.images[j] : images;
+    if (J.mode == HF_KERNEL_SAMPLED && int64_t(n) * images > TAB_OWN_MOST) {
+        HF_LAUNCH(ctx, K_TABLES_1, factors_kernel, dim3((n + 63) / 64, unsigned(J.count)), dim3(64), 0, ctx->stream, J, L, n);
+        HF_LAUNCH(ctx, K_TABLES_2, tables_kernel<true>, each, dim3(TAB_THREADS), 0, ctx->stream, J, L, n);
+    } else {
+        HF_LAUNCH(ctx, K_TABLES_1, tables_kernel<false>, each, dim3(TAB_THREADS), 0, ctx->stream, J, L, n);
+    }
     switch (n) {
 #define HF_FFT_CASE(N) \
     case N: return run_cwt_n<N>(ctx, J, L);

@@ -11,9 +11,8 @@
 
 namespace hf {
 
-// Kernels whose launches the optional per-context timer tracks.  TABLES_2 and MASS
-// have none any more (the work is in the TABLES_1 and Y_FWD launches); their names
-// stay in what hf_profile_read lists.
+// Kernels whose launches the optional per-context timer tracks.  MASS has none any
+// more (its work is in the Y_FWD launch); its name stays in what hf_profile_read lists.
 enum KernelId {
     K_ZERO_GRID, K_DEPOSIT, K_LABEL,
     K_DEP_ATOMIC, K_DEP_PREP, K_DEP_L1_HIST, K_DEP_L1_SCATTER, K_DEP_L2_HIST, K_DEP_L2_SCATTER, K_DEP_FOLD,

@@ -463,7 +463,7 @@ extern "C" hf_status hf_identify_grids(hf_ctx *ctx, double box_len, int32_t frac
                             last ? nullptr : scales[j + 1].cwt, pass);
         if (s == HF_OK) s = hf_label(ctx, &b, pos, dtype, np, sj.cell_label, sj.particle_label);
         if (s == HF_OK) s = groups_count_cells(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, sj.cell_label, g);
-        if (s == HF_OK && sj.max_cap > 0) s = 
+        if (s == HF_OK && sj.max_cap > 0)
             s = groups_count_particles(ctx, b, sj.particle_label, np, g, halo_scale, w0, sb);  // a free region
         if (s == HF_OK)
             s = groups_decide(ctx, b, sj.max_idx, sj.d_count, sj.max_cap, g, dens_th, np, particle_th, pass,

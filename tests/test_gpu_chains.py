@@ -37,3 +37,23 @@ def test_path_over_more_boundaries_than_one_launch_follows(n):
     z, y, x = path[-1]
     assert all(got[cell] == (z * n + y) * n + x for cell in path)
     assert np.array_equal(got, O.segment(c))
+
+
+@pytest.mark.parametrize("n", [160, 165])
+def test_path_left_open_by_the_first_of_two_launches(n):
+    """Grids with more than 1024^2 boundary cells, whose chains take a second launch;
+    against parents made by shifts and followed by pointer doubling."""
+    import paper_2501_10622_amd as hfm
+    path = zigzag(n)
+    assert sum(a[2] != b[2] for a, b in zip(path, path[1:])) > 4 * 1024
+    c = torch.full((n, n, n), 0.25, device="cuda:0")
+    z, y, x = torch.as_tensor(path, device="cuda:0").T
+    c[z, y, x] = 1.0 + torch.arange(len(path), device="cuda:0")
+    index = torch.arange(n ** 3, device="cuda:0").view(n, n, n)
+    key = (4.0 * c).long() * n ** 3 + index  # larger value, then larger index
+    for axis in range(3):
+        key = torch.maximum(key, torch.maximum(torch.roll(key, 1, axis), torch.roll(key, -1, axis)))
+    root = (key % n ** 3).view(-1)
+    while not torch.equal(root[root], root):
+        root = root[root]
+    assert torch.equal(hfm.segment(c).view(-1).long(), root)

@@ -190,3 +190,54 @@ def test_identify_grids_matches_the_oracle_on_the_paper_schedule():
         print(f"  not certified tie-free; agreement {agree:.6f}", flush=True)
         assert agree >= LABEL_AGREEMENT
     assert (ref["halo_scale"] >= 0).any()
+
+
+def test_identify_grids_in_smaller_workspaces():
+    """The loop with velocities in the workspace it asks for, in one without the wider
+    grid of the 353^3 deposit, and in one without the members' records either."""
+    import ctypes
+    import synth
+    from paper_2501_10622_amd import hf
+    L, grids, npt = 64.0, [60, 353], 5_000_000
+    pos, vel, m_p = synth.make_phase_box(L, npt, 250, "f32", 31)
+    pos, vel = cuda(pos), cuda(vel)
+    kws = [60 / 3000.0, 353 / 4000.0]
+    bufs = hfm().identify_grids_buffers(grids, npt, pos.device, L, with_velocities=True)
+    without = hfm().identify_grids_buffers(grids, npt, pos.device, L)["ws"].numel()
+
+    def up(b):
+        return (b + 255) // 256 * 256
+
+    def check_size(g, j):
+        out, b = ctypes.c_size_t(), hf.box(g, L)
+        assert hf.load_library().hf_unbind_ws_size(ctypes.byref(b), npt, bufs["maxima"][j].numel(), ctypes.byref(out)) == 0
+        return out.value
+
+    least = hf.STAGE_STENCIL | hf.STAGE_MAXIMA | hf.STAGE_SEGMENT
+    asked = max(hf.workspace_size(g, L, npt, least | hf.STAGE_DEPOSIT) for g in grids)
+    # 353^3 deposits without a workspace, 60^3 needs its own
+    stages = max(hf.workspace_size(60, L, npt, least | hf.STAGE_DEPOSIT), hf.workspace_size(353, L, npt, least))
+    check = max(check_size(g, j) for j, g in enumerate(grids))
+    records = up(4 * npt) + up(48 * npt)
+    sizes = [without - up(asked) + up(max(s, c)) for s, c in ((asked, check), (stages, check), (stages, check - records))]
+    assert sizes[0] == bufs["ws"].numel() and sizes[0] > sizes[1] > sizes[2]
+    room, first = bufs["ws"], None
+    for size in sizes:
+        bufs["ws"] = room[:size]
+        room.fill_(0x41)
+        hfm().identify_grids_async(pos, L, kws, bufs, 2.0, 15, vel=vel, grav_mass=O.GRAV * m_p)
+        hfm().sync()
+        assert bool((room[size:] == 0x41).all())
+        got = [bufs["halo_scale"], bufs["halo_root"]]
+        for j in range(2):
+            cnt = int(bufs["count"][j].item())
+            got += [bufs[k][j] for k in ("rho", "cwt", "cell_label", "particle_label")]
+            got += [bufs[k][j][:cnt] for k in ("maxima", "group_particles", "group_cells", "group_keep", "bound_keep")]
+        got = [t.clone() for t in got]
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(first, got))
+    assert bool((bufs["halo_scale"] >= 0).any())
+    bufs["ws"] = room[:sizes[2] - 256]
+    with pytest.raises(hf.HFError) as e:
+        hfm().identify_grids_async(pos, L, kws, bufs, 2.0, 15, vel=vel, grav_mass=O.GRAV * m_p)
+    assert e.value.code == hf.HF_ERR_WORKSPACE

@@ -43,14 +43,16 @@ TIMER_SYMBOLS = {
     "tables_1": ("tables_kernel", "factors_kernel"), "fft_x_fwd": ("fft_x_fwd_kernel",),
     "fft_y_fwd": ("fft_y_fwd_kernel",), "fft_z_mul": ("fft_z_mul_kernel",),
     "fft_y_inv": ("fft_y_inv_kernel",), "fft_x_inv": ("fft_x_inv_kernel",),
-    "maxima_mark": ("max_tile_kernel", "max_direct_kernel"), "maxima_count": ("mask_count_kernel",),
-    "maxima_scan": ("one_scan_kernel<1>", "seg_reduce_kernel<1>", "seg_scan_kernel<1>"), "maxima_write": ("list_write_kernel", "list_short_kernel"),
-    "parent": ("parent_resolve_kernel",), "jump_flags": ("zero_words_kernel",),
+    "maxima_count": ("mask_count_kernel",),
+    "maxima_scan": ("one_scan_kernel<1>", "seg_reduce_kernel<1>", "seg_scan_kernel<1>"),
+    "maxima_write": ("list_write_kernel", "list_short_kernel"),
+    "parent": ("parent_resolve_kernel",),  # (without the chains under the timer's "maxima_mark")
+    "jump_flags": ("zero_words_kernel",),
     "jump": ("bnd_chase_kernel",), "finalize": ("seg_finalize_kernel",),
     "label_tiles": ("tile_label_kernel",), "label_level1": ("to_level1_kernel",), "label_input": ("to_input_kernel",),
     "groups_clear": ("groups_clear_kernel",), "groups_cells": ("groups_cells_kernel",),
-    "groups_particles": ("groups_particles_kernel", "groups_runs_kernel<false>", "groups_tally_kernel<false>",
-                         "groups_runs_kernel<true>", "groups_tally_kernel<true>"), "groups_decide": ("groups_decide_kernel",),
+    "groups_particles": ("groups_particles_kernel", "groups_runs_kernel<false>", "groups_runs_kernel<true>"),
+    "groups_decide": ("groups_decide_kernel",),
     "groups_filter": ("groups_filter_kernel",),
     "stencil_x": ("stencil_x_kernel",), "stencil_mass": ("stencil_mass_kernel",),
     "stencil_y": ("stencil_axis_kernel<false>",), "stencil_z": ("stencil_axis_kernel<true>",),
@@ -126,8 +128,7 @@ def short_symbol(name: str) -> str:
     tmpl = m.group(2) or ""
     # keep a template argument only where it names a different pass (the scans' use)
     return m.group(1) + (tmpl if m.group(1) in ("one_scan_kernel", "seg_reduce_kernel", "seg_scan_kernel",
-                                                               "stencil_axis_kernel", "groups_tally_kernel",
-                                                               "groups_runs_kernel") else "")
+                                                               "stencil_axis_kernel", "groups_runs_kernel") else "")
 
 
 def timer_name(symbol: str):

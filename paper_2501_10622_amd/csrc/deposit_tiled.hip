@@ -178,14 +178,6 @@ __device__ __forceinline__ void load_q_batch(const T *__restrict__ pos, int64_t 
     convert_raw(raw, i0, stride, end, fp, q, valid, bad);
 }
 
-template <typename T>
-__device__ __forceinline__ bool load_q(const T *__restrict__ pos, int64_t i, const FixedPoint<T> &fp, Q3 &q) {
-    bool ok = fp.q(pos[3 * i + 0], q.x);
-    ok = fp.q(pos[3 * i + 1], q.y) && ok;
-    ok = fp.q(pos[3 * i + 2], q.z) && ok;
-    return ok;
-}
-
 // In-place exclusive scan of s[0..count) (count <= 512) by the whole workgroup
 // (at least 512 threads); returns the total.  Each wavefront scans 64 entries
 // with shuffles, then the wavefront totals are scanned; tmp holds 8 partials.

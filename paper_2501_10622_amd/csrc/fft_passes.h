@@ -56,9 +56,6 @@ struct PlanOf {
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 // a (wr + i wi) with the roundings spelled out: of the two products of the real
 // part, and of the imaginary part, the one with a.x (X) or a.y (Y) is rounded and
 // goes into the fused multiply-add of the other.  Left to the compiler, the choice
@@ -98,7 +95,9 @@ __device__ __forceinline__ void dft4(float2 &v0, float2 &v1, float2 &v2, float2 
 // Where a transform stands: between stages, at a pass's end with its outputs
 // going to global memory, at the z pass's seam, or as the z pass's only stage.
 // The radix-16 transform has roundings of its own in each, those of the kernels
-// that made the fields so far, and the fields are the same bits on.
+// for all sizes that made the fields before (the same bits at every size when these
+// took their place; the tests hold the fields to a tolerance against FP64).  Radix 8
+// and the multiplier leave the choice to the compiler.
 enum class Place { Mid, End, Seam, Only };
 
 template <int R, bool INV, Place PLACE = Place::Mid>

@@ -96,48 +96,12 @@ __global__ void __launch_bounds__(CX *CY) groups_cells_kernel(const int32_t *__r
 
 // Step 6 groups from labels in the deposit's tile order, where neighbours share
 // groups as cells do.  One workgroup counts GCHUNK labels in an LDS table and adds
-// it to the counters once; with MASKED, labels whose mask byte is nonzero are
-// skipped.  *nrec labels are there: particles that the deposit rejected have none.
+// it to the counters once; each thread takes CELL_RUN consecutive labels (one vector
+// load per four) and adds each run of equal labels to the table once, so a run costs
+// one insert instead of one per label.  With MASKED, labels whose mask byte is nonzero
+// are skipped.  *nrec labels are there: particles that the deposit rejected have none.
+// Both arrays 16-byte aligned (they lie in the workspace).
 constexpr int GCHUNK = 16384;
-
-template <bool MASKED>
-__global__ void __launch_bounds__(GB) groups_tally_kernel(const int32_t *__restrict__ label,
-                                                          const uint8_t *__restrict__ mask,
-                                                          const uint32_t *__restrict__ nrec, int64_t ncells,
-                                                          uint32_t *__restrict__ cells,
-                                                          uint32_t *status) {
-    __shared__ int32_t hkey[CELL_HT];
-    __shared__ uint32_t hcnt[CELL_HT];
-    lds_tally_init<CELL_HT>(hkey, hcnt);
-    __syncthreads();
-    bool bad = false;
-    const int64_t c0 = int64_t(blockIdx.x) * GCHUNK, count = *nrec;
-    const int64_t c1 = c0 + GCHUNK < count ? c0 + GCHUNK : count;
-    for (int64_t base = c0; base < c1; base += int64_t(GB) * GPER) {
-        int32_t l[GPER];
-#pragma unroll
-        for (int k = 0; k < GPER; ++k) {
-            const int64_t i = base + k * GB + threadIdx.x;
-            l[k] = i < c1 ? label[i] : -1;
-            if (MASKED && i < c1 && mask[i]) l[k] = -1;
-        }
-#pragma unroll
-        for (int k = 0; k < GPER; ++k) {
-            if (l[k] >= ncells || l[k] < -1) {
-                bad = true;
-                l[k] = -1;
-            }
-            lds_tally_wave<CELL_HT>(hkey, hcnt, cells, l[k]);
-        }
-    }
-    __syncthreads();
-    lds_tally_flush<CELL_HT>(hkey, hcnt, cells);
-    if (bad) atomicOr(status, ST_INPUT);
-}
-
-// The same by runs: each thread takes CELL_RUN consecutive labels (one vector
-// load per four) and adds each run of equal labels to the LDS table once, so a run
-// costs one insert instead of one per label.  Both arrays 16-byte aligned.
 constexpr int CELL_RUN = 16;
 static_assert(CELL_RUN == 16, "one 16-byte load of mask bytes per run of labels");
 
@@ -845,20 +809,12 @@ hf_status hf::groups_count_particles_tiled(hf_ctx *ctx, const hf_box &box, const
                                            const uint32_t *nrec, int64_t np, const GroupCounters &g) {
     if (np <= 0) return HF_OK;
     const dim3 grid(unsigned((np + GCHUNK - 1) / GCHUNK));
-    const bool aligned = reinterpret_cast<uintptr_t>(label) % sizeof(int4) == 0 &&
-                         reinterpret_cast<uintptr_t>(mask) % sizeof(int4) == 0;
-    if (!mask && aligned)
-        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<false>, grid, dim3(GB), 0, ctx->stream, label, nullptr,
-                  nrec, cells_of(box), g.parts, ctx->d_status);
-    else if (!mask)
-        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_tally_kernel<false>, grid, dim3(GB), 0, ctx->stream, label, nullptr,
-                  nrec, cells_of(box), g.parts, ctx->d_status);
-    else if (aligned)
+    if (mask)
         HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, nrec,
                   cells_of(box), g.parts, ctx->d_status);
     else
-        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_tally_kernel<true>, grid, dim3(GB), 0, ctx->stream, label, mask, nrec,
-                  cells_of(box), g.parts, ctx->d_status);
+        HF_LAUNCH(ctx, K_GROUP_PARTICLES, groups_runs_kernel<false>, grid, dim3(GB), 0, ctx->stream, label, nullptr,
+                  nrec, cells_of(box), g.parts, ctx->d_status);
     return launch_status();
 }
 

@@ -224,7 +224,8 @@ hf_status groups_count_particles(hf_ctx *ctx, const hf_box &box, const int32_t *
                                  const GroupCounters &g, const int32_t *skip = nullptr, void *scratch = nullptr,
                                  size_t scratch_bytes = 0);
 // The same count over the *nrec (at most np) labels in the deposit's tile order (LDS
-// tables; entries whose mask byte is nonzero skipped; mask may be null).
+// tables; entries whose mask byte is nonzero skipped; mask may be null; both 16-byte
+// aligned).
 hf_status groups_count_particles_tiled(hf_ctx *ctx, const hf_box &box, const int32_t *label, const uint8_t *mask,
                                        const uint32_t *nrec, int64_t np, const GroupCounters &g);
 // Decides every group and writes the per-group outputs; then, where given,

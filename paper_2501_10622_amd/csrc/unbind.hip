@@ -28,7 +28,7 @@
 // Nothing here streams: what bounds a group is the chain of its rounds' short
 // loops (dependent loads, LDS passes of the sorts), and what bounds the launch is
 // the largest groups' chains, since most groups have a few hundred members and
-// a few have ten thousand.  So a large group gets a whole CU (16 wavefronts, 96
+// a few have ten thousand.  So a large group gets a whole CU (16 wavefronts, 153
 // KB of LDS) and the largest ones start first, while a small group gets one
 // wavefront, whose sorts and sums need no barrier.  Both sorts go by bins (a
 // histogram, a scan, and a count of the smaller ones in a member's own bin:
@@ -1002,6 +1002,8 @@ __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, cons
     __shared__ double red[6 * UB_WAVES];
     __shared__ uint32_t count[1 + UB_WAVES];
     __shared__ uint32_t s_next;
+    static_assert(sizeof(sort_lds) + sizeof(bins) + sizeof(red) + sizeof(count) + sizeof(s_next) <= 160 * 1024,
+                  "a CU's LDS");
     const uint32_t nhuge = queue[Q_HUGE], nbig = nhuge + queue[Q_MID], nsmall = queue[Q_SMALL];
     const TeamLds whole{sort_lds, reinterpret_cast<uint32_t *>(sort_lds + UB_CHUNK), bins, red, count};
     for (;;) {

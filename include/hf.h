@@ -118,7 +118,7 @@ const char *hf_status_str(hf_status s);
  * device-detected error, highest code first: INPUT, OVERFLOW, CAPACITY. */
 hf_status hf_sync(hf_ctx *ctx);
 
-/* Bytes of workspace the selected stages need for this box and particle count. */
+/* Bytes of workspace the selected stages ask for at this box and particle count. */
 hf_status hf_workspace_size(const hf_box *box, int64_t np, int stage_mask, size_t *bytes);
 
 /* Step 2, Eq. (1): cloud-in-cell deposit.
@@ -496,6 +496,20 @@ hf_status hf_unbind_ws_size(const hf_box *box, int64_t np, int64_t nroots, size_
 hf_status hf_unbind(hf_ctx *ctx, const hf_box *box, const void *pos, const void *vel, hf_dtype dtype, int64_t np,
                     const int32_t *roots, int64_t nroots, const uint8_t *group_keep, int32_t *particle_label,
                     double grav_mass, int64_t particle_th, uint8_t *bound_keep, void *ws, size_t ws_bytes);
+
+/* Parts of a workspace only save time: the wider grid that a deposit is binned on
+ * where n's own tiles have no buckets, the particle order kept from such a grid (n
+ * no multiple of 16, for one), the partition of hf_groups and the members' records
+ * of hf_unbind.  A call whose workspace is smaller than asked for but has room for
+ * the rest does without them: the same results, slower.  These give the least that
+ * each call takes, for the arguments of the function without `_least`. */
+hf_status hf_workspace_size_least(const hf_box *box, int64_t np, int stage_mask, size_t *bytes);
+hf_status hf_find_halos_scales_ws_size_least(const hf_box *box, int64_t np, int32_t count, size_t *bytes);
+hf_status hf_identify_ws_size_least(const hf_box *box, int64_t np, int32_t count, const hf_scale_job *scales,
+                                    size_t *bytes);
+hf_status hf_identify_grids_ws_size_least(double box_len, int32_t frac_bits, int64_t np, int32_t count,
+                                          const hf_grid_scale *scales, int32_t with_velocities, size_t *bytes);
+hf_status hf_unbind_ws_size_least(const hf_box *box, int64_t np, int64_t nroots, size_t *bytes);
 
 /* Serving form of steps 2-6 for `count` (1..HF_CWT_BATCH_MAX) boxes of the same
  * grid size n: the deposits, ONE batched transform (hf_cwt_batch) for the group,

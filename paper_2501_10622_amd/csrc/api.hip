@@ -192,6 +192,10 @@ extern "C" hf_status hf_workspace_size(const hf_box *box, int64_t np, int stage_
     return stage_ws_size(box, np, stage_mask, false, bytes);
 }
 
+extern "C" hf_status hf_workspace_size_least(const hf_box *box, int64_t np, int stage_mask, size_t *bytes) {
+    return stage_ws_size(box, np, stage_mask, true, bytes);
+}
+
 hf_status hf::stage_ws_size(const hf_box *box, int64_t np, int stage_mask, bool least, size_t *bytes) {
     if (!bytes || np < 0) return HF_ERR_ARG;
     hf_status s = (stage_mask & HF_STAGE_CWT) ? check_box(box) : check_box_grid(box);
@@ -218,7 +222,7 @@ hf_status hf::stage_ws_size(const hf_box *box, int64_t np, int stage_mask, bool 
     const bool groups_apart = order && (stage_mask & HF_STAGE_GROUPS);
     if ((stage_mask & HF_STAGE_GROUPS) && !groups_apart) take(groups_ws_bytes(*box));
     // hf_groups on its own (its stage alone): room for its partitioned count
-    if (stage_mask == HF_STAGE_GROUPS) take(groups_ws_bytes(*box) + groups_part_ws_bytes(*box, np));
+    if (stage_mask == HF_STAGE_GROUPS && !least) take(groups_ws_bytes(*box) + groups_part_ws_bytes(*box, np));
     *bytes = (order ? particle_order_bytes(*box, np) : 0) + (groups_apart ? groups_ws_bytes(*box) : 0) + need;
     return HF_OK;
 }

@@ -166,6 +166,10 @@ extern "C" hf_status hf_find_halos_scales_ws_size(const hf_box *box, int64_t np,
     return scales_ws_size(box, np, count, false, bytes);
 }
 
+extern "C" hf_status hf_find_halos_scales_ws_size_least(const hf_box *box, int64_t np, int32_t count, size_t *bytes) {
+    return scales_ws_size(box, np, count, true, bytes);
+}
+
 extern "C" hf_status hf_find_halos_scales(hf_ctx *ctx, const hf_box *box, const void *pos, hf_dtype dtype, int64_t np,
                                           hf_kernel kernel, float tau, int64_t *rho, int32_t count,
                                           const hf_scale_job *scales, void *ws, size_t ws_bytes) {
@@ -252,6 +256,15 @@ extern "C" hf_status hf_identify_ws_size(const hf_box *box, int64_t np, int32_t 
     if (!bytes) return HF_ERR_ARG;
     IdentifyLayout L{};
     hf_status s = identify_layout(box, np, count, scales, false, L);
+    if (s == HF_OK) *bytes = L.total;
+    return s;
+}
+
+extern "C" hf_status hf_identify_ws_size_least(const hf_box *box, int64_t np, int32_t count,
+                                               const hf_scale_job *scales, size_t *bytes) {
+    if (!bytes) return HF_ERR_ARG;
+    IdentifyLayout L{};
+    hf_status s = identify_layout(box, np, count, scales, true, L);
     if (s == HF_OK) *bytes = L.total;
     return s;
 }
@@ -401,6 +414,16 @@ extern "C" hf_status hf_identify_grids_ws_size(double box_len, int32_t frac_bits
     if (!bytes) return HF_ERR_ARG;
     GridsLayout L{};
     hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, true, false, L);
+    if (s == HF_OK) *bytes = L.total;
+    return s;
+}
+
+extern "C" hf_status hf_identify_grids_ws_size_least(double box_len, int32_t frac_bits, int64_t np, int32_t count,
+                                                    const hf_grid_scale *scales, int32_t with_velocities,
+                                                    size_t *bytes) {
+    if (!bytes) return HF_ERR_ARG;
+    GridsLayout L{};
+    hf_status s = grids_layout(box_len, frac_bits, np, count, scales, with_velocities != 0, false, true, L);
     if (s == HF_OK) *bytes = L.total;
     return s;
 }

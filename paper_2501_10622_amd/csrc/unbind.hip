@@ -1120,6 +1120,14 @@ extern "C" hf_status hf_unbind_ws_size(const hf_box *box, int64_t np, int64_t nr
     return HF_OK;
 }
 
+extern "C" hf_status hf_unbind_ws_size_least(const hf_box *box, int64_t np, int64_t nroots, size_t *bytes) {
+    if (!bytes || np < 0 || nroots < 0) return HF_ERR_ARG;
+    hf_status s = check_box_grid(box);
+    if (s != HF_OK) return s;
+    *bytes = unbind_ws_bytes(*box, np, nroots, false);
+    return HF_OK;
+}
+
 extern "C" hf_status hf_unbind(hf_ctx *ctx, const hf_box *box, const void *pos, const void *vel, hf_dtype dtype,
                                int64_t np, const int32_t *roots, int64_t nroots, const uint8_t *group_keep,
                                int32_t *particle_label, double grav_mass, int64_t particle_th,

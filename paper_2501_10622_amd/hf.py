@@ -29,7 +29,8 @@ EXPORTS = ("hf_create", "hf_destroy", "hf_status_str", "hf_sync", "hf_workspace_
            "hf_find_halos_scales_ws_size", "hf_find_halos_scales", "hf_cross_scale", "hf_peaks",
            "hf_cwt_stencil", "hf_stencil_half_width", "hf_identify_ws_size", "hf_identify",
            "hf_find_halos_noalloc", "hf_identify_grids_ws_size", "hf_identify_grids", "hf_unbind_ws_size",
-           "hf_unbind")
+           "hf_unbind", "hf_workspace_size_least", "hf_find_halos_scales_ws_size_least", "hf_identify_ws_size_least",
+           "hf_identify_grids_ws_size_least", "hf_unbind_ws_size_least")
 CWT_BATCH_MAX = 32
 STAGE_ALL = 31
 STAGE_GROUPS = 32
@@ -150,6 +151,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
             "hf_find_halos_filtered": (ctypes.c_int, [vp, bp, ctypes.POINTER(Job), ctypes.POINTER(GroupFilter), vp,
                                                       sz]),
         }
+        sig |= {f"{name}_least": sig[name] for name in list(sig) if f"{name}_least" in EXPORTS}
         for name, (res, args) in sig.items():
             fn = getattr(lib, name)
             fn.restype = res
@@ -240,8 +242,30 @@ def context(device=None, stream=None) -> Context:
     return ctx
 
 
-def workspace(nbytes: int, ctx: Context) -> torch.Tensor:
-    """A reusable device workspace of at least nbytes, one per (device, stream).
+def _allocate(asked: int, least: int, device) -> torch.Tensor:
+    """Bytes for a workspace: as many as the call asks for, or, where the device has
+    no room for those, the least that it takes."""
+    try:
+        return torch.empty(max(asked, 256), dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        if least >= asked:
+            raise
+        return torch.empty(max(least, 256), dtype=torch.uint8, device=device)
+
+
+def _ws_sizes(call: str, *args) -> tuple:
+    """What ``call`` (a workspace size function) asks for, and the least."""
+    out = []
+    for name in (call, f"{call}_least"):
+        size = ctypes.c_size_t()
+        _check(getattr(load_library(), name)(*args, ctypes.byref(size)), name)
+        out.append(size.value)
+    return tuple(out)
+
+
+def workspace(nbytes: int, ctx: Context, least: int | None = None) -> torch.Tensor:
+    """A reusable device workspace of at least nbytes (or ``least`` where the device
+    has no room for those), one per (device, stream).
 
     It is allocated on the context's own stream, the only stream its kernels
     run on, so when a larger one replaces it the caching allocator cannot hand
@@ -250,9 +274,12 @@ def workspace(nbytes: int, ctx: Context) -> torch.Tensor:
     key = (ctx.device, ctx.stream.cuda_stream)
     cur = _ws.get(key)
     if cur is None or cur.numel() < nbytes:
+        # a kept one that has room for the least does where there is no room for more
+        least = nbytes if least is None else (0 if cur is not None and cur.numel() >= least else least)
         with torch.cuda.stream(ctx.stream):
-            cur = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=torch.device("cuda", ctx.device))
-        _ws[key] = cur
+            new = _allocate(nbytes, least, torch.device("cuda", ctx.device))
+        if cur is None or new.numel() > cur.numel():
+            _ws[key] = cur = new
     return cur
 
 
@@ -292,10 +319,10 @@ def deposit(pos: torch.Tensor, box_len: float, n: int, frac_bits: int = 15, out=
     if out is None:
         out = torch.empty((n, n, n), dtype=torch.int64, device=pos.device)
     b = box(n, box_len, frac_bits)
-    need = workspace_size(n, box_len, pos.shape[0], STAGE_DEPOSIT, frac_bits)
-    ws = workspace(need, ctx) if need else None
+    need, least = _ws_sizes("hf_workspace_size", ctypes.byref(b), pos.shape[0], STAGE_DEPOSIT)
+    ws = workspace(need, ctx, least) if need else None
     _check(load_library().hf_deposit(ctx.handle, ctypes.byref(b), _ptr(pos), _dtype_code(pos), pos.shape[0],
-                                     _ptr(out), _ptr(ws), need), "hf_deposit")
+                                     _ptr(out), _ptr(ws), min(need, ws.numel()) if need else 0), "hf_deposit")
     return out
 
 
@@ -548,7 +575,8 @@ def job_buffers(n: int, np_: int, device, with_cwt_ws: bool = True, frac_bits: i
         stages |= STAGE_GROUPS
     if with_stencil:  # the stencil transform's workspace instead of the FFT's (any n)
         stages = (stages & ~STAGE_CWT) | STAGE_STENCIL
-    need = workspace_size(n, 1.0, np_, stages, frac_bits)
+    b = box(n, 1.0, frac_bits)
+    sizes = _ws_sizes("hf_workspace_size", ctypes.byref(b), int(np_), stages)
     cap = ((n + 1) // 2) ** 3
     extra = {}
     if with_groups:
@@ -565,7 +593,7 @@ def job_buffers(n: int, np_: int, device, with_cwt_ws: bool = True, frac_bits: i
         "count": torch.empty(1, dtype=torch.int64, device=device),
         "cell_label": torch.empty((n, n, n), dtype=torch.int32, device=device),
         "particle_label": torch.empty(max(np_, 1), dtype=torch.int32, device=device),
-        "ws": torch.empty(max(need, 256), dtype=torch.uint8, device=device),
+        "ws": _allocate(*sizes, device),
     }
 
 
@@ -598,10 +626,8 @@ def find_halos_noalloc_async(pos: torch.Tensor, box_len: float, n: int, kw: floa
 
 def scales_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) -> dict:
     """Outputs (one list entry per scale) and workspace for find_halos_scales_async."""
-    out = ctypes.c_size_t()
     b = box(n, 1.0, frac_bits)
-    _check(load_library().hf_find_halos_scales_ws_size(ctypes.byref(b), int(np_), int(count), ctypes.byref(out)),
-           "hf_find_halos_scales_ws_size")
+    sizes = _ws_sizes("hf_find_halos_scales_ws_size", ctypes.byref(b), int(np_), int(count))
     cap = ((n + 1) // 2) ** 3
     return {
         "rho": torch.empty((n, n, n), dtype=torch.int64, device=device),
@@ -610,7 +636,7 @@ def scales_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) ->
         "count": [torch.empty(1, dtype=torch.int64, device=device) for _ in range(count)],
         "cell_label": [torch.empty((n, n, n), dtype=torch.int32, device=device) for _ in range(count)],
         "particle_label": [torch.empty(max(np_, 1), dtype=torch.int32, device=device) for _ in range(count)],
-        "ws": torch.empty(max(out.value, 256), dtype=torch.uint8, device=device),
+        "ws": _allocate(*sizes, device),
     }
 
 
@@ -651,12 +677,11 @@ def identify_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) 
     bufs["group_keep"] = [torch.empty(cap, dtype=torch.uint8, device=device) for _ in range(count)]
     bufs["halo_scale"] = torch.empty(max(np_, 1), dtype=torch.int32, device=device)
     bufs["halo_root"] = torch.empty(max(np_, 1), dtype=torch.int32, device=device)
-    out = ctypes.c_size_t()
     b = box(n, 1.0, frac_bits)
     jobs = _scale_jobs([1.0 + j for j in range(count)], bufs)
-    _check(load_library().hf_identify_ws_size(ctypes.byref(b), int(np_), int(count), jobs, ctypes.byref(out)),
-           "hf_identify_ws_size")
-    bufs["ws"] = torch.empty(max(out.value, 256), dtype=torch.uint8, device=device)
+    sizes = _ws_sizes("hf_identify_ws_size", ctypes.byref(b), int(np_), int(count), jobs)
+    del bufs["ws"]  # that of the scales alone makes room
+    bufs["ws"] = _allocate(*sizes, device)
     return bufs
 
 
@@ -717,12 +742,9 @@ def identify_grids_buffers(grids, np_: int, device, box_len: float = 1.0, frac_b
         "halo_scale": torch.empty(max(np_, 1), dtype=torch.int32, device=device),
         "halo_root": torch.empty(max(np_, 1), dtype=torch.int32, device=device),
     }
-    out = ctypes.c_size_t()
     jobs = _grid_scales([0.1 * (j + 1) for j in range(count)], bufs)
-    _check(load_library().hf_identify_grids_ws_size(float(box_len), int(frac_bits), int(np_), count, jobs,
-                                                    int(bool(with_velocities)), ctypes.byref(out)),
-           "hf_identify_grids_ws_size")
-    bufs["ws"] = torch.empty(max(out.value, 256), dtype=torch.uint8, device=device)
+    bufs["ws"] = _allocate(*_ws_sizes("hf_identify_grids_ws_size", float(box_len), int(frac_bits), int(np_), count, jobs,
+                                      int(bool(with_velocities))), device)
     return bufs
 
 
@@ -762,15 +784,13 @@ def unbind(pos: torch.Tensor, vel: torch.Tensor, box_len: float, n: int, roots: 
         raise ValueError("roots and particle_label must be int32, group_keep uint8")
     ctx = ctx or context(pos.device.index)
     b = box(n, box_len, frac_bits)
-    out = ctypes.c_size_t()
-    _check(load_library().hf_unbind_ws_size(ctypes.byref(b), pos.shape[0], roots.numel(), ctypes.byref(out)),
-           "hf_unbind_ws_size")
-    ws = workspace(out.value, ctx)
+    need, least = _ws_sizes("hf_unbind_ws_size", ctypes.byref(b), pos.shape[0], roots.numel())
+    ws = workspace(need, ctx, least)
     bound = torch.empty(max(roots.numel(), 1), dtype=torch.uint8, device=pos.device)[: roots.numel()]
     _check(load_library().hf_unbind(ctx.handle, ctypes.byref(b), _ptr(pos), _ptr(vel), _dtype_code(pos),
                                     pos.shape[0], _ptr(roots), roots.numel(), _ptr(group_keep),
                                     _ptr(particle_label), float(grav_mass), int(particle_th), _ptr(bound),
-                                    _ptr(ws), out.value), "hf_unbind")
+                                    _ptr(ws), min(need, ws.numel())), "hf_unbind")
     return bound
 
 

@@ -17,6 +17,7 @@
 // in FP64 between the x and y passes.  (A fused x-y pass over 2D tiles, which
 // keeps fA and fB in LDS, measured slower than the two passes.)
 #include <cmath>
+#include <type_traits>
 
 #include "hf_internal.h"
 
@@ -169,30 +170,39 @@ __global__ void __launch_bounds__(ST_THREADS)
     unsigned long long lo = 0, hi = 0;
     bool neg = false;
     // a wavefront stages whole rows, X_BATCH loads in flight per lane: slot q = lane
-    // + 64 i keeps its place in its block, and lies 8 i blocks on
+    // + 64 i keeps its place in its block, and lies 8 i blocks on; of rows that take
+    // half a batch or a quarter of it, two or four together (a call at 63^3 27.1 us with
+    // one at a time, 23.8 so)
     static_assert(ST_K == 8, "64 slots are 8 blocks");
     const int lane = tid & 63;
-    for (int r = tid >> 6; r < rows; r += ST_THREADS / 64) {
-        const int64_t *__restrict__ src = rho + (row0 + r) * n;
-        float *dst = buf + r * RF + (lane % ST_K) * LB + lane / ST_K + 1;
-        for (int i0 = 0; i0 * 64 < W; i0 += X_BATCH) {
-            int64_t v[X_BATCH];
-            bool own[X_BATCH];  // each cell counted once, from its own slot
+    auto stage = [&](auto together) {
+        constexpr int R = decltype(together)::value, PARTS = X_BATCH / R, WAVES = ST_THREADS / 64;
+        for (int r0 = tid >> 6; r0 < rows; r0 += WAVES * R) {
+            const int64_t *__restrict__ src = rho + (row0 + r0) * n;
+            float *dst = buf + r0 * RF + (lane % ST_K) * LB + lane / ST_K + 1;
+            for (int i0 = 0; i0 * 64 < W; i0 += PARTS) {
+                int64_t v[X_BATCH];
+                bool own[X_BATCH];  // each cell counted once, from its own slot
 #pragma unroll
-            for (int u = 0; u < X_BATCH; ++u) {
-                const int q = lane + 64 * (i0 + u), x = q - hp;
-                own[u] = unsigned(x) < unsigned(n);
-                v[u] = 0;
-                if (q < W) v[u] = src[wrapq(x, n)];
-            }
+                for (int u = 0; u < X_BATCH; ++u) {
+                    const int k = WAVES * (u / PARTS), q = lane + 64 * (i0 + u % PARTS), x = q - hp;
+                    own[u] = unsigned(x) < unsigned(n);
+                    v[u] = 0;
+                    if (q < W && (k == 0 || r0 + k < rows)) v[u] = src[k * n + wrapq(x, n)];
+                }
 #pragma unroll
-            for (int u = 0; u < X_BATCH; ++u) {
-                neg |= v[u] < 0;
-                add128(lo, hi, own[u] ? static_cast<unsigned long long>(v[u]) : 0ull);
-                if (lane + 64 * (i0 + u) < W) dst[8 * (i0 + u)] = float(v[u]);
+                for (int u = 0; u < X_BATCH; ++u) {
+                    const int k = WAVES * (u / PARTS), i = i0 + u % PARTS;
+                    neg |= v[u] < 0;
+                    add128(lo, hi, own[u] ? static_cast<unsigned long long>(v[u]) : 0ull);
+                    if (lane + 64 * i < W && (k == 0 || r0 + k < rows)) dst[k * RF + 8 * i] = float(v[u]);
+                }
             }
         }
-    }
+    };
+    if (W <= 64 * (X_BATCH / 4)) stage(std::integral_constant<int, 4>{});
+    else if (W <= 64 * (X_BATCH / 2)) stage(std::integral_constant<int, 2>{});
+    else stage(std::integral_constant<int, 1>{});
     if (neg) atomicOr(status, ST_INPUT);
     block_mass(lo, hi, mass + blockIdx.x);  // its barrier also publishes the row buffers
     const float a0 = wa[0];

@@ -992,7 +992,10 @@ __device__ void check_group(uint32_t g, const UnbindJob<T> &jb, const TeamLds &l
 
 // Persistent, one workgroup per CU: first the workgroups take the huge and then
 // the middle groups from their list, one at a time; when it is empty, each
-// wavefront takes small groups for itself.
+// wavefront takes small groups for itself.  No more of either take than there may be
+// groups for (a wavefront per small group beside those of the workgroups that big
+// ones keep busy): the takes of 4096 wavefronts from one counter are 50 us, which a
+// launch with a few groups, or none, would last.
 template <typename T>
 __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, const uint32_t *__restrict__ big,
                                                            int64_t cap, const uint32_t *__restrict__ small,
@@ -1006,7 +1009,7 @@ __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, cons
                   "a CU's LDS");
     const uint32_t nhuge = queue[Q_HUGE], nbig = nhuge + queue[Q_MID], nsmall = queue[Q_SMALL];
     const TeamLds whole{sort_lds, reinterpret_cast<uint32_t *>(sort_lds + UB_CHUNK), bins, red, count};
-    for (;;) {
+    while (blockIdx.x < nbig) {
         if (threadIdx.x == 0) s_next = atomicAdd(queue + Q_TAKE_BIG, 1u);
         __syncthreads();
         const uint32_t k = s_next;
@@ -1015,6 +1018,8 @@ __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, cons
         check_group<UB_WAVES>(k < nhuge ? big[k] : big[cap - 1 - int64_t(k - nhuge)], jb, whole);
     }
     const int wave = threadIdx.x >> 6;
+    const uint32_t busy = nbig < gridDim.x ? nbig : gridDim.x;
+    if (uint32_t(wave) * gridDim.x + blockIdx.x >= nsmall + UB_WAVES * busy) return;
     double *mine = sort_lds + wave * (UB_WAVE_CAP * 3 / 2);
     const TeamLds own{mine, reinterpret_cast<uint32_t *>(mine + UB_WAVE_CAP), bins + wave * 64 * UB_BPER, nullptr,
                       nullptr};

@@ -84,3 +84,26 @@ def test_group_sizes(dtype, spread):
     assert compared >= len(roots) - 1
     again = call(pos, vel, lab, roots, without_records=True)
     assert np.array_equal(again[0], got) and np.array_equal(again[1], bound)
+
+
+@pytest.mark.parametrize("sizes", [(20,), (700,), (5000, 700, 20), (700,) * 3 + (20,) * 40, (20,) * 5000,
+                                   (700,) * 300 + (5000,) + (20,) * 100])
+def test_few_and_many_groups_of_each_kind(sizes):
+    """Fewer groups than workgroups or wavefronts, and more: every group is checked, as
+    it is alone."""
+    rng = np.random.default_rng(len(sizes))
+    roots = np.sort(rng.choice(N ** 3, len(sizes), replace=False)).astype(np.int32)
+    lab = np.repeat(roots, sizes)
+    centre = np.stack([lab % N, lab // N % N, lab // (N * N)], axis=1) * (L / N)
+    m = np.repeat(sizes, sizes)
+    pos = ((centre + rng.normal(scale=0.5, size=(len(lab), 3))) % L).astype(np.float32)
+    vel = (rng.normal(size=(len(lab), 3)) * (0.5 * np.sqrt(GM * m / 0.8))[:, None]).astype(np.float32)
+    got, bound = call(pos, vel, lab, roots)
+    assert set(bound.tolist()) <= {0, 1} and (got >= 0).any()
+    for k in np.unique(np.linspace(0, len(sizes) - 1, 8).astype(int)):
+        mine = np.flatnonzero(lab == roots[k])
+        alone, flag = call(pos[mine], vel[mine], lab[mine], roots[k:k + 1])
+        assert np.array_equal(got[mine], alone) and bound[k] == flag[0], sizes[k]
+    # no group kept: a list of roots that no label names keeps nothing
+    none, flags = call(pos[:0], vel[:0], lab[:0], roots)
+    assert none.size == 0 and not flags.any()

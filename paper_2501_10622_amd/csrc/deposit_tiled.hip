@@ -1127,9 +1127,10 @@ __global__ void __launch_bounds__(PART_THREADS) to_input_kernel(RunMaps m1, int6
 // ---------------------------------------------------------------- host side
 int tile_tx(int n) { return n % 64 == 0 ? 64 : (n % 32 == 0 ? 32 : 16); }
 
-// Tile and bucket shape for an n^3 grid; false if the binned form cannot hold it
-// (at most MAX_DIGITS tiles per bucket and MAX_DIGITS buckets).
-bool make_geom(const hf_box &box, Geom &out) {
+// Tile and bucket shape for an n^3 grid, with `keep` for a deposit whose particle
+// order is kept; false if the binned form cannot hold it (at most MAX_DIGITS tiles
+// per bucket and MAX_DIGITS buckets; the same grids with and without `keep`).
+bool make_geom(const hf_box &box, bool keep, Geom &out) {
     Geom g{};
     g.n = box.n;
     g.bits = box.frac_bits;
@@ -1141,13 +1142,15 @@ bool make_geom(const hf_box &box, Geom &out) {
     g.ntiles = g.ntx * g.nty * g.ntz;
     g.skirt = g.tx * AYZ + g.tx * TYZ;  // y and z faces
     // buckets of whole rows of tiles along x where that fits (the accumulation
-    // walks each row in order), then one bucket where it can hold every tile,
-    // else the smaller larger one of buckets and tiles per bucket, then the most
-    // cube-like bucket.  512^3: 128 buckets of 256 tiles against the fewest
-    // possible, 64 of 512: the labels' pass to level-1 order 1074 -> 902 us for
-    // three scales, the pass to input order 846 -> 911 us, level-1 scatter
-    // 841 -> 892 us; 1024^3 has one choice (512 of 512)
-    const bool one = g.ntiles <= MAX_DIGITS;
+    // walks each row in order), then the fewest, which is what the scatters like
+    // best, or, where the order is kept, one bucket where it can hold every tile, else
+    // the smaller larger one of buckets and tiles per bucket, which is what the way
+    // back likes best; then the most cube-like bucket.  512^3: 128 buckets of 256 tiles
+    // against the fewest possible, 64 of 512: the labels' pass to level-1 order 1074
+    // -> 902 us for three scales, the pass to input order 846 -> 911, but the scatters
+    // 776 + 633 -> 820 + 657 us and the histograms 697 -> 682; deposits alone at 300^3
+    // with four particles per cell 2.67 -> 2.74 ms.  1024^3 has one choice (512 of 512)
+    const bool few = !keep || g.ntiles <= MAX_DIGITS;
     long best_nb = -1;
     double best_shape = 0.0;
     auto search = [&](int bx_from) {
@@ -1164,7 +1167,7 @@ bool make_geom(const hf_box &box, Geom &out) {
                     const double lo = ex < ey ? (ex < ez ? ex : ez) : (ey < ez ? ey : ez);
                     const double shape = hi / lo;
                     const long tiles = long(bx) * by * bz;
-                    const long wide = one ? nb : (nb > tiles ? nb : tiles);
+                    const long wide = few ? nb : (nb > tiles ? nb : tiles);
                     if (best_nb < 0 || wide < best_nb || (wide == best_nb && shape < best_shape)) {
                         best_nb = wide;
                         best_shape = shape;
@@ -1370,7 +1373,7 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
                     char *ws, const ParticleOrder *order) {
     Geom g;  // on the padded grid where n is not a multiple of 16; the fixed point is the box's own
     const bool padded = padded_n(box.n) != box.n;
-    if (!make_geom(padded_box(box), g)) return HF_ERR_SIZE;
+    if (!make_geom(padded_box(box), order != nullptr, g)) return HF_ERR_SIZE;
     if (order && g.nbuckets < 2) return HF_ERR_ARG;  // no level-1 records to keep
     const DepLayout L = dep_layout(g, np, order != nullptr, padded);
     auto *rho = padded ? reinterpret_cast<unsigned long long *>(ws + L.pad) : rho_out;
@@ -1449,7 +1452,7 @@ hf_status run_tiled(hf_ctx *ctx, const hf_box &box, const T *pos, int64_t np, un
 template <typename T>
 hf_status run_group(hf_ctx *ctx, int n, int frac_bits, int count, const GroupBox *b) {
     Geom g;
-    if (!make_geom(hf_box{n, frac_bits, 1.0}, g)) return HF_ERR_SIZE;
+    if (!make_geom(hf_box{n, frac_bits, 1.0}, false, g)) return HF_ERR_SIZE;
     Boxes<uint32_t *, int64_t> zero{};
     Boxes<L2Input<T, false>, uint32_t *, uint32_t *> hist{};
     Boxes<ScanJob> scan{};
@@ -1498,7 +1501,7 @@ hf_status run_group(hf_ctx *ctx, int n, int frac_bits, int count, const GroupBox
 // One bucket, whole tiles, and the tiles' scan by one workgroup.
 bool hf::deposit_group_supported(int n, int frac_bits, int count, const GroupBox *b) {
     Geom g;
-    if (n % 16 || !make_geom(hf_box{n, frac_bits, 1.0}, g) || g.nbuckets != 1 || g.ntiles > SCAN_SMALL) return false;
+    if (n % 16 || !make_geom(hf_box{n, frac_bits, 1.0}, false, g) || g.nbuckets != 1 || g.ntiles > SCAN_SMALL) return false;
     for (int j = 0; j < count; ++j)
         if (!deposit_tiled_supported(hf_box{n, frac_bits, b[j].box_len}, b[j].np)) return false;
     return true;
@@ -1521,7 +1524,7 @@ bool hf::deposit_ws_optional(const hf_box &box) { return widened(box); }
 size_t hf::deposit_tiled_ws_bytes(const hf_box &box, int64_t np, bool keep_order) {
     Geom g;
     const bool padded = padded_n(box.n) != box.n;
-    return make_geom(padded_box(box), g) ? dep_layout(g, np, keep_order, padded).total : 0;
+    return make_geom(padded_box(box), keep_order, g) ? dep_layout(g, np, keep_order, padded).total : 0;
 }
 
 hf_status hf::deposit_tiled(hf_ctx *ctx, const hf_box &box, const void *pos, hf_dtype dtype, int64_t np,
@@ -1542,20 +1545,20 @@ constexpr int64_t ORDER_MIN = int64_t(1) << 23;
 bool hf::particle_order_supported(const hf_box &box, int64_t np) {
     Geom g;
     if (np < (particle_order_optional(box) ? ORDER_MIN : 1)) return false;
-    return deposit_tiled_supported(box, np) && make_geom(padded_box(box), g) && g.nbuckets > 1;
+    return deposit_tiled_supported(box, np) && make_geom(padded_box(box), true, g) && g.nbuckets > 1;
 }
 
 bool hf::particle_order_optional(const hf_box &box) { return padded_n(box.n) != box.n; }
 
 size_t hf::particle_order_bytes(const hf_box &box, int64_t np) {
     Geom g;
-    return make_geom(padded_box(box), g) ? order_layout(g, np).total : 0;
+    return make_geom(padded_box(box), true, g) ? order_layout(g, np).total : 0;
 }
 
 hf::ParticleOrder hf::particle_order_at(const hf_box &box, void *base, int64_t np) {
     Geom g;
     ParticleOrder o{};
-    if (!make_geom(padded_box(box), g)) return o;
+    if (!make_geom(padded_box(box), true, g)) return o;
     const OrderLayout L = order_layout(g, np);
     char *p = static_cast<char *>(base);
     o.rec2 = reinterpret_cast<uint64_t *>(p + L.rec2);
@@ -1578,7 +1581,7 @@ hf_status hf::label_tiles(hf_ctx *ctx, const hf_box &box, int64_t np, const Part
                           const int32_t *cell_label, void *scratch, uint32_t *parts) {
     if (np <= 0) return HF_OK;
     Geom g;
-    if (!make_geom(padded_box(box), g)) return HF_ERR_SIZE;
+    if (!make_geom(padded_box(box), true, g)) return HF_ERR_SIZE;
     auto *lab2 = static_cast<int32_t *>(scratch);
     if (parts)
         HF_LAUNCH(ctx, K_LABEL_TILES, tile_label_kernel<true>, dim3(g.ntiles), dim3(ACC_THREADS), 0, ctx->stream,
@@ -1594,7 +1597,7 @@ hf_status hf::label_back(hf_ctx *ctx, const hf_box &box, int64_t np, const Parti
                          const TileClaim *tile_claim) {
     if (np <= 0) return HF_OK;
     Geom g;
-    if (!make_geom(padded_box(box), g)) return HF_ERR_SIZE;
+    if (!make_geom(padded_box(box), true, g)) return HF_ERR_SIZE;
     auto *lab2 = static_cast<int32_t *>(scratch);
     auto *lab1 = reinterpret_cast<int32_t *>(static_cast<char *>(scratch) + align_up(sizeof(int32_t) * size_t(np)));
     const unsigned blocks = unsigned((np + CHUNK - 1) / CHUNK);

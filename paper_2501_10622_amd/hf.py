@@ -242,30 +242,38 @@ def context(device=None, stream=None) -> Context:
     return ctx
 
 
-def _allocate(asked: int, least: int, device) -> torch.Tensor:
-    """Bytes for a workspace: as many as the call asks for, or, where the device has
-    no room for those, the least that it takes."""
-    try:
-        return torch.empty(max(asked, 256), dtype=torch.uint8, device=device)
-    except torch.cuda.OutOfMemoryError:
-        if least >= asked:
-            raise
-        return torch.empty(max(least, 256), dtype=torch.uint8, device=device)
+class _WsSize:
+    """What a workspace size function asks for at its arguments, and the least."""
+
+    def __init__(self, call: str, *args):
+        self.call, self.args = call, args
+
+    def _query(self, name: str) -> int:
+        out = ctypes.c_size_t()
+        _check(getattr(load_library(), name)(*self.args, ctypes.byref(out)), name)
+        return out.value
+
+    def asked(self) -> int:
+        return self._query(self.call)
+
+    def least(self) -> int:
+        return self._query(f"{self.call}_least")
+
+    def allocate(self, device) -> torch.Tensor:
+        """As many bytes as the call asks for, or, where the device has no room for
+        those, the least that it takes."""
+        asked = self.asked()
+        try:
+            return torch.empty(max(asked, 256), dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            if self.least() >= asked:
+                raise
+            return torch.empty(max(self.least(), 256), dtype=torch.uint8, device=device)
 
 
-def _ws_sizes(call: str, *args) -> tuple:
-    """What ``call`` (a workspace size function) asks for, and the least."""
-    out = []
-    for name in (call, f"{call}_least"):
-        size = ctypes.c_size_t()
-        _check(getattr(load_library(), name)(*args, ctypes.byref(size)), name)
-        out.append(size.value)
-    return tuple(out)
-
-
-def workspace(nbytes: int, ctx: Context, least: int | None = None) -> torch.Tensor:
-    """A reusable device workspace of at least nbytes (or ``least`` where the device
-    has no room for those), one per (device, stream).
+def workspace(nbytes: int, ctx: Context, size: _WsSize | None = None) -> torch.Tensor:
+    """A reusable device workspace of at least nbytes (or the least of ``size`` where
+    the device has no room for those), one per (device, stream).
 
     It is allocated on the context's own stream, the only stream its kernels
     run on, so when a larger one replaces it the caching allocator cannot hand
@@ -274,12 +282,17 @@ def workspace(nbytes: int, ctx: Context, least: int | None = None) -> torch.Tens
     key = (ctx.device, ctx.stream.cuda_stream)
     cur = _ws.get(key)
     if cur is None or cur.numel() < nbytes:
-        # a kept one that has room for the least does where there is no room for more
-        least = nbytes if least is None else (0 if cur is not None and cur.numel() >= least else least)
         with torch.cuda.stream(ctx.stream):
-            new = _allocate(nbytes, least, torch.device("cuda", ctx.device))
-        if cur is None or new.numel() > cur.numel():
-            _ws[key] = cur = new
+            device = torch.device("cuda", ctx.device)
+            try:
+                cur = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+            except torch.cuda.OutOfMemoryError:
+                least = nbytes if size is None else size.least()
+                if least >= nbytes:
+                    raise
+                if cur is None or cur.numel() < least:
+                    cur = torch.empty(max(least, 256), dtype=torch.uint8, device=device)
+        _ws[key] = cur
     return cur
 
 
@@ -319,8 +332,9 @@ def deposit(pos: torch.Tensor, box_len: float, n: int, frac_bits: int = 15, out=
     if out is None:
         out = torch.empty((n, n, n), dtype=torch.int64, device=pos.device)
     b = box(n, box_len, frac_bits)
-    need, least = _ws_sizes("hf_workspace_size", ctypes.byref(b), pos.shape[0], STAGE_DEPOSIT)
-    ws = workspace(need, ctx, least) if need else None
+    size = _WsSize("hf_workspace_size", ctypes.byref(b), pos.shape[0], STAGE_DEPOSIT)
+    need = size.asked()
+    ws = workspace(need, ctx, size) if need else None
     _check(load_library().hf_deposit(ctx.handle, ctypes.byref(b), _ptr(pos), _dtype_code(pos), pos.shape[0],
                                      _ptr(out), _ptr(ws), min(need, ws.numel()) if need else 0), "hf_deposit")
     return out
@@ -576,7 +590,7 @@ def job_buffers(n: int, np_: int, device, with_cwt_ws: bool = True, frac_bits: i
     if with_stencil:  # the stencil transform's workspace instead of the FFT's (any n)
         stages = (stages & ~STAGE_CWT) | STAGE_STENCIL
     b = box(n, 1.0, frac_bits)
-    sizes = _ws_sizes("hf_workspace_size", ctypes.byref(b), int(np_), stages)
+    size = _WsSize("hf_workspace_size", ctypes.byref(b), int(np_), stages)
     cap = ((n + 1) // 2) ** 3
     extra = {}
     if with_groups:
@@ -593,7 +607,7 @@ def job_buffers(n: int, np_: int, device, with_cwt_ws: bool = True, frac_bits: i
         "count": torch.empty(1, dtype=torch.int64, device=device),
         "cell_label": torch.empty((n, n, n), dtype=torch.int32, device=device),
         "particle_label": torch.empty(max(np_, 1), dtype=torch.int32, device=device),
-        "ws": _allocate(*sizes, device),
+        "ws": size.allocate(device),
     }
 
 
@@ -627,7 +641,7 @@ def find_halos_noalloc_async(pos: torch.Tensor, box_len: float, n: int, kw: floa
 def scales_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) -> dict:
     """Outputs (one list entry per scale) and workspace for find_halos_scales_async."""
     b = box(n, 1.0, frac_bits)
-    sizes = _ws_sizes("hf_find_halos_scales_ws_size", ctypes.byref(b), int(np_), int(count))
+    size = _WsSize("hf_find_halos_scales_ws_size", ctypes.byref(b), int(np_), int(count))
     cap = ((n + 1) // 2) ** 3
     return {
         "rho": torch.empty((n, n, n), dtype=torch.int64, device=device),
@@ -636,7 +650,7 @@ def scales_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) ->
         "count": [torch.empty(1, dtype=torch.int64, device=device) for _ in range(count)],
         "cell_label": [torch.empty((n, n, n), dtype=torch.int32, device=device) for _ in range(count)],
         "particle_label": [torch.empty(max(np_, 1), dtype=torch.int32, device=device) for _ in range(count)],
-        "ws": _allocate(*sizes, device),
+        "ws": size.allocate(device),
     }
 
 
@@ -679,9 +693,8 @@ def identify_buffers(n: int, np_: int, count: int, device, frac_bits: int = 15) 
     bufs["halo_root"] = torch.empty(max(np_, 1), dtype=torch.int32, device=device)
     b = box(n, 1.0, frac_bits)
     jobs = _scale_jobs([1.0 + j for j in range(count)], bufs)
-    sizes = _ws_sizes("hf_identify_ws_size", ctypes.byref(b), int(np_), int(count), jobs)
     del bufs["ws"]  # that of the scales alone makes room
-    bufs["ws"] = _allocate(*sizes, device)
+    bufs["ws"] = _WsSize("hf_identify_ws_size", ctypes.byref(b), int(np_), int(count), jobs).allocate(device)
     return bufs
 
 
@@ -743,8 +756,8 @@ def identify_grids_buffers(grids, np_: int, device, box_len: float = 1.0, frac_b
         "halo_root": torch.empty(max(np_, 1), dtype=torch.int32, device=device),
     }
     jobs = _grid_scales([0.1 * (j + 1) for j in range(count)], bufs)
-    bufs["ws"] = _allocate(*_ws_sizes("hf_identify_grids_ws_size", float(box_len), int(frac_bits), int(np_), count, jobs,
-                                      int(bool(with_velocities))), device)
+    bufs["ws"] = _WsSize("hf_identify_grids_ws_size", float(box_len), int(frac_bits), int(np_), count, jobs,
+                         int(bool(with_velocities))).allocate(device)
     return bufs
 
 
@@ -784,8 +797,9 @@ def unbind(pos: torch.Tensor, vel: torch.Tensor, box_len: float, n: int, roots: 
         raise ValueError("roots and particle_label must be int32, group_keep uint8")
     ctx = ctx or context(pos.device.index)
     b = box(n, box_len, frac_bits)
-    need, least = _ws_sizes("hf_unbind_ws_size", ctypes.byref(b), pos.shape[0], roots.numel())
-    ws = workspace(need, ctx, least)
+    size = _WsSize("hf_unbind_ws_size", ctypes.byref(b), pos.shape[0], roots.numel())
+    need = size.asked()
+    ws = workspace(need, ctx, size)
     bound = torch.empty(max(roots.numel(), 1), dtype=torch.uint8, device=pos.device)[: roots.numel()]
     _check(load_library().hf_unbind(ctx.handle, ctypes.byref(b), _ptr(pos), _ptr(vel), _dtype_code(pos),
                                     pos.shape[0], _ptr(roots), roots.numel(), _ptr(group_keep),

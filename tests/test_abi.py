@@ -189,6 +189,11 @@ def test_cross_scale_rejects_before_any_device_call(lib):
     assert lib.hf_cross_scale(None, ctypes.byref(b), vp(0), 0, vp(0), 16, vp(0), vp(0)) == hf.HF_ERR_ARG
 
 
+def _sizes(*args):
+    size = hf._WsSize(*args)
+    return size.asked(), size.least()
+
+
 @pytest.mark.parametrize("n,np_", [(64, 300000), (96, 5), (101, 10 ** 6), (216, 1 << 23), (353, 5 * 10 ** 6),
                                    (972, 1 << 31), (1023, 1 << 30)])
 def test_least_workspaces(lib, n, np_):
@@ -196,21 +201,21 @@ def test_least_workspaces(lib, n, np_):
     b = hf.box(n, 50.0)
     padded = n % 16 != 0
     widened = n in (353, 972)  # no buckets for the tiles of their first multiple of 16
-    asked, least = hf._ws_sizes("hf_workspace_size", ctypes.byref(b), np_, hf.STAGE_DEPOSIT)
+    asked, least = _sizes("hf_workspace_size", ctypes.byref(b), np_, hf.STAGE_DEPOSIT)
     assert least == (0 if widened else asked)
-    asked, least = hf._ws_sizes("hf_workspace_size", ctypes.byref(b), np_, hf.STAGE_GROUPS)
+    asked, least = _sizes("hf_workspace_size", ctypes.byref(b), np_, hf.STAGE_GROUPS)
     assert least == 2 * ((4 * n ** 3 + 255) // 256 * 256) < asked
-    asked, least = hf._ws_sizes("hf_unbind_ws_size", ctypes.byref(b), np_, 100)
+    asked, least = _sizes("hf_unbind_ws_size", ctypes.byref(b), np_, 100)
     assert asked - least == (4 * np_ + 255) // 256 * 256 + (48 * np_ + 255) // 256 * 256
     grids = (hf.GridScale * 1)(hf.GridScale(0.1, n, *[0] * 3, 100))
     for velocities in (0, 1):
-        asked, least = hf._ws_sizes("hf_identify_grids_ws_size", 50.0, 15, np_, 1, grids, velocities)
+        asked, least = _sizes("hf_identify_grids_ws_size", 50.0, 15, np_, 1, grids, velocities)
         assert least < asked if velocities and np_ > n ** 3 else least <= asked
     if n in (64, 96, 216, 972):  # the transform's sizes
         for args in (("hf_workspace_size", ctypes.byref(b), np_, hf.STAGE_ALL),
                      ("hf_find_halos_scales_ws_size", ctypes.byref(b), np_, 2),
                      ("hf_identify_ws_size", ctypes.byref(b), np_, 1, (hf.ScaleJob * 1)(hf.ScaleJob(0.1, 0, 0, 100)))):
-            asked, least = hf._ws_sizes(*args)
+            asked, least = _sizes(*args)
             assert (least < asked) == (padded and np_ >= 1 << 23), args[0]
 
 
@@ -227,7 +232,7 @@ def test_the_least_workspace_where_the_device_has_no_more_room(lib, monkeypatch)
         return real(*size, **kw)
 
     monkeypatch.setattr(torch, "empty", empty)
-    asked, least = hf._ws_sizes("hf_unbind_ws_size", ctypes.byref(hf.box(32, 1.0)), 10 ** 6, 16 ** 3)
+    asked, least = _sizes("hf_unbind_ws_size", ctypes.byref(hf.box(32, 1.0)), 10 ** 6, 16 ** 3)
     limit = asked - 1
     grids = hf.identify_grids_buffers([32], 10 ** 6, "cpu", with_velocities=True)
     assert refused and least <= grids["ws"].numel() < refused[0]

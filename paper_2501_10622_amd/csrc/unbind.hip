@@ -179,16 +179,15 @@ __global__ void __launch_bounds__(UB_THREADS) ub_count_kernel(int32_t *__restric
 
 // One slot per member in its group's run (in the order the cursors give).  Where
 // the members have been counted before (guard), labels come as the loop over scales
-// left them: those of roots past the end of a list that is too short for its maxima
-// are among them, have no slot, and are reported and dropped, as ub_count_kernel does
-// where it runs.  With rec, the member's position and velocity are put into the slot too
+// left them: a listed root's only if its group is kept, but also those of roots past
+// the end of a list that is too short for its maxima, which have no slot, and are
+// reported and dropped, as ub_count_kernel does where it runs.  With rec, the member's position and velocity are put into the slot too
 // (6 values): here they stream by in input order, while the check would fetch
 // two lines from all over the arrays for every member and pass over them.
 template <typename T>
 __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restrict__ label, int64_t np, bool guard,
                                                                const int32_t *__restrict__ roots,
                                                                const int64_t *d_count, int64_t cap, int64_t ncells,
-                                                               const uint8_t *__restrict__ keep,
                                                                const uint32_t *__restrict__ slot,
                                                                const uint32_t *__restrict__ start,
                                                                uint32_t *__restrict__ cur, int32_t *__restrict__ pid,
@@ -199,8 +198,10 @@ __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restri
     for (int64_t p = blockIdx.x * int64_t(UB_THREADS) + threadIdx.x; p < np; p += int64_t(gridDim.x) * UB_THREADS) {
         const int32_t l = label[p];
         if (l < 0) continue;
-        if (guard && group_of(l, roots, nroots, ncells, slot, keep, bad) < 0) {
+        const uint32_t g = l < ncells ? slot[l] : 0xffffffffu;
+        if (guard && (int64_t(g) >= nroots || roots[g] != l)) {
             label[p] = -1;
+            bad = true;
             continue;
         }
         T v[6];
@@ -211,7 +212,6 @@ __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restri
                 v[3 + a] = vel[3 * p + a];
             }
         }
-        const uint32_t g = slot[l];
         const int64_t k = int64_t(start[g]) + atomicAdd(cur + g, 1u);
         if (guard && k >= int64_t(start[g + 1])) {  // more members than were counted: the run is full
             label[p] = -1;
@@ -1086,7 +1086,7 @@ hf_status hf::unbind_dev(hf_ctx *ctx, const hf_box &box, const void *pos, const 
     auto gather = [&](auto *p, auto *v) {
         using T = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
         HF_LAUNCH(ctx, K_UNBIND, ub_gather_kernel<T>, dim3(ub_grid(ctx, np)), dim3(UB_THREADS), 0, st, label, np,
-                  counted != nullptr, roots, d_count, nroots, ncells, keep, slot, start, cur, pid, p, v,
+                  counted != nullptr, roots, d_count, nroots, ncells, slot, start, cur, pid, p, v,
                   records ? reinterpret_cast<T *>(w + L.rec) : nullptr, ctx->d_status);
     };
     if (np > 0 && dtype == HF_F32) gather(static_cast<const float *>(pos), static_cast<const float *>(vel));

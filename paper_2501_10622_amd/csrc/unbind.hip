@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restri
 
 // The kept groups by size: the huge ones at the front of `big`, the middle ones
 // at its back, the small ones in `small` (no order within a list, none is
-// needed); bound_keep of the others is 0.  A workgroup gathers the groups of
+// needed); bound_keep of the others, and of those without a member, is 0.  A workgroup gathers the groups of
 // UB_LIST roots in LDS and reserves their places once per list: one counter
 // atomic per group took 158 us for the 15,841 groups of 2.5 million roots.
 constexpr int UB_LIST = 8 * UB_THREADS;
@@ -252,11 +252,11 @@ __global__ void __launch_bounds__(UB_THREADS) ub_list_kernel(const int64_t *d_co
             const int64_t g = g0 + u * UB_THREADS + threadIdx.x;
             list[u] = -1;
             if (g >= nroots) continue;
-            if (!keep[g]) {
+            const uint32_t m = start[g + 1] - start[g];
+            if (!keep[g] || m == 0u) {
                 bound_keep[g] = 0;
                 continue;
             }
-            const uint32_t m = start[g + 1] - start[g];
             list[u] = m > UB_HUGE ? Q_HUGE : (m > UB_WAVE_MOST ? Q_MID : Q_SMALL);
             at[u] = atomicAdd(&n[list[u]], 1u);
         }
@@ -994,8 +994,10 @@ __device__ void check_group(uint32_t g, const UnbindJob<T> &jb, const TeamLds &l
 // the middle groups from their list, one at a time; when it is empty, each
 // wavefront takes small groups for itself.  No more of either take than there may be
 // groups for (a wavefront per small group beside those of the workgroups that big
-// ones keep busy): the takes of 4096 wavefronts from one counter are 50 us, which a
-// launch with a few groups, or none, would last.
+// ones keep busy), and small groups go several to a take where there are many (eight
+// takes per wavefront, then): a take from the one counter is 12 ns, 50 us for 4096
+// wavefronts, which a launch with a few groups, or none, would last, and 7.6 ms for
+// 650,000 groups of a member or two.
 template <typename T>
 __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, const uint32_t *__restrict__ big,
                                                            int64_t cap, const uint32_t *__restrict__ small,
@@ -1023,12 +1025,14 @@ __global__ void __launch_bounds__(UB_TEAM) ub_group_kernel(UnbindJob<T> jb, cons
     double *mine = sort_lds + wave * (UB_WAVE_CAP * 3 / 2);
     const TeamLds own{mine, reinterpret_cast<uint32_t *>(mine + UB_WAVE_CAP), bins + wave * 64 * UB_BPER, nullptr,
                       nullptr};
+    const uint32_t share = nsmall / (8u * UB_WAVES * gridDim.x), batch = share < 1u ? 1u : (share < 64u ? share : 64u);
     for (;;) {
         uint32_t k = 0;
-        if ((threadIdx.x & 63) == 0) k = atomicAdd(queue + Q_TAKE_SMALL, 1u);
-        k = __shfl(k, 0, 64);
+        if ((threadIdx.x & 63) == 0) k = atomicAdd(queue + Q_TAKE_SMALL, batch);
+        k = uniform(__shfl(k, 0, 64));
         if (k >= nsmall) break;
-        check_group<1>(small[k], jb, own);
+        const uint32_t end = nsmall - k < batch ? nsmall : k + batch;
+        for (; k < end; ++k) check_group<1>(small[k], jb, own);
     }
 }
 

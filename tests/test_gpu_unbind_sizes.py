@@ -107,3 +107,30 @@ def test_few_and_many_groups_of_each_kind(sizes):
     # no group kept: a list of roots that no label names keeps nothing
     none, flags = call(pos[:0], vel[:0], lab[:0], roots)
     assert none.size == 0 and not flags.any()
+
+
+def test_many_small_groups_and_empty_ones():
+    """More groups than eight per wavefront, which go several to a take, as in parts
+    that do not; and kept groups without a member, which keep nothing."""
+    import paper_2501_10622_amd as hfm
+    n, box_len = 48, 48.0
+    rng = np.random.default_rng(4)
+    roots = np.arange(n ** 3, dtype=np.int32)
+    lab = np.concatenate([roots, roots[: n ** 3 // 2]])[rng.permutation(n ** 3 * 3 // 2)]
+    lab = lab[lab % 5 != 3]  # one root in five has no member, half of the others two
+    pos = np.stack([lab % n, lab // n % n, lab // (n * n)], axis=1) + rng.normal(scale=0.4, size=(len(lab), 3))
+    pos, vel = cuda((pos % box_len).astype(np.float32)), cuda(rng.normal(scale=0.03, size=pos.shape).astype(np.float32))
+    keep = torch.ones(n ** 3, dtype=torch.uint8, device="cuda")
+    keep[::7] = 0
+    whole = cuda(lab)
+    flags = hfm.unbind(pos, vel, box_len, n, cuda(roots), keep, whole, 1.0e-3, 1)
+    hfm.sync()
+    for part in np.array_split(roots, 8):
+        mine = torch.as_tensor(np.isin(lab, part)).cuda()
+        got = torch.where(mine, cuda(lab), -1)
+        kept = hfm.unbind(pos, vel, box_len, n, cuda(part), keep[part[0]:part[-1] + 1], got, 1.0e-3, 1)
+        hfm.sync()
+        assert torch.equal(got, torch.where(mine, whole, -1))
+        assert torch.equal(kept, flags[part[0]:part[-1] + 1])
+    some = torch.bincount(cuda(lab).long(), minlength=n ** 3) > 0
+    assert not flags[~some].any() and not flags[keep == 0].any() and bool(flags[some].any())

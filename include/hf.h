@@ -38,8 +38,9 @@
  *    stages and for the pipelines with HF_KERNEL_STENCIL (the flowchart's
  *    per-scale grids N_g are arbitrary integers).
  *    frac_bits (B, CIC fraction bits per axis) in [8, 20].
- *  - Workspaces are device buffers of at least hf_workspace_size() bytes,
- *    256-byte aligned.  One workspace may be reused by every stage in turn.
+ *  - Workspaces are device buffers of at least hf_workspace_size() bytes (or
+ *    hf_workspace_size_least(), slower), 256-byte aligned.  One workspace may be
+ *    reused by every stage in turn.
  *  - Argument errors are returned synchronously and nothing is enqueued.
  *    Errors found by kernels (overflow, capacity, bad input values) set a
  *    status word in the context; hf_sync() waits for the stream and returns
@@ -61,7 +62,7 @@ typedef enum {
     HF_OK = 0,
     HF_ERR_ARG = 1,       /* null pointer, bad enum, non-finite scale, bad count */
     HF_ERR_SIZE = 2,      /* n not supported (see above) or frac_bits out of range */
-    HF_ERR_WORKSPACE = 3, /* workspace smaller than hf_workspace_size or misaligned */
+    HF_ERR_WORKSPACE = 3, /* workspace smaller than the least size or misaligned */
     HF_ERR_OVERFLOW = 4,  /* device: a CIC cell exceeded 2^63 - 1 */
     HF_ERR_CAPACITY = 5,  /* device: more maxima than the list capacity */
     HF_ERR_DEVICE = 6,    /* HIP runtime failure */
@@ -302,9 +303,10 @@ hf_status hf_cwt_batch(hf_ctx *ctx, int32_t n, int32_t count, const hf_cwt_item 
  * particles into more than one bucket (more than 512 tiles of 16-64 x 8 x 8
  * cells, frac_bits <= 17, np < 2^32) on the grid itself, or from 2^23 particles
  * on a wider one (n no multiple of 16, for one), and the workspace has the size
- * asked for, the binned order is kept and step 6 runs through it: records are labelled tile by tile and the labels brought back
- * to input order, with the same result as hf_label.  Device-detected errors are
- * reported by hf_sync as for the separate calls. */
+ * asked for, the binned order is kept and step 6 runs through it: records are
+ * labelled tile by tile and the labels brought back to input order, with the same
+ * result as hf_label.  Device-detected errors are reported by hf_sync as for the
+ * separate calls. */
 typedef struct {
     const void *pos;         /* [np][3] positions */
     int64_t np;

@@ -181,9 +181,11 @@ __global__ void __launch_bounds__(UB_THREADS) ub_count_kernel(int32_t *__restric
 // the members have been counted before (guard), labels come as the loop over scales
 // left them: a listed root's only if its group is kept, but also those of roots past
 // the end of a list that is too short for its maxima, which have no slot, and are
-// reported and dropped, as ub_count_kernel does where it runs.  With rec, the member's position and velocity are put into the slot too
-// (6 values): here they stream by in input order, while the check would fetch
-// two lines from all over the arrays for every member and pass over them.
+// reported and dropped, as ub_count_kernel does where it runs (the lookups and the
+// run's end: 1.04 -> 1.20 ms for the three scales above).  With rec, the member's
+// position and velocity are put into the slot too (6 values): here they stream by in
+// input order, while the check would fetch two lines from all over the arrays for
+// every member and pass over them.
 template <typename T>
 __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restrict__ label, int64_t np, bool guard,
                                                                const int32_t *__restrict__ roots,
@@ -229,9 +231,10 @@ __global__ void __launch_bounds__(UB_THREADS) ub_gather_kernel(int32_t *__restri
 
 // The kept groups by size: the huge ones at the front of `big`, the middle ones
 // at its back, the small ones in `small` (no order within a list, none is
-// needed); bound_keep of the others, and of those without a member, is 0.  A workgroup gathers the groups of
-// UB_LIST roots in LDS and reserves their places once per list: one counter
-// atomic per group took 158 us for the 15,841 groups of 2.5 million roots.
+// needed); bound_keep of the others, and of those without a member, is 0.  A
+// workgroup gathers the groups of UB_LIST roots in LDS and reserves their places
+// once per list: one counter atomic per group took 158 us for the 15,841 groups of
+// 2.5 million roots.
 constexpr int UB_LIST = 8 * UB_THREADS;
 
 __global__ void __launch_bounds__(UB_THREADS) ub_list_kernel(const int64_t *d_count, int64_t cap,
